@@ -508,6 +508,26 @@ __device__ __forceinline__ void deposit_site(const Dev& D, const float* __restri
 // its cell), taken first over blocks of 4 x 4 x 4 cells from a table small
 // enough to stay in cache, then cell by cell.  Clamped coordinates and boxes
 // reaching beyond the grid are handled as the interpolation handles them.
+// Least entry of a table of nx x ny x .. cells over the box of cells [c0, c1].
+// Four rows are read at a time (a clamped row repeats the last one): one load
+// per round trip made the bound of a 4 x 8 x 15 box take most of a step's
+// melting.  An entry below `enough` ends the scan, the bound being negative
+// whatever the rest holds.
+__device__ __forceinline__ float table_min(const float* __restrict__ tab, size_t nx, size_t ny,
+                                           const int c0[3], const int c1[3], float enough) {
+  float m = INFINITY;
+  for (int k = c0[2]; k <= c1[2]; ++k)
+    for (int j = c0[1]; j <= c1[1]; j += 4) {
+      const float* r0 = tab + ((size_t)k * ny + j) * nx;
+      const float* r1 = tab + ((size_t)k * ny + min(j + 1, c1[1])) * nx;
+      const float* r2 = tab + ((size_t)k * ny + min(j + 2, c1[1])) * nx;
+      const float* r3 = tab + ((size_t)k * ny + min(j + 3, c1[1])) * nx;
+      for (int i = c0[0]; i <= c1[0]; ++i)
+        m = fminf(m, fminf(fminf(r0[i], r1[i]), fminf(r2[i], r3[i])));
+      if (m < enough) return m;
+    }
+  return m;
+}
 __device__ __forceinline__ float bound_margin(float m) { return m - 1e-5f * fabsf(m) - 1e-6f; }
 template <int PM = 2>
 __device__ bool may_melt(const Dev& D, P3 lo, P3 hi, float lin_c) {
@@ -549,17 +569,9 @@ __device__ bool may_melt(const Dev& D, P3 lo, P3 hi, float lin_c) {
   }
   const size_t cx = (size_t)D.fn[0] - 1, cy = (size_t)D.fn[1] - 1;
   const size_t kx = (cx + 3) >> 2, ky = (cy + 3) >> 2;
-  float m = INFINITY;
-  for (int k = c0[2] >> 2; k <= c1[2] >> 2; ++k)
-    for (int j = c0[1] >> 2; j <= c1[1] >> 2; ++j)
-      for (int i = c0[0] >> 2; i <= c1[0] >> 2; ++i)
-        m = fminf(m, D.fcoarse[((size_t)k * ky + j) * kx + i]);
-  if (bound_margin(m) - D.theta >= 0.0f) return false;
-  m = INFINITY;
-  for (int k = c0[2]; k <= c1[2]; ++k)
-    for (int j = c0[1]; j <= c1[1]; ++j)
-      for (int i = c0[0]; i <= c1[0]; ++i) m = fminf(m, D.fcmin[((size_t)k * cy + j) * cx + i]);
-  return bound_margin(m) - D.theta < 0.0f;
+  const int b0[3] = {c0[0] >> 2, c0[1] >> 2, c0[2] >> 2}, b1[3] = {c1[0] >> 2, c1[1] >> 2, c1[2] >> 2};
+  if (bound_margin(table_min(D.fcoarse, kx, ky, b0, b1, -INFINITY)) - D.theta >= 0.0f) return false;
+  return bound_margin(table_min(D.fcmin, cx, cy, c0, c1, D.theta)) - D.theta < 0.0f;
 }
 
 // Undercooling at the departure site of a record is negative (the site
@@ -2759,73 +2771,94 @@ __global__ __launch_bounds__(TPB) void k_resample(Bind Bd) {
 //      moving towards T (travel 0), and T is claimed as its target
 //      (k_walkback);
 //   4. a grain left without reached sites has melted entirely; its
-//      nucleation site is dormant again (k_melt_grains).
+//      nucleation site is dormant again (k_melt_stopped, first).
 // Work is confined by lower bounds of the field over boxes: a box whose
 // bound is not negative holds no melting site.
 
-// Least node value of each cell of a node grid.
+// Least node value of each cell of a node grid, and the least of those over
+// each block of 4 x 4 x 4 cells (clipped at the grid's end), in one pass: a
+// thread block takes 64 x 4 x 4 cells, a lane a column of four cells along z
+// (five node planes, each read once), and the coarse minima are formed from
+// the lanes' column minima by shuffles along x and through LDS along y.
+// Bound by the node reads and the cell minima written (8 B per cell).  One
+// thread per coarse block reading its 64 cells took 11.5 us at 24^3 nodes and
+// 20 us at 256^3, beside 4.7 and 50 us of the cell pass it followed.
 template <class Bind>
-__global__ __launch_bounds__(TPB) void k_field_cellmin(Bind Bd) {
-  Dev D;
-  VGrid V;
-  Bd.bind(D, V);
-  if (dead(D) || !(D.fkind == F_GRID || D.fkind == F_ROSENTHAL)) return;
-  const uint32_t cx = (uint32_t)D.fn[0] - 1u, cy = (uint32_t)D.fn[1] - 1u, cz = (uint32_t)D.fn[2] - 1u;
-  const uint64_t total = (uint64_t)cx * cy * cz;
-  const size_t sy = (size_t)D.fn[0], sz = (size_t)D.fn[0] * (size_t)D.fn[1];
-  GridWalk gw(cx, cy, (uint64_t)V.b * TPB + threadIdx.x, (uint64_t)V.G * TPB);
-  for (uint64_t v = gw.v; v < total; v = gw.next()) {
-    const size_t b = gw.k * sz + gw.j * sy + gw.i;
-    const float* g = D.fgrid;
-    float m = fminf(fminf(g[b], g[b + 1]), fminf(g[b + sy], g[b + sy + 1]));
-    m = fminf(m, fminf(fminf(g[b + sz], g[b + sz + 1]), fminf(g[b + sz + sy], g[b + sz + sy + 1])));
-    D.fcmin[v] = m;
-  }
-}
-
-// Least of the cell minima over each block of 4 x 4 x 4 cells (clipped at
-// the grid's end).
-template <class Bind>
-__global__ __launch_bounds__(TPB) void k_field_coarsemin(Bind Bd) {
+__global__ __launch_bounds__(TPB) void k_field_min(Bind Bd) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
   if (dead(D) || !(D.fkind == F_GRID || D.fkind == F_ROSENTHAL)) return;
   const uint32_t cx = (uint32_t)D.fn[0] - 1u, cy = (uint32_t)D.fn[1] - 1u, cz = (uint32_t)D.fn[2] - 1u;
   const uint32_t kx = (cx + 3u) >> 2, ky = (cy + 3u) >> 2, kz = (cz + 3u) >> 2;
-  const uint64_t total = (uint64_t)kx * ky * kz;
-  for (uint64_t v = (uint64_t)V.b * TPB + threadIdx.x; v < total; v += (uint64_t)V.G * TPB) {
-    const uint32_t i = (uint32_t)(v % kx), j = (uint32_t)((v / kx) % ky),
-                   k = (uint32_t)(v / ((uint64_t)kx * ky));
-    float m = INFINITY;
-    for (uint32_t c = 4u * k; c < min(4u * k + 4u, cz); ++c)
-      for (uint32_t b = 4u * j; b < min(4u * j + 4u, cy); ++b)
-        for (uint32_t a = 4u * i; a < min(4u * i + 4u, cx); ++a)
-          m = fminf(m, D.fcmin[((size_t)c * cy + b) * cx + a]);
-    D.fcoarse[v] = m;
+  const uint32_t tx = (cx + 63u) >> 6;
+  const size_t sy = (size_t)D.fn[0], sz = (size_t)D.fn[0] * (size_t)D.fn[1];
+  const uint32_t lx = threadIdx.x & 63u, ly = threadIdx.x >> 6;
+  __shared__ float s_min[4][16];
+  const uint64_t tiles = (uint64_t)tx * ky * kz;
+  for (uint64_t t = V.b; t < tiles; t += V.G) {
+    const uint32_t bx = (uint32_t)(t % tx), by = (uint32_t)((t / tx) % ky), bz = (uint32_t)(t / ((uint64_t)tx * ky));
+    const uint32_t i = 64u * bx + lx, j = 4u * by + ly;
+    float col = INFINITY;
+    if (i < cx && j < cy) {
+      const uint32_t k0 = 4u * bz, k1 = min(k0 + 4u, cz);
+      // Node planes k0 .. k1 of the column, repeated past its end.
+      float p[5];
+#pragma unroll
+      for (uint32_t q = 0; q < 5; ++q) {
+        const float* g = D.fgrid + min(k0 + q, k1) * sz + (size_t)j * sy + i;
+        p[q] = fminf(fminf(g[0], g[1]), fminf(g[sy], g[sy + 1]));
+      }
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q) {
+        if (k0 + q >= k1) break;
+        const float m = fminf(p[q], p[q + 1]);
+        D.fcmin[((size_t)(k0 + q) * cy + j) * cx + i] = m;
+        col = fminf(col, m);
+      }
+    }
+    col = fminf(col, __shfl_xor(col, 1));
+    col = fminf(col, __shfl_xor(col, 2));
+    if ((lx & 3u) == 0u) s_min[ly][lx >> 2] = col;
+    __syncthreads();
+    if (threadIdx.x < 16u) {
+      const uint32_t bi = 16u * bx + threadIdx.x;
+      if (bi < kx)
+        D.fcoarse[((size_t)bz * ky + by) * kx + bi] =
+            fminf(fminf(s_min[0][threadIdx.x], s_min[1][threadIdx.x]),
+                  fminf(s_min[2][threadIdx.x], s_min[3][threadIdx.x]));
+    }
+    __syncthreads();
   }
 }
 
 // Box of world positions holding every site of a brick (sites 0..7 of each
-// axis lie at most 4 lattice steps from site 3) or of one z layer of it
-// (half_z = 0), padded by half a lattice step against the rounding of the
-// site positions.
+// axis lie at most 4 lattice steps from site 3), padded by half a lattice
+// step against the rounding of the site positions.
 __device__ __forceinline__ void brick_box(const float* __restrict__ G, int bx, int by, int bz,
-                                          int w, float half_z, P3& lo, P3& hi) {
-  const P3 c = lattice_pos(G, bx * 8 + 3, by * 8 + 3, bz * 8 + w, 0, 0.0f);
-  const float ex = 4.5f * (fabsf(G[13]) + fabsf(G[14])) + half_z * fabsf(G[15]);
-  const float ey = 4.5f * (fabsf(G[16]) + fabsf(G[17])) + half_z * fabsf(G[18]);
-  const float ez = 4.5f * (fabsf(G[19]) + fabsf(G[20])) + half_z * fabsf(G[21]);
+                                          P3& lo, P3& hi) {
+  const P3 c = lattice_pos(G, bx * 8 + 3, by * 8 + 3, bz * 8 + 3, 0, 0.0f);
+  const float ex = 4.5f * (fabsf(G[13]) + fabsf(G[14]) + fabsf(G[15]));
+  const float ey = 4.5f * (fabsf(G[16]) + fabsf(G[17]) + fabsf(G[18]));
+  const float ez = 4.5f * (fabsf(G[19]) + fabsf(G[20]) + fabsf(G[21]));
   lo = P3{c.x - ex, c.y - ey, c.z - ez};
   hi = P3{c.x + ex, c.y + ey, c.z + ez};
 }
 
-// Occupied claim slots, from the list of their keys, in groups of 64 per
-// wave: each lane bounds the field over the brick of its key; the bricks
-// whose bound is negative are then taken one at a time by the whole wave, a
-// z layer of 64 sites per pass, one site per lane (the bit of a site in its
-// layer word is its lane).  The reached sites below zero undercooling melt;
-// a slot with melted sites goes to the walk-back list.
+// Occupied claim slots, from the list of their keys, shared out evenly among
+// the waves, up to 64 keys per wave at a time: each lane bounds the field
+// over the brick of its key, and the bricks whose bound is negative are then
+// taken one at a time by the whole wave, its 512 sites as eight layers of 64
+// (the bit of a site in its layer word is its lane).  The reached sites below
+// zero undercooling melt; a slot with melted sites goes to the walk-back list.
+//
+// With fewer keys than waves every wave has one key and tests its sites at
+// once: bounding a box costs one lane as many dependent rounds as the 64
+// lanes need for the sites themselves.  (Groups of 64 keys whatever their
+// number, with a bound per layer, left 414 keys to seven waves and took 1197
+// us per step at a 24^3 field.  A step of the scaled moving-source run went
+// from 1.78 to 0.16 ms, one at 3M active particles and 256^3 nodes from 1.50
+// to 1.36 ms, the wider reads of the bounds included.)
 template <class Bind>
 __global__ __launch_bounds__(TPB) void k_melt_sites(Bind Bd) {
   Dev D;
@@ -2840,17 +2873,21 @@ __global__ __launch_bounds__(TPB) void k_melt_sites(Bind Bd) {
   uint32_t melted = 0;
   const uint64_t used = min((uint64_t)D.cnt->claim_used, D.cmask + 1);
   const uint64_t waves = (uint64_t)V.G * (TPB / 64);
-  for (uint64_t base = ((uint64_t)V.b * (TPB / 64) + (threadIdx.x >> 6)) * 64; base < used;
-       base += waves * 64) {
+  const uint32_t per = (uint32_t)min((used + waves - 1) / waves, (uint64_t)64);
+  for (uint64_t base = ((uint64_t)V.b * (TPB / 64) + (threadIdx.x >> 6)) * per; base < used;
+       base += waves * per) {
     bool cand = false;
     unsigned long long key = CLAIM_EMPTY;
-    if (base + lane < used) {
+    if ((uint32_t)lane < per && base + lane < used) {
       key = D.clist[base + lane];
-      const float* G = D.gtab + (size_t)(key >> 36) * GT_STRIDE;
-      P3 lo, hi;
-      brick_box(G, (int)((key >> 24) & 0xFFFull) - 2048, (int)((key >> 12) & 0xFFFull) - 2048,
-                (int)(key & 0xFFFull) - 2048, 3, 4.5f, lo, hi);
-      cand = may_melt(D, lo, hi, lin_c);
+      cand = per == 1u;
+      if (!cand) {
+        const float* G = D.gtab + (size_t)(key >> 36) * GT_STRIDE;
+        P3 lo, hi;
+        brick_box(G, (int)((key >> 24) & 0xFFFull) - 2048, (int)((key >> 12) & 0xFFFull) - 2048,
+                  (int)(key & 0xFFFull) - 2048, lo, hi);
+        cand = may_melt(D, lo, hi, lin_c);
+      }
     }
     unsigned long long todo = __ballot(cand);
     while (todo) {
@@ -2868,17 +2905,21 @@ __global__ __launch_bounds__(TPB) void k_melt_sites(Bind Bd) {
       const int bz = (int)(key_c & 0xFFFull) - 2048;
       const float* G = D.gtab + (size_t)g * GT_STRIDE;
       unsigned long long* q = D.cbits + slot * 24;
+      unsigned long long rm[8];
+#pragma unroll
+      for (int w = 0; w < 8; ++w) rm[w] = q[CB_REACHED + w];
+      const int sx = bx * 8 + (lane & 7), sy = by * 8 + (lane >> 3);
+      uint32_t mine = 0;  // layers whose site of this lane melts
+#pragma unroll
+      for (int w = 0; w < 8; ++w) {
+        if (!((rm[w] >> lane) & 1ull)) continue;
+        if (field_at(D, lattice_pos(G, sx, sy, bz * 8 + w, 0, 0.0f), lin_c) - D.theta < 0.0f)
+          mine |= 1u << w;
+      }
+      if (!__any(mine != 0u)) continue;
       uint32_t n = 0;
       for (int w = 0; w < 8; ++w) {
-        const unsigned long long rm = q[CB_REACHED + w];
-        if (!rm) continue;
-        P3 lo, hi;
-        brick_box(G, bx, by, bz, w, 0.0f, lo, hi);
-        if (!may_melt(D, lo, hi, lin_c)) continue;
-        const int sx = bx * 8 + (lane & 7), sy = by * 8 + (lane >> 3), sz = bz * 8 + w;
-        bool melt = false;
-        if ((rm >> lane) & 1ull)
-          melt = field_at(D, lattice_pos(G, sx, sy, sz, 0, 0.0f), lin_c) - D.theta < 0.0f;
+        const bool melt = (mine >> w) & 1u;
         const unsigned long long mask = __ballot(melt);
         if (!mask) continue;
         if (lane == 0) {
@@ -2888,11 +2929,11 @@ __global__ __launch_bounds__(TPB) void k_melt_sites(Bind Bd) {
         }
         n += (uint32_t)__popcll(mask);
         if (melt && D.gcnt) {
-          const uint32_t cell = deposit_cell(D, G, sx, sy, sz);
+          const uint32_t cell = deposit_cell(D, G, sx, sy, bz * 8 + w);
           if (cell != NIL) atomicSub(&D.gcnt[cell], 1u);
         }
       }
-      if (n && lane == 0) {
+      if (lane == 0) {
         atomicSub(&D.greach[g], n);
         melted += n;
         D.mslots[atomicAdd(&D.cnt->n_melt_slots, 1u)] = (uint32_t)slot;
@@ -2981,25 +3022,6 @@ __global__ __launch_bounds__(TPB) void k_walkback(Bind Bd) {
   if (threadIdx.x == 0 && s_new) atomicAdd(&D.cnt->reactivated, (unsigned long long)s_new);
 }
 
-// Grains left without reached sites have melted entirely: their nucleation
-// sites are dormant again.
-template <class Bind>
-__global__ __launch_bounds__(TPB) void k_melt_grains(Bind Bd) {
-  Dev D;
-  VGrid V;
-  Bd.bind(D, V);
-  if (dead(D)) return;
-  const uint32_t ng = D.cnt->n_grains;
-  for (uint32_t g = V.b * TPB + threadIdx.x; g < ng; g += V.G * TPB) {
-    if (D.gdead[g] || D.greach[g] != 0u) continue;
-    D.gdead[g] = 1u;
-    atomicAdd(&D.cnt->grains_melted, 1ull);
-    const int32_t si = D.gsite[g];
-    if (si >= 0) D.sstate[si] = SITE_DORMANT;
-  }
-  if (V.b == 0 && threadIdx.x == 0) D.cnt->n_melt_slots = 0;
-}
-
 // Stopped particles whose departure site melted are removed: the record is
 // retired and its position made NaN, so that no test meets it; the re-sort
 // drops it.  The cell-sorted prefix of the store is taken brick by brick:
@@ -3031,6 +3053,17 @@ __global__ __launch_bounds__(TPB) void k_melt_stopped(Bind Bd) {
   if (threadIdx.x == 0) s_rm = 0;
   __syncthreads();
   uint32_t rm = 0;
+  // Grains left without reached sites have melted entirely: their nucleation
+  // sites are dormant again.  (The walk-back is done: its list is emptied.)
+  const uint32_t ng = D.cnt->n_grains;
+  for (uint32_t g = V.b * TPB + threadIdx.x; g < ng; g += V.G * TPB) {
+    if (D.gdead[g] || D.greach[g] != 0u) continue;
+    D.gdead[g] = 1u;
+    atomicAdd(&D.cnt->grains_melted, 1ull);
+    const int32_t si = D.gsite[g];
+    if (si >= 0) D.sstate[si] = SITE_DORMANT;
+  }
+  if (V.b == 0 && threadIdx.x == 0) D.cnt->n_melt_slots = 0;
   const uint32_t n = min(D.cnt->n_stopped, D.cap_s);
   const uint32_t ns = min(D.cnt->n_sorted, n);
   const uint32_t nb = D.n_bricks;
@@ -3830,13 +3863,11 @@ void launch_mushy_fraction(const uint32_t* cnt, uint64_t n, double site_over_cel
 void launch_melt(const Dev& d, hipStream_t s) {
   if (d.fkind == F_GRID || d.fkind == F_ROSENTHAL) {
     const uint64_t c[3] = {(uint64_t)d.fn[0] - 1, (uint64_t)d.fn[1] - 1, (uint64_t)d.fn[2] - 1};
-    k_field_cellmin<<<grid_for(c[0] * c[1] * c[2], 8192), TPB, 0, s>>>(Plain{d});
-    k_field_coarsemin<<<grid_for(((c[0] + 3) >> 2) * ((c[1] + 3) >> 2) * ((c[2] + 3) >> 2), 2048),
-                        TPB, 0, s>>>(Plain{d});
+    const uint64_t tiles = ((c[0] + 63) >> 6) * ((c[1] + 3) >> 2) * ((c[2] + 3) >> 2);
+    k_field_min<<<(unsigned)std::min<uint64_t>(tiles, 16384), TPB, 0, s>>>(Plain{d});
   }
   k_melt_sites<<<grid_for(d.cmask + 1, 16384), TPB, 0, s>>>(Plain{d});
   k_walkback<<<1024, TPB, 0, s>>>(Plain{d});
-  k_melt_grains<<<grid_for(d.cap_grains, 256), TPB, 0, s>>>(Plain{d});
   k_melt_stopped<<<STREAM_GRID, TPB, 0, s>>>(Plain{d});
 }
 void launch_count_reached(const Dev& d, hipStream_t s) {

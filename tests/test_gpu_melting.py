@@ -127,6 +127,43 @@ def test_plane_cut_at_the_box_face_matches_the_oracle(kind):
     ctx.close()
 
 
+@pytest.mark.parametrize("n", [(2, 2, 2), (3, 6, 5), (66, 9, 18), (130, 5, 7)])
+@pytest.mark.parametrize("bricks", [1024, 1 << 14])
+def test_plane_cut_on_node_grids(n, bricks):
+    """A plane cut on node grids whose cells end inside a block of the field
+    minima (one cell, a part of a block of four, just past 64 and 128 along
+    x), with fewer claim bricks than waves and with several per wave: claims
+    and particles as sets equal the oracle's."""
+    require_gpu()
+    r, cut, G = 16, 3, 1e4
+    x_cut = C[0] + (cut + 0.5) * LAM
+    sp = tuple(1e-3 / (m - 1) for m in n)
+    x = np.arange(n[0]) * sp[0]
+    data = np.broadcast_to((G * (x_cut - x)).astype(np.float32), (n[2], n[1], n[0]))
+    f = W.Field(W.FIELD_GRID, n=n, origin=(0.0, 0.0, 0.0), spacing=sp,
+                data=np.ascontiguousarray(data))
+    q = np.array([[1.0, 0, 0, 0]])
+    p = B.make_params(BOX[0], BOX[1], LAM, LAM, LAM, W.KIN_A, W.KIN_B, cap_particles=1 << 14,
+                      cap_stopped=1 << 14, cap_claim_bricks=bricks, field_n=n)
+    ctx = B.Context(p)
+    ctx.set_thermal_field(f)
+    ctx.init_grains(C[None, :], q, np.array([r], np.int32))
+    ctx.set_melting(True)
+    st = ctx.step(1e-4, 1)
+    o = _orc(f)
+    o.init_grains(C[None, :], q, np.array([r], np.int32))
+    o.set_melting(True)
+    o.step(1e-4, 1)
+    assert st["melted"] == o.melt_stats()["melted"] > 500
+    gc, _ = gpu_claims(ctx)
+    oc, _ = orc_claims(o)
+    assert _claim_set(gc) == _claim_set(oc)
+    gp, _ = gpu_parts(ctx)
+    op, _ = orc_parts(o)
+    assert _part_set(gp) == _part_set(op)
+    ctx.close()
+
+
 def test_uniform_superheat_melts_the_grain():
     require_gpu()
     ctx = _ctx(W.Field(W.FIELD_UNIFORM, dT=-1.0))
