@@ -3437,46 +3437,148 @@ __global__ __launch_bounds__(TPB) void k_claim_slots(Bind Bd, const SlotOut* in,
 
 // Grain map: voxel centre y takes the grain whose reached site is y's rounded
 // lattice position; nearest such site wins, then the lower grain.
+//
+// A block takes a tile of MAP_X x 4 ty x 4 tz voxels and lists the grains
+// whose lattice bounding box meets the tile (in the grain's own frame: the
+// tile's centre and half widths there, a lattice step of margin for the
+// rounding to sites and of the arithmetic).  Each sub-tile of 256 voxels, one
+// per thread, narrows that list in chunks of 256 and tests what is left, in
+// the order of the grains.  Bound by those tests and the directory probes
+// behind them: 408 us for 8M voxels and 760 grains, 22 us for 432k voxels and 8
+// grains with two periodic axes, where the loop over every grain at every
+// voxel took 6057 and 130 us.
+constexpr uint32_t MAP_X = 16, MAP_LIST = 1024;
+struct MapTile {
+  P3 c, h;  // centre and half widths of the voxel centres
+};
+// Grain (and image of the voxels, with periodic axes) number q: entries of
+// one grain are consecutive, so that list order is grain order.
+struct MapEntry {
+  uint32_t g;
+  int image;  // 13: the voxel itself
+};
+__device__ __forceinline__ MapEntry map_entry(const Dev& D, uint32_t q) {
+  if (!D.periodic) return {q, 13};
+  return {q / 27u, (int)(q % 27u)};
+}
+__device__ __forceinline__ bool map_meets(const Dev& D, float inv_l, const MapTile& t, uint32_t q) {
+  const MapEntry e = map_entry(D, q);
+  P3 c = t.c;
+  if (D.periodic && !image_of(D, t.c, e.image, c)) return false;
+  const float* G = D.gtab + (size_t)e.g * GT_STRIDE;
+  const int32_t* bb = D.gbox + (size_t)e.g * 6;
+  const float dx = c.x - G[0], dy = c.y - G[1], dz = c.z - G[2];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float l = (G[4 + k] * dx + G[7 + k] * dy + G[10 + k] * dz) * inv_l;
+    const float h = (fabsf(G[4 + k]) * t.h.x + fabsf(G[7 + k]) * t.h.y + fabsf(G[10 + k]) * t.h.z) * inv_l;
+    const float w = 1.0001f * h + 1e-5f * fabsf(l) + 1.0f;
+    if (l + w < (float)bb[k] || l - w > (float)bb[3 + k]) return false;
+  }
+  return true;
+}
+// Rank of this thread's entry among those with `take` set, in thread order.
+__device__ __forceinline__ uint32_t block_rank(bool take, uint32_t* wcnt, uint32_t& total) {
+  const unsigned long long m = __ballot(take);
+  const uint32_t w = threadIdx.x >> 6;
+  if (lane_id() == 0) wcnt[w] = (uint32_t)__popcll(m);
+  __syncthreads();
+  uint32_t r = (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull));
+  total = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < TPB / 64; ++k) {
+    if (k < w) r += wcnt[k];
+    total += wcnt[k];
+  }
+  __syncthreads();
+  return r;
+}
+
 template <class Bind>
-__global__ __launch_bounds__(TPB) void k_grain_map(Bind Bd, int32_t n0, int32_t n1, int32_t n2,
+__global__ __launch_bounds__(TPB) void k_grain_map(Bind Bd, uint32_t n0, uint32_t n1, uint32_t n2,
                                                    float o0, float o1, float o2, float s0, float s1,
-                                                   float s2, uint32_t* out) {
+                                                   float s2, uint32_t ty, uint32_t tz, uint32_t* out) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
-  const uint64_t total = (uint64_t)n0 * n1 * n2;
-  const uint32_t ng = D.cnt->n_grains;
+  __shared__ uint32_t s_list[MAP_LIST], s_sub[TPB], s_cnt[TPB / 64];
+  const uint32_t ng = D.cnt->n_grains * (D.periodic ? 27u : 1u);
   const float inv_l = 1.0f / D.lambda0;
-  for (uint64_t v = (uint64_t)V.b * TPB + threadIdx.x; v < total;
-       v += (uint64_t)V.G * TPB) {
-    const uint64_t i = v % (uint64_t)n0, j = (v / (uint64_t)n0) % (uint64_t)n1,
-                   k = v / ((uint64_t)n0 * n1);
-    const P3 y = {o0 + ((float)i + 0.5f) * s0, o1 + ((float)j + 0.5f) * s1,
-                  o2 + ((float)k + 0.5f) * s2};
-    uint32_t best = 0;
-    float bd = INFINITY;
-    for (uint32_t g = 0; g < ng; ++g) {
-      const float* G = D.gtab + (size_t)g * GT_STRIDE;
-      // The voxel centre and, with periodic axes, its images.
-      for (int k = 0; k < (D.periodic ? 27 : 1); ++k) {
-        P3 yi = y;
-        if (D.periodic && !image_of(D, y, k, yi)) continue;
-        int l[3];
-        lattice_round(G, inv_l, yi, l);
-        const int32_t* bb = D.gbox + (size_t)g * 6;
-        if (l[0] < bb[0] || l[1] < bb[1] || l[2] < bb[2] || l[0] > bb[3] || l[1] > bb[4] ||
-            l[2] > bb[5])
-          continue;
-        if (!claim_test(D, g, l[0], l[1], l[2], M_REACHED)) continue;
-        const P3 ps = lattice_pos(G, l[0], l[1], l[2], 0, 0.0f);
-        const float d = dist2(yi, ps);
-        if (d < bd) {
-          bd = d;
-          best = g + 1;
-        }
-      }
+  const uint32_t b0 = (n0 + MAP_X - 1u) / MAP_X, b1 = (n1 + 4u * ty - 1u) / (4u * ty),
+                 b2 = (n2 + 4u * tz - 1u) / (4u * tz);
+  const uint64_t tiles = (uint64_t)b0 * b1 * b2;
+  // Tile of nx x ny x nz voxels from voxel (i, j, k).
+  auto tile = [&](uint32_t i, uint32_t j, uint32_t k, uint32_t ny, uint32_t nz) {
+    MapTile t;
+    t.h = P3{0.5f * (float)(MAP_X - 1u) * s0, 0.5f * (float)(ny - 1u) * s1, 0.5f * (float)(nz - 1u) * s2};
+    t.c = P3{o0 + ((float)i + 0.5f) * s0 + t.h.x, o1 + ((float)j + 0.5f) * s1 + t.h.y,
+             o2 + ((float)k + 0.5f) * s2 + t.h.z};
+    return t;
+  };
+  for (uint64_t v = V.b; v < tiles; v += V.G) {
+    const uint32_t i0 = (uint32_t)(v % b0) * MAP_X, j0 = (uint32_t)((v / b0) % b1) * 4u * ty,
+                   k0 = (uint32_t)(v / ((uint64_t)b0 * b1)) * 4u * tz;
+    const MapTile T = tile(i0, j0, k0, 4u * ty, 4u * tz);
+    uint32_t n_list = 0;
+    for (uint32_t q0 = 0; q0 < ng && n_list <= MAP_LIST; q0 += TPB) {
+      const uint32_t q = q0 + threadIdx.x;
+      const bool take = q < ng && map_meets(D, inv_l, T, q);
+      uint32_t tot;
+      const uint32_t r = n_list + block_rank(take, s_cnt, tot);
+      if (take && r < MAP_LIST) s_list[r] = q;
+      n_list += tot;
     }
-    out[v] = best;
+    __syncthreads();
+    // A list that does not fit is not used: every entry is tried.
+    const bool listed = n_list <= MAP_LIST;
+    const uint32_t n_src = listed ? n_list : ng;
+    for (uint32_t sub = 0; sub < ty * tz; ++sub) {
+      const uint32_t j1 = j0 + 4u * (sub % ty), k1 = k0 + 4u * (sub / ty);
+      if (j1 >= n1 || k1 >= n2) continue;
+      const uint32_t i = i0 + threadIdx.x % MAP_X, j = j1 + ((threadIdx.x / MAP_X) & 3u),
+                     k = k1 + threadIdx.x / (4u * MAP_X);
+      const bool valid = i < n0 && j < n1 && k < n2;
+      const P3 y = {o0 + ((float)i + 0.5f) * s0, o1 + ((float)j + 0.5f) * s1,
+                    o2 + ((float)k + 0.5f) * s2};
+      const MapTile S = tile(i0, j1, k1, 4u, 4u);
+      uint32_t best = 0;
+      float bd = INFINITY;
+      for (uint32_t c0 = 0; c0 < n_src; c0 += TPB) {
+        uint32_t q = 0;
+        bool take = false;
+        if (c0 + threadIdx.x < n_src) {
+          q = listed ? s_list[c0 + threadIdx.x] : c0 + threadIdx.x;
+          take = map_meets(D, inv_l, S, q);
+        }
+        uint32_t n_sub;
+        const uint32_t r = block_rank(take, s_cnt, n_sub);
+        if (take) s_sub[r] = q;
+        __syncthreads();
+        for (uint32_t t = 0; t < n_sub; ++t) {
+          const MapEntry e = map_entry(D, uniform_u32(s_sub[t]));
+          const float* G = D.gtab + (size_t)e.g * GT_STRIDE;
+          P3 yi = y;
+          if (!valid || (D.periodic && !image_of(D, y, e.image, yi))) continue;
+          int l[3];
+          lattice_round(G, inv_l, yi, l);
+          const int32_t* bb = D.gbox + (size_t)e.g * 6;
+          if (l[0] < bb[0] || l[1] < bb[1] || l[2] < bb[2] || l[0] > bb[3] || l[1] > bb[4] ||
+              l[2] > bb[5])
+            continue;
+          // Nothing is claimed during a query: the reads may be cached.
+          BlockCache bc{~0ull, -1};
+          if (!cached_test(D, bc, e.g, l[0], l[1], l[2], M_REACHED)) continue;
+          const P3 ps = lattice_pos(G, l[0], l[1], l[2], 0, 0.0f);
+          const float d = dist2(yi, ps);
+          if (d < bd) {
+            bd = d;
+            best = e.g + 1;
+          }
+        }
+        __syncthreads();
+      }
+      if (valid) out[((size_t)k * n1 + j) * n0 + i] = best;
+    }
   }
 }
 
@@ -3959,10 +4061,20 @@ void launch_export_claims(const Dev& d, uint32_t* counter, void* out, uint32_t c
 }
 void launch_grain_map(const Dev& d, const int32_t n[3], const float origin[3],
                       const float spacing[3], uint32_t* out, hipStream_t s) {
-  const uint64_t total = (uint64_t)n[0] * n[1] * n[2];
-  k_grain_map<<<grid_for(total, 8192), TPB, 0, s>>>(Plain{d}, n[0], n[1], n[2], origin[0], origin[1],
-                                                    origin[2], spacing[0], spacing[1], spacing[2],
-                                                    out);
+  // Sub-tiles per block: 16 while that leaves eight blocks for every compute
+  // unit, then 4, then 1 (a list is formed once per block, but the blocks have
+  // to fill the chip).
+  const uint32_t nv[3] = {(uint32_t)n[0], (uint32_t)n[1], (uint32_t)n[2]};
+  uint32_t t = 4;
+  uint64_t tiles = 0;
+  for (;; t >>= 1) {
+    tiles = (uint64_t)((nv[0] + MAP_X - 1u) / MAP_X) * (uint64_t)((nv[1] + 4u * t - 1u) / (4u * t)) *
+            (uint64_t)((nv[2] + 4u * t - 1u) / (4u * t));
+    if (t == 1u || tiles >= 2048u) break;
+  }
+  k_grain_map<<<(unsigned)std::min<uint64_t>(tiles, 1u << 20), TPB, 0, s>>>(
+      Plain{d}, nv[0], nv[1], nv[2], origin[0], origin[1], origin[2], spacing[0], spacing[1],
+      spacing[2], t, t, out);
 }
 void launch_digest(const Dev& d, unsigned long long* out, hipStream_t s) {
   k_digest<<<2048, TPB, 0, s>>>(Plain{d}, out);
