@@ -480,19 +480,24 @@ __device__ __forceinline__ void bbox_add(const Dev& D, uint32_t g, int sx, int s
 // crystal-frame cube (lambda0^3) to the deposition cell holding its centre;
 // cell (i, j, k) is the node-centred box of node (i, j, k) of the deposition
 // grid.  FP32, single-rounded: i = floor((x - origin) * inv_spacing + 1/2).
+// Cell indices (as floats) of a site; false outside the grid.
+__device__ __forceinline__ bool deposit_coords(const Dev& D, const float* __restrict__ G, int sx,
+                                               int sy, int sz, float f[3]) {
+  const P3 x = place(D, lattice_pos(G, sx, sy, sz, 0, 0.0f)).p;
+  const float xs[3] = {x.x, x.y, x.z};
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    f[a] = floorf((xs[a] - D.go[a]) * D.ginv[a] + 0.5f);
+    if (!(f[a] >= 0.0f && f[a] < (float)D.gn[a])) return false;
+  }
+  return true;
+}
 // Deposition cell of a site, or NIL outside the grid.
 __device__ __forceinline__ uint32_t deposit_cell(const Dev& D, const float* __restrict__ G, int sx,
                                                  int sy, int sz) {
-  const P3 x = place(D, lattice_pos(G, sx, sy, sz, 0, 0.0f)).p;
-  const float xs[3] = {x.x, x.y, x.z};
-  uint32_t idx[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const float f = floorf((xs[a] - D.go[a]) * D.ginv[a] + 0.5f);
-    if (!(f >= 0.0f && f < (float)D.gn[a])) return NIL;
-    idx[a] = (uint32_t)f;
-  }
-  return (idx[2] * (uint32_t)D.gn[1] + idx[1]) * (uint32_t)D.gn[0] + idx[0];
+  float f[3];
+  if (!deposit_coords(D, G, sx, sy, sz, f)) return NIL;
+  return ((uint32_t)f[2] * (uint32_t)D.gn[1] + (uint32_t)f[1]) * (uint32_t)D.gn[0] + (uint32_t)f[0];
 }
 __device__ __forceinline__ void deposit_site(const Dev& D, const float* __restrict__ G, int sx,
                                              int sy, int sz) {
@@ -3599,32 +3604,108 @@ __global__ __launch_bounds__(TPB) void k_solute_nodes(const double* __restrict__
     out[k] = (float)((liq_T + liq_m * w[k]) - T[k]);
 }
 
-// Deposition counts from the whole claim hash (every reached site), after
-// the counts were cleared: one lane per (slot, z-layer) word.
+// Deposition counts from the claims (every reached site), after the counts
+// were cleared: one wave per occupied slot of the list of claim keys, a z
+// layer of 64 sites per pass, one site per lane (the bit of a site in its
+// layer word is its lane).  The sites of a slot lie in few cells: the wave
+// counts them in LDS over the box of cells that holds the slot (its centre
+// and half widths, with half a lattice step to spare against rounding) and
+// adds that box to the grid once.  Boxes of more than DEP_BOX cells, and
+// contexts with periodic axes (whose positions wrap), take a table of cells
+// in registers, one cell and its count per lane, filled by one ballot per
+// distinct cell of a layer.
+//
+// Bound by the site arithmetic and the counting.  272k slots (33M sites) of a
+// moving-source state took 2666 us with an atomic on the grid per site and a
+// lane's 64 sites one after another, 388 us with the register table alone,
+// 250 us now.
+constexpr int DEP_BOX = 256;
 template <class Bind>
 __global__ __launch_bounds__(TPB) void k_deposit_all(Bind Bd) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
-  const uint64_t slots = D.cmask + 1;
-  for (uint64_t v = (uint64_t)V.b * TPB + threadIdx.x; v < slots * 8;
-       v += (uint64_t)V.G * TPB) {
-    const uint64_t slot = v >> 3;
-    const uint32_t w = (uint32_t)(v & 7u);
-    const unsigned long long key = D.ckeys[slot];
-    if (key == CLAIM_EMPTY) continue;
-    unsigned long long rm = D.cbits[slot * 24 + CB_REACHED + w];
-    if (!rm) continue;
-    const uint32_t g = (uint32_t)(key >> 36);
+  __shared__ uint32_t s_box[TPB / 64][DEP_BOX];
+  const int lane = lane_id();
+  uint32_t* box = s_box[threadIdx.x >> 6];
+  for (int t = lane; t < DEP_BOX; t += 64) box[t] = 0u;
+  wave_lds_sync();
+  const uint64_t used = min((uint64_t)D.cnt->claim_used, D.cmask + 1);
+  const uint64_t waves = (uint64_t)V.G * (TPB / 64);
+  for (uint64_t k = (uint64_t)V.b * (TPB / 64) + (threadIdx.x >> 6); k < used; k += waves) {
+    const unsigned long long key = D.clist[k];
+    const int64_t blk = block_find<true>(D, claim_block_key(key));
+    if (blk < 0) continue;  // listed keys are in the hash: never taken
+    const unsigned long long* q =
+        D.cbits + ((uint64_t)blk * CLAIM_BLOCK_SLOTS + claim_fine(key)) * 24;
+    unsigned long long rm[8];
+#pragma unroll
+    for (int z = 0; z < 8; ++z) rm[z] = q[CB_REACHED + z];
     const int bx = (int)((key >> 24) & 0xFFFull) - 2048;
     const int by = (int)((key >> 12) & 0xFFFull) - 2048;
     const int bz = (int)(key & 0xFFFull) - 2048;
-    const float* G = D.gtab + (size_t)g * GT_STRIDE;
-    while (rm) {
-      const int bit = __ffsll((long long)rm) - 1;
-      rm &= rm - 1ull;
-      deposit_site(D, G, bx * 8 + (bit & 7), by * 8 + ((bit >> 3) & 7), bz * 8 + (int)w);
+    const float* G = D.gtab + (size_t)uniform_u32((uint32_t)(key >> 36)) * GT_STRIDE;
+    const int sx = bx * 8 + (lane & 7), sy = by * 8 + (lane >> 3);
+    // The box of cells of the slot, clipped to the grid.
+    P3 lo, hi;
+    brick_box(G, bx, by, bz, lo, hi);
+    const float l[3] = {lo.x, lo.y, lo.z}, h[3] = {hi.x, hi.y, hi.z};
+    float c0[3], m[3];
+    bool off = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      c0[a] = fmaxf(floorf((l[a] - D.go[a]) * D.ginv[a] + 0.5f), 0.0f);
+      const float c1 = fminf(floorf((h[a] - D.go[a]) * D.ginv[a] + 0.5f), (float)(D.gn[a] - 1));
+      m[a] = c1 - c0[a] + 1.0f;
+      off |= !(m[a] >= 1.0f);
     }
+    if (!D.periodic && (off || m[0] * m[1] * m[2] <= (float)DEP_BOX)) {
+      if (off) continue;
+#pragma unroll
+      for (int z = 0; z < 8; ++z) {
+        float f[3];
+        if (((rm[z] >> lane) & 1ull) && deposit_coords(D, G, sx, sy, bz * 8 + z, f))
+          atomicAdd(&box[(int)(((f[2] - c0[2]) * m[1] + (f[1] - c0[1])) * m[0] + (f[0] - c0[0]))], 1u);
+      }
+      wave_lds_sync();
+      const int m0 = (int)m[0], m01 = m0 * (int)m[1], n = m01 * (int)m[2];
+      for (int t = lane; t < n; t += 64) {
+        const uint32_t v = box[t];
+        if (!v) continue;
+        box[t] = 0u;
+        const int z = t / m01, y = (t - z * m01) / m0, x = t - z * m01 - y * m0;
+        atomicAdd(&D.gcnt[((uint32_t)((int)c0[2] + z) * (uint32_t)D.gn[1] + (uint32_t)((int)c0[1] + y)) *
+                              (uint32_t)D.gn[0] + (uint32_t)((int)c0[0] + x)], v);
+      }
+      wave_lds_sync();
+      continue;
+    }
+    uint32_t cell = NIL, cnt = 0u;  // this lane's entry of the table
+    int n_cells = 0;
+    for (int z = 0; z < 8; ++z) {
+      uint32_t c = NIL;
+      if ((q[CB_REACHED + z] >> lane) & 1ull) c = deposit_cell(D, G, sx, sy, bz * 8 + z);
+      unsigned long long left = __ballot(c != NIL);
+      while (left) {
+        const uint32_t cc = (uint32_t)__builtin_amdgcn_readlane((int)c, __ffsll((long long)left) - 1);
+        const unsigned long long same = __ballot(c == cc);
+        left &= ~same;
+        const unsigned long long at = __ballot(cell == cc);
+        int e = at ? __ffsll((long long)at) - 1 : n_cells;
+        if (e == 64) {
+          atomicAdd(&D.gcnt[cell], cnt);
+          cell = NIL;
+          cnt = 0u;
+          e = n_cells = 0;
+        }
+        if (!at) ++n_cells;
+        if (lane == e) {
+          cell = cc;
+          cnt += (uint32_t)__popcll(same);
+        }
+      }
+    }
+    if (cell != NIL) atomicAdd(&D.gcnt[cell], cnt);
   }
 }
 
@@ -3961,7 +4042,7 @@ void launch_solute_nodes(const double* T, const double* w, double liq_T, double 
   k_solute_nodes<<<grid_for(n, 8192), TPB, 0, s>>>(T, w, liq_T, liq_m, n, out);
 }
 void launch_deposit_all(const Dev& d, hipStream_t s) {
-  k_deposit_all<<<grid_for((d.cmask + 1) * 8, 16384), TPB, 0, s>>>(Plain{d});
+  k_deposit_all<<<grid_for(d.cmask + 1, 4096), TPB, 0, s>>>(Plain{d});
 }
 void launch_mushy_fraction(const uint32_t* cnt, uint64_t n, double site_over_cell, float* out,
                            hipStream_t s) {

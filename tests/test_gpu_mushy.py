@@ -64,6 +64,29 @@ def test_deposition_counts_match_the_fp32_checker():
     ctx.close()
 
 
+@pytest.mark.parametrize("cells", [(24, 24, 24), (1, 1, 1), (24, 1, 3), (5, 3, 2)])
+@pytest.mark.parametrize("inside", [1.0, 0.4])
+def test_recount_matches_the_fp32_checker(cells, inside):
+    """Setting the grid counts every reached site: cells smaller than the
+    site spacing (a slot of 512 sites then lies in hundreds of them), one
+    cell for all, and grids that end inside the grains."""
+    require_gpu()
+    q = W.shoemake_quaternions(W.rng(11), 3)
+    c = np.array([[4e-5, 5e-5, 5e-5], [6e-5, 4e-5, 5e-5], [5e-5, 6e-5, 6e-5]])
+    p = B.make_params((0, 0, 0), (1e-4,) * 3, 4e-6, 4e-6, 4e-6, W.KIN_A, W.KIN_B,
+                      cap_particles=1 << 14, cap_stopped=1 << 14, cap_claim_bricks=1 << 12,
+                      field_n=(24, 24, 24))
+    ctx = B.Context(p)
+    ctx.init_grains(c, q, np.array([9, 7, 0], np.int32))
+    spacing = tuple(inside * 9e-5 / k for k in cells)
+    origin = tuple(5e-6 + 0.5 * s for s in spacing)
+    ctx.set_deposition_grid(cells, origin, spacing)
+    want = _checker(ctx, cells, origin, spacing)
+    assert want.any()
+    np.testing.assert_array_equal(ctx.mushy_counts(), want)
+    ctx.close()
+
+
 def test_deposition_agrees_with_the_oracle_run():
     require_gpu()
     w = _cet()
