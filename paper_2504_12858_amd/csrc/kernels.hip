@@ -3742,42 +3742,65 @@ __device__ __forceinline__ float velocity_slope(const Dev& D, float dT) {
          D.ka[1] * D.kb[1] * exp2f((D.kb[1] - 1.0f) * l);
 }
 
-// Gradient of the undercooling interpolant at p: the derivative of the
-// trilinear form, zero along an axis clamped outside the grid.
-__device__ __forceinline__ P3 field_grad(const Dev& D, P3 p) {
-  if (D.fkind == F_UNIFORM) return P3{0.0f, 0.0f, 0.0f};
-  if (D.fkind == F_LINEAR) return P3{D.fgrad[0], D.fgrad[1], D.fgrad[2]};
-  p = place(D, p).p;
-  float u[3] = {(p.x - D.fo[0]) * D.finv[0], (p.y - D.fo[1]) * D.finv[1],
-                (p.z - D.fo[2]) * D.finv[2]};
-  int i0[3];
-  float f[3];
-  bool cl[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    float fl = floorf(u[a]);
-    fl = fmaxf(fl, 0.0f);
-    fl = fminf(fl, (float)(D.fn[a] - 2));
-    i0[a] = (int)fl;
-    const float w = u[a] - fl;
-    cl[a] = w < 0.0f || w > 1.0f;
-    f[a] = fminf(fmaxf(w, 0.0f), 1.0f);
+// Undercooling (field_at) and, with GRAD, its gradient at p: the derivative of
+// the trilinear form, zero along an axis clamped outside the grid.  The cell of
+// the last call is kept, with its corner values: a particle moves a small part
+// of a cell per step.  p lies in that cell when its distances w to the cell's
+// low corner are in [0, 1); these differences are exact there, so the test is
+// that of the floor, and w are the weights.
+struct FieldCell {
+  float lo[3];  // low corner (node indices); NaN: none yet
+  float v[8];   // corners 000, 100, 010, 110, 001, 101, 011, 111 (x fastest)
+};
+template <bool GRAD>
+__device__ __forceinline__ float field_cell(const Dev& D, P3 p, float lin_c, FieldCell& fc, P3& grad) {
+  if (D.fkind == F_UNIFORM) {
+    if (GRAD) grad = P3{0.0f, 0.0f, 0.0f};
+    return D.fdT;
   }
-  const size_t sy = (size_t)D.fn[0], sz = (size_t)D.fn[0] * (size_t)D.fn[1];
-  const size_t b = (size_t)i0[2] * sz + (size_t)i0[1] * sy + (size_t)i0[0];
-  const float* __restrict__ g = D.fgrid;
-  const float c000 = g[b], c100 = g[b + 1], c010 = g[b + sy], c110 = g[b + sy + 1];
-  const float c001 = g[b + sz], c101 = g[b + sz + 1], c011 = g[b + sz + sy], c111 = g[b + sz + sy + 1];
-  const float c00 = fmaf(f[0], c100 - c000, c000), c10 = fmaf(f[0], c110 - c010, c010);
-  const float c01 = fmaf(f[0], c101 - c001, c001), c11 = fmaf(f[0], c111 - c011, c011);
+  p = place(D, p).p;
+  if (D.fkind == F_LINEAR) {
+    if (GRAD) grad = P3{D.fgrad[0], D.fgrad[1], D.fgrad[2]};
+    return ((lin_c + D.fgrad[0] * p.x) + D.fgrad[1] * p.y) + D.fgrad[2] * p.z;
+  }
+  const float u[3] = {(p.x - D.fo[0]) * D.finv[0], (p.y - D.fo[1]) * D.finv[1],
+                      (p.z - D.fo[2]) * D.finv[2]};
+  float f[3] = {u[0] - fc.lo[0], u[1] - fc.lo[1], u[2] - fc.lo[2]};
+  bool cl[3] = {false, false, false};
+  if (!(fminf(fminf(f[0], f[1]), f[2]) >= 0.0f && fmaxf(fmaxf(f[0], f[1]), f[2]) < 1.0f)) {
+    int i0[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      float fl = floorf(u[a]);
+      fl = fmaxf(fl, 0.0f);
+      fl = fminf(fl, (float)(D.fn[a] - 2));
+      i0[a] = (int)fl;
+      fc.lo[a] = fl;
+      const float w = u[a] - fl;
+      cl[a] = w < 0.0f || w > 1.0f;
+      f[a] = fminf(fmaxf(w, 0.0f), 1.0f);
+    }
+    const size_t sy = (size_t)D.fn[0], sz = (size_t)D.fn[0] * (size_t)D.fn[1];
+    const float* __restrict__ g =
+        D.fgrid + ((size_t)i0[2] * sz + (size_t)i0[1] * sy + (size_t)i0[0]);
+    fc.v[0] = g[0], fc.v[1] = g[1], fc.v[2] = g[sy], fc.v[3] = g[sy + 1];
+    fc.v[4] = g[sz], fc.v[5] = g[sz + 1], fc.v[6] = g[sz + sy], fc.v[7] = g[sz + sy + 1];
+  }
+  const float dx00 = fc.v[1] - fc.v[0], dx10 = fc.v[3] - fc.v[2];
+  const float dx01 = fc.v[5] - fc.v[4], dx11 = fc.v[7] - fc.v[6];
+  const float c00 = fmaf(f[0], dx00, fc.v[0]), c10 = fmaf(f[0], dx10, fc.v[2]);
+  const float c01 = fmaf(f[0], dx01, fc.v[4]), c11 = fmaf(f[0], dx11, fc.v[6]);
   const float c0 = fmaf(f[1], c10 - c00, c00), c1 = fmaf(f[1], c11 - c01, c01);
-  const float d0y0 = fmaf(f[1], (c110 - c010) - (c100 - c000), c100 - c000);
-  const float d0y1 = fmaf(f[1], (c111 - c011) - (c101 - c001), c101 - c001);
-  const float gx = fmaf(f[2], d0y1 - d0y0, d0y0);
-  const float gy = fmaf(f[2], (c11 - c01) - (c10 - c00), c10 - c00);
-  const float gz = c1 - c0;
-  return P3{cl[0] ? 0.0f : gx * D.finv[0], cl[1] ? 0.0f : gy * D.finv[1],
-            cl[2] ? 0.0f : gz * D.finv[2]};
+  if (GRAD) {
+    const float d0y0 = fmaf(f[1], dx10 - dx00, dx00);
+    const float d0y1 = fmaf(f[1], dx11 - dx01, dx01);
+    const float gx = fmaf(f[2], d0y1 - d0y0, d0y0);
+    const float gy = fmaf(f[2], (c11 - c01) - (c10 - c00), c10 - c00);
+    const float gz = c1 - c0;
+    grad = P3{cl[0] ? 0.0f : gx * D.finv[0], cl[1] ? 0.0f : gy * D.finv[1],
+              cl[2] ? 0.0f : gz * D.finv[2]};
+  }
+  return fmaf(f[2], c1 - c0, c0);
 }
 
 // Tracked set: the records of the active store at the start of the
@@ -3828,10 +3851,22 @@ __global__ __launch_bounds__(TPB) void k_adj_positions(Bind Bd, uint32_t n, floa
 }
 
 // Reverse sweep, one thread per tracked particle.  Each checkpoint segment
-// of K steps is recomputed from its checkpoint into seg[j][i] (step-major,
-// coalesced) with the forward's own arithmetic, then walked backwards.
-// Per-block FP64 partial sums go to part[block][3].
-template <class Bind>
+// of K steps is recomputed from its checkpoint with the forward's own
+// arithmetic, its travels kept in LDS (K <= ADJ_LDS_STEPS: a column per thread,
+// step-major, up to 64 KB per block) or else in seg[j][i] (step-major,
+// coalesced), then walked backwards.  Per-block FP64 partial sums go to
+// part[block][3].
+//
+// Bound by the arithmetic of two field evaluations per step.  Segments in LDS,
+// the corner values of a particle's node cell kept in registers (eight gathers
+// per evaluation otherwise) and its site position formed once: 518k particles,
+// 500 steps on a node grid took 3104 us before, 735 us now.
+constexpr int32_t ADJ_LDS_STEPS = 60;
+//
+// FK: the field kind, for contexts without periodic axes and with exponents
+// (2, 3), or -1: everything as the context has it (the general form's branches
+// in the loops over the steps: 1170 us there).
+template <class Bind, int FK, bool LDS>
 __global__ __launch_bounds__(TPB) void k_adj_backward(Bind Bd, uint32_t n, int32_t n_steps,
                                                       int32_t K, const float* linc, float dt,
                                                       const float* dLdx, float* seg,
@@ -3839,20 +3874,37 @@ __global__ __launch_bounds__(TPB) void k_adj_backward(Bind Bd, uint32_t n, int32
   Dev D;
   VGrid V;
   Bd.bind(D, V);
+  if constexpr (FK >= 0) {
+    D.fkind = FK;
+    D.periodic = 0;
+    D.kin_poly = 1;
+  }
   __shared__ double s_red[3][TPB / 64];
+  extern __shared__ float s_seg[];
   double ga0 = 0.0, ga1 = 0.0, gth = 0.0;
   uint32_t bad = 0;
+  const bool linear = D.fkind == F_LINEAR;
   for (uint32_t i = V.b * TPB + threadIdx.x; i < n; i += V.G * TPB) {
     const uint4 r = D.adj_rec[i];
     const int32_t nact = D.adj_nact[i];
     if (nact <= 0) continue;
+    float* col = LDS ? s_seg + threadIdx.x : seg + i;
+    const size_t stride = LDS ? (size_t)TPB : (size_t)n;
+    // x(s) = o + (+-s) e as lattice_pos forms it; u = R e_d.
+    const int ax = rec_dir(r) >> 1;
+    const float sg = (rec_dir(r) & 1) ? -1.0f : 1.0f;
     const float* G = D.gtab + (size_t)rec_grain(r) * GT_STRIDE;
-    const int d = rec_dir(r), sx = rec_sx(r), sy = rec_sy(r), sz = rec_sz(r);
-    // u = R e_d: column axis(d) of R (rows at G[4..12]), with the sign of d.
-    const int ax = d >> 1;
-    const float sg = (d & 1) ? -1.0f : 1.0f;
-    const P3 u = {sg * G[4 + ax], sg * G[7 + ax], sg * G[10 + ax]};
+    const P3 e = {G[4 + ax], G[7 + ax], G[10 + ax]};
+    const SiteFrame F = site_frame(load_grow(G), rec_sx(r), rec_sy(r), rec_sz(r));
+    const P3 o = F.o;
+    auto at = [&](float s) {
+      const float ss = sg * s;
+      return P3{fmaf(ss, e.x, o.x), fmaf(ss, e.y, o.y), fmaf(ss, e.z, o.z)};
+    };
+    const P3 u = {sg * e.x, sg * e.y, sg * e.z};
     float lam = (dLdx[3 * i] * u.x + dLdx[3 * i + 1] * u.y) + dLdx[3 * i + 2] * u.z;
+    FieldCell fc;
+    fc.lo[0] = fc.lo[1] = fc.lo[2] = NAN;
     const int32_t nck = (n_steps + K - 1) / K;
     for (int32_t c = nck - 1; c >= 0; --c) {
       const int32_t k0 = c * K;
@@ -3860,16 +3912,16 @@ __global__ __launch_bounds__(TPB) void k_adj_backward(Bind Bd, uint32_t n, int32
       const int32_t k1 = min(k0 + K, nact);
       float s = D.adj_ck[(size_t)c * D.adj_ncap + i];
       for (int32_t k = k0; k < k1; ++k) {
-        seg[(size_t)(k - k0) * n + i] = s;
-        const P3 x = lattice_pos(G, sx, sy, sz, d, s);
-        const float dT = field_at(D, x, linc[k]) - D.theta;
+        col[(size_t)(k - k0) * stride] = s;
+        P3 gF;
+        const float dT = field_cell<false>(D, at(s), linear ? linc[k] : 0.0f, fc, gF) - D.theta;
         s = s + velocity(D, dT) * dt;
       }
       if (k1 == nact && s != D.adj_sfin[i]) bad += 1;
       for (int32_t k = k1 - 1; k >= k0; --k) {
-        const float sk = seg[(size_t)(k - k0) * n + i];
-        const P3 x = lattice_pos(G, sx, sy, sz, d, sk);
-        const float dT = field_at(D, x, linc[k]) - D.theta;
+        const float sk = col[(size_t)(k - k0) * stride];
+        P3 gF;
+        const float dT = field_cell<true>(D, at(sk), linear ? linc[k] : 0.0f, fc, gF) - D.theta;
         const float vp = velocity_slope(D, dT);
         if (dT > 0.0f) {
           const double w = (double)lam * (double)dt;
@@ -3883,7 +3935,6 @@ __global__ __launch_bounds__(TPB) void k_adj_backward(Bind Bd, uint32_t n, int32
           }
         }
         gth -= (double)lam * (double)dt * (double)vp;
-        const P3 gF = field_grad(D, x);
         const float du = (gF.x * u.x + gF.y * u.y) + gF.z * u.z;
         lam = lam * fmaf(dt * vp, du, 1.0f);
       }
@@ -3907,12 +3958,20 @@ __global__ __launch_bounds__(TPB) void k_adj_backward(Bind Bd, uint32_t n, int32
 }
 
 // Sum of the per-block partials in a fixed order: lane l of wave q adds
-// blocks l, l + 64, ... of component q, then a fixed shuffle tree.
+// blocks l, l + 64, ... of component q (sixteen loads at a time: one after
+// another took 18 us), then a fixed shuffle tree.
 __global__ void k_adj_reduce(const double* part, uint32_t nblocks, double* out) {
   const int q = threadIdx.x >> 6, l = lane_id();
   if (q >= 3) return;
   double x = 0.0;
-  for (uint32_t b = (uint32_t)l; b < nblocks; b += 64u) x += part[(size_t)b * 3 + q];
+  for (uint32_t b0 = (uint32_t)l; b0 < nblocks; b0 += 1024u) {
+    double v[16];
+#pragma unroll
+    for (uint32_t k = 0; k < 16; ++k)
+      v[k] = b0 + 64u * k < nblocks ? part[(size_t)(b0 + 64u * k) * 3 + q] : 0.0;
+#pragma unroll
+    for (uint32_t k = 0; k < 16; ++k) x += v[k];
+  }
   for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off);
   if (l == 0) out[q] = x;
 }
@@ -4175,7 +4234,17 @@ void launch_adj_positions(const Dev& d, uint32_t n, float* xN, hipStream_t s) {
 void launch_adj_backward(const Dev& d, uint32_t n, int32_t n_steps, int32_t K, const float* linc,
                          float dt, const float* dLdx, float* seg, double* part, double* grad_out,
                          uint32_t* mismatch, hipStream_t s) {
-  k_adj_backward<<<ADJ_BLOCKS, TPB, 0, s>>>(Plain{d}, n, n_steps, K, linc, dt, dLdx, seg, part, mismatch);
+  // A segment fits a block's LDS up to ADJ_LDS_STEPS steps.
+  const bool lds = K <= ADJ_LDS_STEPS;
+  const size_t bytes = lds ? (size_t)K * TPB * 4 : 0;
+  auto run = [&](auto kernel) {
+    kernel<<<ADJ_BLOCKS, TPB, bytes, s>>>(Plain{d}, n, n_steps, K, linc, dt, dLdx, seg, part, mismatch);
+  };
+  if (!lds) run(k_adj_backward<Plain, -1, false>);
+  else if (d.periodic || !d.kin_poly) run(k_adj_backward<Plain, -1, true>);
+  else if (d.fkind == F_UNIFORM) run(k_adj_backward<Plain, F_UNIFORM, true>);
+  else if (d.fkind == F_LINEAR) run(k_adj_backward<Plain, F_LINEAR, true>);
+  else run(k_adj_backward<Plain, F_GRID, true>);
   k_adj_reduce<<<1, 192, 0, s>>>(part, ADJ_BLOCKS, grad_out);
 }
 

@@ -161,6 +161,40 @@ def test_gradient_through_a_periodic_face():
     ctx.close()
 
 
+@pytest.mark.parametrize("ckpt_every", [60, 61, 200])
+def test_gradient_on_a_node_grid_with_long_segments(ckpt_every):
+    """Particles cross cells of 10 x 25 x 250 um during the run, with the
+    longest segments kept on chip (60 steps) and longer ones: the gradient is
+    bitwise that of short segments (the travels and the sums over the steps
+    are the same) and matches the oracle's."""
+    require_gpu()
+    n = (101, 41, 5)
+    x, y = np.arange(n[0]) * 1e-5, np.arange(n[1]) * 2.5e-5
+    data = 6.0 + np.sin(2e4 * x)[None, None, :] * np.cos(9e3 * y)[None, :, None] + \
+        np.zeros((n[2], 1, 1))
+    f = W.Field(W.FIELD_GRID, n=n, origin=(0.0,) * 3, spacing=(1e-5, 2.5e-5, 2.5e-4),
+                data=np.ascontiguousarray(data, np.float32))
+    q = W.shoemake_quaternions(W.rng(5), 3)
+    dt, N = 1e-3, 130
+    p = B.make_params(BOX[0], BOX[1], LAM, LAM, LAM, W.KIN_A, W.KIN_B, branching=0,
+                      cap_particles=1 << 14, cap_stopped=1 << 14, cap_claim_bricks=1 << 12,
+                      field_n=n)
+    grads = []
+    for k in (7, ckpt_every):
+        ctx = B.Context(p)
+        ctx.set_thermal_field(f)
+        ctx.init_grains(CASE["centre"], q, CASE["shells"])
+        ctx.adjoint_forward(dt, N, ckpt_every=k)
+        tr = ctx.adjoint_tracked()
+        dLdx = W.rng(3).normal(size=(len(tr), 3)).astype(np.float32)
+        grads.append(np.array(ctx.adjoint_backward(dLdx)))
+        ctx.close()
+    assert np.array_equal(grads[0], grads[1])
+    o = _oracle(f, CASE["centre"], q, CASE["shells"])
+    go = o.adjoint_grad(_tracked_parts(tr), tr["nact"], 0.0, dt, N, dLdx.astype(np.float64))
+    np.testing.assert_allclose(grads[1], go, rtol=2e-4)
+
+
 def test_envelope_run_autograd():
     """torch.autograd through EnvelopeRun: loss = sum |x_N - xhat|^2; the
     parameter gradient equals the adjoint call on dL/dx = 2 (x_N - xhat)
