@@ -67,12 +67,14 @@ enum : int { TK_ADVANCE = 0, TK_BRANCH, TK_CELLSCAN, TK_SCATTER, TK_CHILDREN, TK
 enum : int32_t { F_UNIFORM = 0, F_LINEAR = 1, F_GRID = 2, F_ROSENTHAL = 3 };
 
 struct Counters {
+  // Totals of the brick scan, added to as one 64-bit word each.
+  alignas(8) uint32_t n_out;       // records written by the scatter = sorted region of B
+  uint32_t n_occ;                  // occupied bricks this step
+  alignas(8) uint32_t n_resorted;  // live records counted by the stopped-store re-sort
+  uint32_t n_socc;                 // bricks holding sorted stopped particles
   uint32_t n_active;   // records in A (sorted region + nucleated tail)
-  uint32_t n_out;      // records written by the scatter = sorted region of B
-  uint32_t n_occ;      // occupied bricks this step
   uint32_t n_stopped;  // stopped store length
   uint32_t n_sorted;   // cell-sorted prefix of the stopped store
-  uint32_t n_socc;     // bricks holding sorted stopped particles
   uint32_t n_grains;
   uint32_t claim_used; // occupied claim slots
   uint32_t err;        // sticky error bits
@@ -89,7 +91,6 @@ struct Counters {
   // re-activated, grains melted entirely
   unsigned long long melted, removed, reactivated, grains_melted;
   uint32_t n_melt_slots;  // claim slots with sites melted this step
-  uint32_t n_resorted;    // live records counted by the stopped-store re-sort
   // step state, advanced on the device by k_finish (so that a captured
   // sequence of steps replays without host involvement)
   uint32_t par;        // 1: the active-store roles of A and B (and their tags) are swapped
@@ -195,7 +196,7 @@ struct Dev {
   uint32_t* smask;     // [cells] slabs (eighths of the cell per axis, 8 bits per axis)
                        //  that hold stopped particles
   uint32_t* occ;       // [bricks] occupied-brick list
-  uint64_t* scan_tmp;  // block partial sums of the brick scan
+  uint64_t* scan_tmp;  // block partial sums of the brick scan (large grids)
   // claims: the slot bricks of a grain in cubic blocks of CLAIM_BLOCK_SLOTS
   // consecutive slots; a hash directory of the blocks
   unsigned long long* ckeys;   // [slots] key of each taken slot, else CLAIM_EMPTY
@@ -265,6 +266,7 @@ struct BatchLaunch {
   char* base;
   BatchSite site[BS_N];
   int32_t any_periodic;  // some context has periodic axes
+  uint32_t max_bricks;   // most bricks of a context
 };
 
 // -------------------------------------------------- host-side launchers --

@@ -11,7 +11,7 @@
 //   k_branch     outer directions of each spawner against the grain's claims;
 //                same-step competitors for one target resolved by lowest
 //                direction; counts of the children
-//   k_scan_*     exclusive scan of brick counts -> brick starts, occupied list
+//   k_scan, k_scan_*   scan of brick counts -> brick starts, occupied list
 //   k_cellscan   one wave per occupied brick, one lane per cell: cell starts
 //   k_scatter    records and positions -> cell-sorted arrays (ranks from
 //                wave-aggregated decrements of the cell counts)
@@ -1024,6 +1024,8 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
   }
   __syncthreads();
   const uint32_t n = D.cnt->n_active;
+  // The totals of the step's brick scan.
+  if (V.b == 0 && threadIdx.x == 0) D.cnt->n_out = D.cnt->n_occ = 0u;
   const Chunk ch = chunk_of(V, n, TPB);
   const int lane = lane_id();
   float max_step = 0.0f;
@@ -1358,10 +1360,27 @@ __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
 // Mode 0 (active particles of the step): writes start, count and the epoch
 // of each occupied brick.  Mode 1 (stopped-store re-sort): writes start and
 // count of every brick.  Both list the occupied bricks and reset the counts.
+//
+// Up to SCAN_ONE_LAUNCH bricks it is one launch: a block scans a tile of
+// bricks and takes the tile's stretch of the store and of the list of occupied
+// bricks with one 64-bit atomic on their two totals (n_out | n_occ << 32;
+// zeroed by k_advance, resp. k_srb_count).  The tiles then lie in the store in
+// the order in which their blocks come, which nothing depends on: a brick's
+// particles are found through its own start, and its cells are contiguous.  A
+// tile without particles takes nothing.  Larger grids take three launches
+// (tile sums, their scan by one block, starts).
+//
+// Bound by launches on small grids (4.5 us each), by the counts on large ones;
+// the single launch by its atomics as well, about 25 ns each on one word, and
+// the order of the tiles costs the later kernels some of the locality between
+// tiles.  2M bricks, a third of them occupied: 7.5 us against 15 us in three
+// launches, but k_dirty 69 against 64 us and the whole step the same; 7.8M
+// bricks in 3800 tiles: 99 us against 39 us.  Hence the line at 512 tiles.
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = TPB * SCAN_ITEMS;
 static_assert(SCAN_TILE == (int)SCAN_TILE_HOST, "brick-scan tile of the host launchers");
 static_assert(SCAN_ITEMS == 8, "two 16-byte loads per thread");
+constexpr uint32_t SCAN_ONE_LAUNCH = 512u * (uint32_t)SCAN_TILE;
 
 // The counts of bricks b0 .. b0 + 7 (zero past the last brick): two 16-byte
 // loads when all eight exist (b0 is a multiple of eight and the count array
@@ -1381,6 +1400,65 @@ __device__ __forceinline__ void load_counts8(const Dev& D, uint64_t b0, uint32_t
   } else {
 #pragma unroll
     for (int k = 0; k < 8; ++k) c[k] = b0 + k < D.n_bricks ? D.bcnt[b0 + k] : 0u;
+  }
+}
+
+template <class Bind>
+__global__ __launch_bounds__(TPB) void k_scan(Bind Bd, int mode) {
+  Dev D;
+  VGrid V;
+  Bd.bind(D, V);
+  if (dead(D) || (mode == 1 && !resort_due(D))) return;
+  const uint32_t epoch = step_epoch(D);
+  __shared__ unsigned long long wsum[TPB / 64], s_base;
+  const uint64_t b0 = (uint64_t)V.b * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
+  uint32_t c[SCAN_ITEMS];
+  load_counts8(D, b0, c);
+  unsigned long long v = 0;
+  uint32_t any = 0;
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) {
+    v += (unsigned long long)c[k] | ((unsigned long long)(c[k] > 0u) << 32);
+    any |= c[k];
+  }
+  unsigned long long total;
+  unsigned long long ex = block_excl_scan64(v, wsum, total);
+  if (threadIdx.x == 0 && total) {
+    uint32_t* sums = mode == 0 ? &D.cnt->n_out : &D.cnt->n_resorted;
+    const unsigned long long base = atomicAdd(reinterpret_cast<unsigned long long*>(sums), total);
+    if (mode == 0 && (base & 0xFFFFFFFFull) + (total & 0xFFFFFFFFull) > D.cap_p)
+      atomicOr(&D.cnt->err, ERR_CAPACITY);
+    s_base = base;
+  }
+  __syncthreads();
+  if (total) ex += s_base;
+  // Counts back to zero: the eight at once when they all exist.
+  const bool whole = b0 + 8u <= D.n_bricks;
+  if (whole && any) {
+    *reinterpret_cast<uint4*>(D.bcnt + b0) = make_uint4(0u, 0u, 0u, 0u);
+    *reinterpret_cast<uint4*>(D.bcnt + b0 + 4) = make_uint4(0u, 0u, 0u, 0u);
+  }
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) {
+    const uint64_t b = b0 + k;
+    if (b < D.n_bricks) {
+      const uint32_t start = (uint32_t)(ex & 0xFFFFFFFFull);
+      const uint32_t occ = (uint32_t)(ex >> 32);
+      if (mode == 1) D.bsinfo[b] = make_uint2(start, c[k]);
+      if (c[k] > 0u) {
+        if (mode == 0) {
+          D.binfo[b] = make_uint2(start, c[k]);
+          // Step stamp and an empty owner range; the stopped owner word (.w)
+          // is kept.
+          uint4* m = D.bmeta + b;
+          *reinterpret_cast<uint2*>(m) = make_uint2(epoch, NIL);
+          reinterpret_cast<uint32_t*>(m)[2] = 0u;
+        }
+        D.occ[occ] = (uint32_t)b;
+        if (!whole) D.bcnt[b] = 0u;
+      }
+      ex += (unsigned long long)c[k] | ((unsigned long long)(c[k] > 0u) << 32);
+    }
   }
 }
 
@@ -2619,6 +2697,8 @@ __global__ __launch_bounds__(TPB) void k_srb_count(Bind Bd) {
   if (dead(D) || !resort_due(D)) return;
   const uint32_t n = min(D.cnt->n_stopped, D.cap_s);
   const uint32_t ns = D.cnt->n_sorted;
+  // The totals of the re-sort's brick scan.
+  if (V.b == 0 && threadIdx.x == 0) D.cnt->n_resorted = D.cnt->n_socc = 0u;
   const Chunk ch = chunk_of(V, n, TPB);
   for (uint32_t base = ch.begin; base < ch.end; base += TPB) {
     const uint32_t j = base + threadIdx.x;
@@ -4059,9 +4139,13 @@ void launch_advance(const Dev& d, float dt, hipStream_t s) {
 void launch_branch(const Dev& d, hipStream_t s) { k_branch<<<d.sched[TK_BRANCH], TPB, 0, s>>>(Plain{d}); }
 static void scan_bricks(const Dev& d, int mode, hipStream_t s) {
   const uint32_t ntiles = (uint32_t)((d.n_bricks + SCAN_TILE - 1) / SCAN_TILE);
-  k_scan_reduce<<<ntiles, TPB, 0, s>>>(Plain{d}, mode);
-  k_scan_top<<<1, TPB, 0, s>>>(Plain{d}, mode);
-  k_scan_write<<<ntiles, TPB, 0, s>>>(Plain{d}, mode);
+  if (d.n_bricks <= SCAN_ONE_LAUNCH) {
+    k_scan<<<ntiles, TPB, 0, s>>>(Plain{d}, mode);
+  } else {
+    k_scan_reduce<<<ntiles, TPB, 0, s>>>(Plain{d}, mode);
+    k_scan_top<<<1, TPB, 0, s>>>(Plain{d}, mode);
+    k_scan_write<<<ntiles, TPB, 0, s>>>(Plain{d}, mode);
+  }
   k_cellscan<<<mode == 0 ? d.sched[TK_CELLSCAN] : (uint32_t)STREAM_GRID, TPB, 0, s>>>(Plain{d}, mode);
 }
 void launch_scan(const Dev& d, hipStream_t s) { scan_bricks(d, 0, s); }
@@ -4263,6 +4347,15 @@ void launch_batch_reset_stats(const BatchLaunch& L, hipStream_t s) {
 // device step count decides whether its stopped store is re-sorted.
 void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s) {
   const uint32_t one = L.site[BS_ONE].total, tiles = L.site[BS_TILES].total;
+  auto batch_scan = [&](int mode) {
+    if (L.max_bricks <= SCAN_ONE_LAUNCH) {
+      k_scan<<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), mode);
+      return;
+    }
+    k_scan_reduce<<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), mode);
+    k_scan_top<<<one, TPB, 0, s>>>(bind_of(L, BS_ONE), mode);
+    k_scan_write<<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), mode);
+  };
   if (L.site[BS_RESAMPLE].total)
     k_resample<<<L.site[BS_RESAMPLE].total, TPB, 0, s>>>(bind_of(L, BS_RESAMPLE));
   if (L.any_periodic)
@@ -4271,9 +4364,7 @@ void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s) {
     k_advance<Batch, 0><<<L.site[BS_ADVANCE].total, TPB, 0, s>>>(bind_of(L, BS_ADVANCE), (float)dt);
   k_spawn_scan<<<one, 1024, 0, s>>>(bind_of(L, BS_ONE));
   k_branch<<<L.site[BS_BRANCH].total, TPB, 0, s>>>(bind_of(L, BS_BRANCH));
-  k_scan_reduce<<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), 0);
-  k_scan_top<<<one, TPB, 0, s>>>(bind_of(L, BS_ONE), 0);
-  k_scan_write<<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), 0);
+  batch_scan(0);
   k_cellscan<<<L.site[BS_CELLSCAN].total, TPB, 0, s>>>(bind_of(L, BS_CELLSCAN), 0);
   k_scatter<<<L.site[BS_SCATTER].total, TPB, 0, s>>>(bind_of(L, BS_SCATTER));
   k_scatter_children<<<L.site[BS_CHILDREN].total, TPB, 0, s>>>(bind_of(L, BS_CHILDREN));
@@ -4287,9 +4378,7 @@ void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s) {
   }
   k_finish<<<one, 1, 0, s>>>(bind_of(L, BS_ONE), dt);
   k_srb_count<<<L.site[BS_RESORT].total, TPB, 0, s>>>(bind_of(L, BS_RESORT));
-  k_scan_reduce<<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), 1);
-  k_scan_top<<<one, TPB, 0, s>>>(bind_of(L, BS_ONE), 1);
-  k_scan_write<<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), 1);
+  batch_scan(1);
   k_cellscan<<<L.site[BS_RESORT].total, TPB, 0, s>>>(bind_of(L, BS_RESORT), 1);
   k_srb_scatter<<<L.site[BS_RESORT].total, TPB, 0, s>>>(bind_of(L, BS_RESORT));
   k_srb_finish<<<one, 1, 0, s>>>(bind_of(L, BS_ONE));

@@ -122,7 +122,6 @@ Layout layout(const ge_params* p, const Geometry& g) {
     return o;
   };
   const uint64_t cp = (uint64_t)p->cap_particles, cs = (uint64_t)p->cap_stopped;
-  const uint64_t ntiles = (g.n_bricks + 2047) / 2048;
   L.A = put(16 * cp);
   L.B = put(16 * cp);
   L.P = put(16 * cp);
@@ -154,7 +153,7 @@ Layout layout(const ge_params* p, const Geometry& g) {
   L.cown = put(8 * g.n_cells);
   L.smask = put(4 * g.n_cells);
   L.occ = put(4 * g.n_bricks);
-  L.scan_tmp = put(8 * ntiles);
+  L.scan_tmp = put(8 * ((g.n_bricks + ge::SCAN_TILE_HOST - 1) / ge::SCAN_TILE_HOST));
   L.ckeys = put(8 * g.slots);
   L.cbits = put(192 * g.slots);
   L.clist = put(8 * g.slots);
@@ -2138,7 +2137,11 @@ ge_status ge_batch_create(int32_t n, const ge_params* params, void* workspace, s
   }
   b->R = b->mem[0]->resort_every;
   b->L.any_periodic = 0;
-  for (ge_ctx* m : b->mem) b->L.any_periodic |= m->d.periodic != 0 ? 1 : 0;
+  b->L.max_bricks = 0;
+  for (ge_ctx* m : b->mem) {
+    b->L.any_periodic |= m->d.periodic != 0 ? 1 : 0;
+    b->L.max_bricks = std::max(b->L.max_bricks, m->d.n_bricks);
+  }
   *out = b;
   return GE_OK;
 }

@@ -376,3 +376,48 @@ def test_graph_replays_equal_plain_steps():
                 a.set_schedule({"branch": 512, "contain": 768})
         a.close()
         b.close()
+
+
+def test_brick_scan_forms_agree():
+    """Two grains grow into each other near a corner of boxes from 512 to
+    1.3M bricks (part of a tile of the brick scan, whole tiles, tile sums in a
+    launch of their own), past two re-sorts: the particles and claims are the
+    same, bit for bit, and so are those of batches with and without the
+    largest."""
+    require_gpu()
+    lam, steps, dt = 5e-6, 40, 1e-3
+    c = np.array([[6e-5, 7e-5, 7e-5], [1e-4, 8.5e-5, 8e-5]])
+    q = W.shoemake_quaternions(W.rng(8), 2)
+    shells = np.array([4, 3], np.int32)
+    sizes = (1.6e-4, 1e-3, 2.2e-3)
+
+    def params(L):
+        return B.make_params((0, 0, 0), (L, L, L), lam, lam, lam, W.KIN_A, W.KIN_B,
+                             cap_particles=1 << 14, cap_stopped=1 << 14, cap_claim_bricks=1 << 12)
+
+    def state(ctx):
+        p, _ = gpu_parts(ctx)
+        return p.tobytes(), gpu_claims(ctx)[0].tobytes()
+
+    def start(ctx):
+        ctx.set_thermal_field(W.Field(W.FIELD_UNIFORM, dT=5.0))
+        ctx.init_grains(c, q, shells)
+
+    want = None
+    for L in sizes:
+        print(f"box {L}", flush=True)
+        ctx = B.Context(params(L))
+        start(ctx)
+        st = ctx.step(dt, steps)
+        assert st["contained"] > 0 and st["children"] > 0
+        got = state(ctx)
+        ctx.close()
+        want = want or got
+        assert got == want
+    for some in (sizes[:2], sizes):
+        batch = B.Batch([params(L) for L in some])
+        for m in batch.members:
+            start(m)
+        batch.step(dt, steps)
+        assert all(state(m) == want for m in batch.members)
+        batch.close()
