@@ -82,8 +82,6 @@ struct Counters {
   uint32_t max_step;   // float bits of max v dt (non-negative floats order as uints)
   uint32_t n_fired;    // sites fired this step
   uint32_t n_live;     // active particles (A also holds records stopped at the end of a step)
-  uint32_t n_newstop;  // particles stopped by containment this step
-  uint32_t n_dpart;    // particles of dirty bricks this step
   unsigned long long advanced, exited, spawners, children, contained, nucleated;
   unsigned long long pair_tests;  // candidate particles examined by containment
   unsigned long long dirty_tests; // active particles in dirty bricks
@@ -99,6 +97,21 @@ struct Counters {
   uint32_t dir_used;   // occupied entries of the claim-block directory
   double t;            // time
   unsigned long long step;  // steps taken
+};
+
+// Per-step sums of the kernels' blocks, spread over N_BANKS words each: atomics
+// on one word take 10 to 25 ns each, one after another, so a sum over the
+// blocks of a launch in one word takes longer than most of the launches.  A
+// block adds to the bank of its logical number (consecutive blocks share a
+// bank); k_finish adds the banks to the counters and clears them.
+constexpr uint32_t N_BANKS = 16;
+struct alignas(128) Bank {
+  unsigned long long advanced, exited, spawners, children, pair_tests;
+  uint32_t max_step;   // float bits
+  uint32_t n_spawn;    // spawners of the step
+  uint32_t n_newstop;  // particles stopped by containment this step
+  uint32_t n_dpart;    // particles of dirty bricks this step: entries of the
+  uint32_t dpart0;     //   bank's stretch of dpart, and where that starts
 };
 
 // Rosenthal moving point source over a linear background (field kind 3).
@@ -161,7 +174,6 @@ struct Dev {
   uint32_t* spslot;       // [cap_p] claim slot of each spawner's reached site, at
                           //  the spawner's position in the per-block regions
   uint32_t* spawn_cnt;    // [STREAM_GRID]
-  uint32_t* spawn_off;    // [STREAM_GRID + 1] exclusive prefix of spawn_cnt
   uint32_t* newstop;      // [cap_p], per-block regions
   uint32_t* newstop_cnt;  // [STREAM_GRID]
   // stopped store: records S, positions PS; [0, n_sorted) cell-sorted
@@ -217,6 +229,7 @@ struct Dev {
   uint32_t n_sites;
   // counters
   Counters* cnt;
+  Bank* bank;  // [N_BANKS]
   // adjoint recording (all null when off): tags travel with the records of
   // A and B (tag = index into the tracked set, NIL for untracked particles)
   uint32_t* tagA;
@@ -238,11 +251,11 @@ struct Dev {
 // Every pointer member of Dev (a batched launch stores them as offsets from
 // the batch workspace and rebuilds them on the device).
 #define GE_DEV_POINTERS(X)                                                                   \
-  X(fgrid) X(gcnt) X(fcmin) X(fcoarse) X(mslots) X(greach) X(gsite) X(gdead) X(gtab) X(gbox) X(A) X(B) X(P) X(spawn) X(spslot) X(spawn_cnt) X(spawn_off) X(newstop)      \
+  X(fgrid) X(gcnt) X(fcmin) X(fcoarse) X(mslots) X(greach) X(gsite) X(gdead) X(gtab) X(gbox) X(A) X(B) X(P) X(spawn) X(spslot) X(spawn_cnt) X(newstop)      \
   X(newstop_cnt) X(S) X(PS) X(S2) X(PS2) X(snext) X(shead) X(sstart) X(bsinfo)      \
   X(ccnt) X(cstart) X(bcnt) X(binfo) X(bmeta) X(dlist) X(dlist_cnt) X(dpart) X(dmask)       \
   X(doff) X(bown)                                                                             \
-  X(cown) X(smask) X(occ) X(scan_tmp) X(ckeys) X(cbits) X(clist) X(dirkeys) X(stab) X(sstate) X(cand) X(sgrain) X(cnt) X(tagA)      \
+  X(cown) X(smask) X(occ) X(scan_tmp) X(ckeys) X(cbits) X(clist) X(dirkeys) X(stab) X(sstate) X(cand) X(sgrain) X(cnt) X(bank) X(tagA)      \
   X(tagB) X(adj_rec) X(adj_nact) X(adj_sfin) X(adj_ck) X(adj_linc)
 constexpr uintptr_t NULL_OFFSET = ~(uintptr_t)0;
 

@@ -664,6 +664,17 @@ __device__ __forceinline__ Chunk chunk_at(uint32_t n, uint32_t granule, uint32_t
 __device__ __forceinline__ Chunk chunk_of(const VGrid& V, uint32_t n, uint32_t granule) {
   return chunk_at(n, granule, V.G, logical_block(V));
 }
+// Bank of logical block lb of G blocks, and the first logical block of bank q
+// (consecutive blocks share a bank).
+__device__ __forceinline__ uint32_t bank_of(uint32_t lb, uint32_t G) {
+  return lb * N_BANKS / G;  // G <= STREAM_GRID
+}
+__device__ __forceinline__ uint32_t bank_first(uint32_t q, uint32_t G) {
+  return (q * G + N_BANKS - 1u) / N_BANKS;
+}
+__device__ __forceinline__ Bank* block_bank(const Dev& D, const VGrid& V) {
+  return D.bank + bank_of(logical_block(V), V.G);
+}
 // Regions of a per-block list written by a kernel of G_w blocks, as read by
 // this block: an even share [lb G_w / G, (lb + 1) G_w / G) of them, so that
 // with grids that are multiples of 8 a region is read on the XCD that wrote it.
@@ -1151,52 +1162,53 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
   }
   if (threadIdx.x == 0) {
     D.spawn_cnt[logical_block(V)] = s_nsp;
-    if (s_adv) atomicAdd(&D.cnt->advanced, (unsigned long long)s_adv);
-    if (s_exit) atomicAdd(&D.cnt->exited, (unsigned long long)s_exit);
+    Bank* bk = block_bank(D, V);
+    if (s_nsp) atomicAdd(&bk->n_spawn, s_nsp);
+    if (s_adv) atomicAdd(&bk->advanced, (unsigned long long)s_adv);
+    if (s_exit) atomicAdd(&bk->exited, (unsigned long long)s_exit);
     if (s_bad) atomicOr(&D.cnt->err, s_bad);
-    if (s_max) atomicMax(&D.cnt->max_step, s_max);
+    if (s_max) atomicMax(&bk->max_step, s_max);
   }
 }
 
-// Exclusive prefix of the per-block spawner counts (one block): spawner i
-// of the step is in the region r with spawn_off[r] <= i < spawn_off[r + 1].
-template <class Bind>
-__global__ __launch_bounds__(1024) void k_spawn_scan(Bind Bd) {
-  Dev D;
-  VGrid V;
-  Bd.bind(D, V);
-  __shared__ uint32_t s_w[16];
-  const uint32_t G = D.sched[TK_ADVANCE];
-  const uint32_t per = (G + 1023u) / 1024u;  // regions per thread, G <= STREAM_GRID
-  const uint32_t r0 = threadIdx.x * per;
-  uint32_t v[2] = {0u, 0u};
-  for (uint32_t k = 0; k < per && k < 2u; ++k) v[k] = r0 + k < G ? D.spawn_cnt[r0 + k] : 0u;
-  uint32_t tot;
-  const uint32_t ex = wave_excl_scan(v[0] + v[1], tot);
-  if (lane_id() == 0) s_w[threadIdx.x >> 6] = tot;
-  __syncthreads();
-  uint32_t wbase = 0;
-  for (uint32_t w = 0; w < (threadIdx.x >> 6); ++w) wbase += s_w[w];
-  uint32_t acc = wbase + ex;
-  for (uint32_t k = 0; k < per && k < 2u; ++k) {
-    if (r0 + k < G) D.spawn_off[r0 + k] = acc;
-    acc += v[k];
-  }
-  if (threadIdx.x == 1023u) D.spawn_off[G] = acc;
-}
-
-// The step's spawners as one list: this block's even share of them, and the
-// lookup of spawner i (the region offsets are staged in LDS).
+// The step's spawners as one list: this block's even share of them, in whole
+// waves, and the lookup of spawner i.  Spawner i is in the region r with
+// s_off[r] <= i < s_off[r + 1]; a block with a share forms this exclusive
+// prefix of the per-block counts for itself in LDS (at most eight counts per
+// thread), which takes less than the launch of a kernel that formed it once
+// (4.6 us) while the blocks without a share leave at once (all blocks forming
+// it cost a small state as much as the launch).
 struct SpawnView {
-  uint32_t n, G, total;
+  uint32_t n, G, begin, end;
 };
-__device__ __forceinline__ SpawnView spawn_view(const Dev& D, uint32_t* s_off) {
+__device__ __forceinline__ SpawnView spawn_view(const Dev& D, const VGrid& V, uint32_t* s_off) {
+  constexpr uint32_t RUN = (uint32_t)STREAM_GRID / TPB;  // regions per thread, G <= STREAM_GRID
+  __shared__ uint32_t wsum[TPB / 64];
   SpawnView v;
-  v.n = D.cnt->n_active;
+  uint32_t n_spawn = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < N_BANKS; ++q) n_spawn += D.bank[q].n_spawn;
+  const Chunk it = chunk_of(V, uniform_u32(n_spawn), 64u);
+  v.begin = it.begin;
+  v.end = it.end;
+  v.n = uniform_u32(D.cnt->n_active);
   v.G = D.sched[TK_ADVANCE];
-  for (uint32_t r = threadIdx.x; r <= v.G; r += blockDim.x) s_off[r] = D.spawn_off[r];
+  if (it.begin >= it.end) return v;
+  const uint32_t per = (v.G + TPB - 1u) / TPB, r0 = threadIdx.x * per;
+  uint32_t c[RUN], sum = 0, total;
+#pragma unroll
+  for (uint32_t k = 0; k < RUN; ++k) {
+    c[k] = k < per && r0 + k < v.G ? D.spawn_cnt[r0 + k] : 0u;
+    sum += c[k];
+  }
+  uint32_t acc = block_excl_scan(sum, wsum, total);
+#pragma unroll
+  for (uint32_t k = 0; k < RUN; ++k) {
+    if (k < per && r0 + k < v.G) s_off[r0 + k] = acc;
+    acc += c[k];
+  }
+  if (threadIdx.x == 0) s_off[v.G] = total;
   __syncthreads();
-  v.total = s_off[v.G];
   return v;
 }
 // Position of spawner i of the step in the per-block regions of the
@@ -1227,8 +1239,8 @@ __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
   }
   __syncthreads();
   __shared__ uint32_t s_off[STREAM_GRID + 1];
-  const SpawnView v = spawn_view(D, s_off);
-  const Chunk it = chunk_of(V, v.total, 1u);
+  const SpawnView it = spawn_view(D, V, s_off);
+  if (it.begin >= it.end) return;
   uint32_t nsp = 0, nch = 0;
   // The next round's spawner (index, record, claim slot) is loaded during
   // this round, off the chain of dependent loads.  Each record is read and
@@ -1236,7 +1248,7 @@ __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
   uint32_t ni = 0, nslot = NIL;
   uint4 nr = make_uint4(0u, 0u, 0u, 0u);
   if (it.begin + threadIdx.x < it.end) {
-    const uint32_t np = spawn_pos(v, s_off, it.begin + threadIdx.x);
+    const uint32_t np = spawn_pos(it, s_off, it.begin + threadIdx.x);
     ni = D.spawn[np];
     nr = D.A[ni];
     nslot = D.spslot[np];
@@ -1248,7 +1260,7 @@ __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
     const uint32_t i = ni, slot = nslot;
     const uint4 r = nr;
     if (k + TPB < it.end) {
-      const uint32_t np = spawn_pos(v, s_off, k + TPB);
+      const uint32_t np = spawn_pos(it, s_off, k + TPB);
       ni = D.spawn[np];
       nr = D.A[ni];
       nslot = D.spslot[np];
@@ -1351,8 +1363,9 @@ __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
   if (nch) atomicAdd(&s_ch, nch);
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (s_sp) atomicAdd(&D.cnt->spawners, (unsigned long long)s_sp);
-    if (s_ch) atomicAdd(&D.cnt->children, (unsigned long long)s_ch);
+    Bank* bk = block_bank(D, V);
+    if (s_sp) atomicAdd(&bk->spawners, (unsigned long long)s_sp);
+    if (s_ch) atomicAdd(&bk->children, (unsigned long long)s_ch);
   }
 }
 
@@ -1696,10 +1709,9 @@ __global__ __launch_bounds__(TPB) void k_scatter_children(Bind Bd) {
   Bd.bind(D, V);
   if (dead(D)) return;
   __shared__ uint32_t s_off[STREAM_GRID + 1];
-  const SpawnView v = spawn_view(D, s_off);
-  const Chunk it = chunk_of(V, v.total, 1u);
+  const SpawnView it = spawn_view(D, V, s_off);
   for (uint32_t k = it.begin + threadIdx.x; k < it.end; k += TPB) {
-    const uint32_t kp = spawn_pos(v, s_off, k);
+    const uint32_t kp = spawn_pos(it, s_off, k);
     const uint4 r = D.A[D.spawn[kp]];
     const uint32_t fl = rec_fl(r);
     const uint32_t gs = rec_grain(r);
@@ -1750,7 +1762,7 @@ __global__ __launch_bounds__(TPB) void k_scatter_children(Bind Bd) {
 // the particles of the cells that need the test go to one contiguous stretch
 // of the global list `dpart` per block.
 template <class Bind>
-__global__ __launch_bounds__(TPB) void k_dirty(Bind Bd) {
+__global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
@@ -1892,7 +1904,15 @@ __global__ __launch_bounds__(TPB) void k_dirty(Bind Bd) {
   }
   flush();
   __syncthreads();
-  if (threadIdx.x == 0) s_base = s_np ? atomicAdd(&D.cnt->n_dpart, s_np) : 0u;
+  if (threadIdx.x == 0) {
+    // The block's stretch of the list, in the stretch of its bank: the list
+    // positions that the particles of the bank's bricks have in the store.
+    const uint32_t lb = logical_block(V), q = bank_of(lb, V.G), first = bank_first(q, V.G);
+    const uint32_t k_first = chunk_at(nocc, TPB / 64, V.G, first).begin;
+    const uint32_t b0 = k_first < nocc ? D.binfo[D.occ[k_first]].x : 0u;
+    if (first == lb) D.bank[q].dpart0 = b0;
+    s_base = b0 + (s_np ? atomicAdd(&D.bank[q].n_dpart, s_np) : 0u);
+  }
   __syncthreads();
   const uint32_t nd = s_n, base = s_base;
   // The next dirty brick's list entry is loaded during this one.
@@ -2291,6 +2311,7 @@ __device__ __forceinline__ void stencil_entries(const Dev& D, const Stencil& st,
 constexpr uint32_t HIT_BUF = 64;  // stops held per wave before they are written out
 struct ContainShared {
   uint32_t n, tests;
+  uint32_t pre[N_BANKS + 1], dst[N_BANKS];  // entries of dpart before each bank's; their start
   float4 pos[TPB];
   uint32_t hit[TPB];
   uint3 ent[TPB / 64][CE_MAX];
@@ -2307,15 +2328,33 @@ struct ContainShared {
 template <bool S8, bool PER>
 __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint32_t epoch,
                                              ContainShared& S) {
-  if (threadIdx.x == 0) {
-    S.n = 0;
-    S.tests = 0;
+  const uint32_t lane = (uint32_t)lane_id();
+  if (threadIdx.x < 64u) {
+    const uint32_t c = lane < N_BANKS ? D.bank[lane].n_dpart : 0u;
+    uint32_t all;
+    const uint32_t before = wave_excl_scan(c, all);
+    if (lane < N_BANKS) {
+      S.pre[lane] = before;
+      S.dst[lane] = D.bank[lane].dpart0;
+    }
+    if (lane == 0u) {
+      S.pre[N_BANKS] = all;
+      S.n = 0;
+      S.tests = 0;
+    }
   }
   __syncthreads();
   const uint32_t lb = logical_block(V);
-  const uint32_t nd = D.cnt->n_dpart;
+  const uint32_t nd = S.pre[N_BANKS];
   const Chunk ch = chunk_of(V, nd, TPB);
-  const uint32_t lane = (uint32_t)lane_id();
+  // Entry k of the list, its bank looked for from the chunk's first one.
+  uint32_t bank0 = 0;
+  while (bank0 + 1u < N_BANKS && ch.begin >= S.pre[bank0 + 1u]) ++bank0;
+  auto entry = [&](uint32_t k) {
+    uint32_t q = bank0;
+    while (k >= S.pre[q + 1u]) ++q;
+    return D.dpart[S.dst[q] + (k - S.pre[q])];
+  };
   const uint32_t w = threadIdx.x >> 6;
   uint3* ent = S.ent[w];
   uint2* hbuf = S.hbuf[w];
@@ -2327,10 +2366,10 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
   uint32_t i1 = 0, i2 = 0;
   float4 q1 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   if (ch.begin + threadIdx.x < ch.end) {
-    i1 = D.dpart[ch.begin + threadIdx.x];
+    i1 = entry(ch.begin + threadIdx.x);
     q1 = D.P[i1];
   }
-  if (ch.begin + TPB + threadIdx.x < ch.end) i2 = D.dpart[ch.begin + TPB + threadIdx.x];
+  if (ch.begin + TPB + threadIdx.x < ch.end) i2 = entry(ch.begin + TPB + threadIdx.x);
   for (uint32_t k0 = ch.begin; k0 < ch.end; k0 += TPB) {
     const uint32_t k = k0 + threadIdx.x;
     const uint32_t i = i1;
@@ -2339,7 +2378,7 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
       i1 = i2;
       q1 = D.P[i1];
     }
-    if (k + 2u * TPB < ch.end) i2 = D.dpart[k + 2u * TPB];
+    if (k + 2u * TPB < ch.end) i2 = entry(k + 2u * TPB);
     uint32_t act = 0u, stp = 0u;
     Stencil st = {0, 0, 0, 0, 0, 0};
     if (k < ch.end) {
@@ -2418,7 +2457,9 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
   __syncthreads();
   if (threadIdx.x == 0) {
     D.newstop_cnt[lb] = S.n;
-    if (S.tests) atomicAdd(&D.cnt->pair_tests, (unsigned long long)S.tests);
+    Bank* bk = block_bank(D, V);
+    if (S.n) atomicAdd(&bk->n_newstop, S.n);
+    if (S.tests) atomicAdd(&bk->pair_tests, (unsigned long long)S.tests);
     if (lb == 0) atomicAdd(&D.cnt->dirty_tests, (unsigned long long)nd);
   }
 }
@@ -2448,26 +2489,37 @@ __global__ __launch_bounds__(TPB, 6) void k_contain(Bind Bd) {
   }
 }
 
+// Places of the stops in the stopped store: region after region of the
+// per-block stop lists, behind the n_stopped particles stored so far (k_finish
+// adds the step's).  A block with stops sums the counts of the regions before
+// its own; one atomic per region on the store's length took 20 ns each, one
+// after another (46 us for 1536 regions at 14M active particles, now 19 us).
 template <class Bind>
 __global__ __launch_bounds__(TPB) void k_stoplink(Bind Bd) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
   if (dead(D)) return;
-  __shared__ uint32_t s_base;
-  const uint32_t n = D.cnt->n_dpart, G = D.sched[TK_CONTAIN];
+  __shared__ uint32_t s_sum[TPB / 64];
+  const uint32_t G = D.sched[TK_CONTAIN];
   const Chunk rr = regions_of(V, G);
+  uint32_t any = 0;
+  for (uint32_t rg = rr.begin; rg < rr.end; ++rg) any |= D.newstop_cnt[rg];
+  if (!any) return;
+  uint32_t before = 0, n = 0;
+  for (uint32_t rg = threadIdx.x; rg < rr.begin; rg += TPB) before += D.newstop_cnt[rg];
+#pragma unroll
+  for (uint32_t q = 0; q < N_BANKS; ++q) n += D.bank[q].n_dpart;
+  uint32_t wsum;
+  (void)wave_excl_scan(before, wsum);
+  if (lane_id() == 0) s_sum[threadIdx.x >> 6] = wsum;
+  __syncthreads();
+  uint32_t base = D.cnt->n_stopped;
+#pragma unroll
+  for (uint32_t w = 0; w < TPB / 64; ++w) base += s_sum[w];
   for (uint32_t rg = rr.begin; rg < rr.end; ++rg) {
     const uint32_t cnt = D.newstop_cnt[rg];
-    if (cnt == 0u) continue;
     const uint32_t beg = chunk_at(n, TPB, G, rg).begin;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      s_base = atomicAdd(&D.cnt->n_stopped, cnt);
-      atomicAdd(&D.cnt->n_newstop, cnt);
-    }
-    __syncthreads();
-    const uint32_t base = s_base;
     for (uint32_t k = threadIdx.x; k < cnt; k += TPB) {
       const uint32_t i = D.newstop[beg + k];
       const uint4 r = with_fl(D.B[i], ST_STOPPED);
@@ -2481,6 +2533,7 @@ __global__ __launch_bounds__(TPB) void k_stoplink(Bind Bd) {
         }
       }
     }
+    base += cnt;
   }
 }
 
@@ -2643,12 +2696,39 @@ __global__ __launch_bounds__(TPB) void k_nuc_fire(Bind Bd) {
   }
 }
 
+template <class T>
+__device__ __forceinline__ T bank_sum(T v) {
+#pragma unroll
+  for (int o = 1; o < (int)N_BANKS; o <<= 1) v += __shfl_xor(v, o);
+  return v;
+}
+// One wave: the first N_BANKS lanes read a bank each.
 template <class Bind>
-__global__ void k_finish(Bind Bd, double dt) {
+__global__ __launch_bounds__(64) void k_finish(Bind Bd, double dt) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
   Counters* c = D.cnt;
+  Bank b = {};
+  if (threadIdx.x < N_BANKS) {
+    b = D.bank[threadIdx.x];
+    D.bank[threadIdx.x] = Bank{};
+  }
+  const unsigned long long advanced = bank_sum(b.advanced), exited = bank_sum(b.exited),
+                           spawners = bank_sum(b.spawners), children = bank_sum(b.children),
+                           pair_tests = bank_sum(b.pair_tests);
+  const uint32_t n_newstop = bank_sum(b.n_newstop);
+  uint32_t max_step = b.max_step;
+#pragma unroll
+  for (int o = 1; o < (int)N_BANKS; o <<= 1) max_step = max(max_step, (uint32_t)__shfl_xor(max_step, o));
+  if (threadIdx.x != 0) return;
+  c->advanced += advanced;
+  c->exited += exited;
+  c->spawners += spawners;
+  c->children += children;
+  c->pair_tests += pair_tests;
+  c->n_stopped += n_newstop;
+  if (max_step > c->max_step) c->max_step = max_step;
   if (c->err & (ERR_CAPACITY | HOLD)) return;
   // The step's sorted output becomes the next step's input; the step ends.
   c->par ^= 1u;
@@ -2657,10 +2737,8 @@ __global__ void k_finish(Bind Bd, double dt) {
   c->epoch += 1u;
   if (c->epoch == 0u) c->err |= ERR_CAPACITY;  // brick step stamps exhausted (2^32 steps)
   c->n_active = c->n_out + 6u * c->n_fired;
-  c->n_live = c->n_out - c->n_newstop + 6u * c->n_fired;
-  c->contained += c->n_newstop;
-  c->n_newstop = 0;
-  c->n_dpart = 0;
+  c->n_live = c->n_out - n_newstop + 6u * c->n_fired;
+  c->contained += n_newstop;
   c->n_cand = 0;
   c->n_fired = 0;
 }
@@ -4134,7 +4212,6 @@ hipError_t resident_grids(Dev& d) {
 void launch_advance(const Dev& d, float dt, hipStream_t s) {
   if (d.periodic) k_advance<Plain, 1><<<d.sched[TK_ADVANCE], TPB, 0, s>>>(Plain{d}, dt);
   else k_advance<Plain, 0><<<d.sched[TK_ADVANCE], TPB, 0, s>>>(Plain{d}, dt);
-  k_spawn_scan<<<1, 1024, 0, s>>>(Plain{d});
 }
 void launch_branch(const Dev& d, hipStream_t s) { k_branch<<<d.sched[TK_BRANCH], TPB, 0, s>>>(Plain{d}); }
 static void scan_bricks(const Dev& d, int mode, hipStream_t s) {
@@ -4168,7 +4245,7 @@ void launch_nucleate(const Dev& d, hipStream_t s) {
   k_nuc_test<<<grid_for(d.n_sites, 1024), TPB, 0, s>>>(Plain{d});
   k_nuc_fire<<<1, TPB, 0, s>>>(Plain{d});
 }
-void launch_finish(const Dev& d, double dt, hipStream_t s) { k_finish<<<1, 1, 0, s>>>(Plain{d}, dt); }
+void launch_finish(const Dev& d, double dt, hipStream_t s) { k_finish<<<1, 64, 0, s>>>(Plain{d}, dt); }
 void launch_reset_stats(const Dev& d, hipStream_t s) { k_reset_stats<<<1, 1, 0, s>>>(Plain{d}); }
 void launch_stopped_rebuild(const Dev& d, hipStream_t s) {
   k_srb_count<<<STREAM_GRID, TPB, 0, s>>>(Plain{d});
@@ -4362,7 +4439,6 @@ void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s) {
     k_advance<Batch, 2><<<L.site[BS_ADVANCE].total, TPB, 0, s>>>(bind_of(L, BS_ADVANCE), (float)dt);
   else
     k_advance<Batch, 0><<<L.site[BS_ADVANCE].total, TPB, 0, s>>>(bind_of(L, BS_ADVANCE), (float)dt);
-  k_spawn_scan<<<one, 1024, 0, s>>>(bind_of(L, BS_ONE));
   k_branch<<<L.site[BS_BRANCH].total, TPB, 0, s>>>(bind_of(L, BS_BRANCH));
   batch_scan(0);
   k_cellscan<<<L.site[BS_CELLSCAN].total, TPB, 0, s>>>(bind_of(L, BS_CELLSCAN), 0);
@@ -4376,7 +4452,7 @@ void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s) {
     k_nuc_test<<<L.site[BS_NUCTEST].total, TPB, 0, s>>>(bind_of(L, BS_NUCTEST));
     k_nuc_fire<<<L.site[BS_NUCFIRE].total, TPB, 0, s>>>(bind_of(L, BS_NUCFIRE));
   }
-  k_finish<<<one, 1, 0, s>>>(bind_of(L, BS_ONE), dt);
+  k_finish<<<one, 64, 0, s>>>(bind_of(L, BS_ONE), dt);
   k_srb_count<<<L.site[BS_RESORT].total, TPB, 0, s>>>(bind_of(L, BS_RESORT));
   batch_scan(1);
   k_cellscan<<<L.site[BS_RESORT].total, TPB, 0, s>>>(bind_of(L, BS_RESORT), 1);

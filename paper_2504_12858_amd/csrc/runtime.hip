@@ -32,9 +32,9 @@ struct Geometry {
 };
 
 struct Layout {
-  size_t A, B, P, spawn, spslot, spawn_cnt, spawn_off, newstop, newstop_cnt, S, PS, S2, PS2, snext, shead, sstart,
+  size_t A, B, P, spawn, spslot, spawn_cnt, newstop, newstop_cnt, S, PS, S2, PS2, snext, shead, sstart,
       bsinfo, ccnt, cstart, bcnt, binfo, bmeta, dlist, dlist_cnt, dpart, dmask, doff, bown, cown, smask, occ, scan_tmp, ckeys, cbits, clist, dirkeys, gtab, gbox,
-      stab, sstate, cand, sgrain, fgrid, gcnt, fcmin, fcoarse, mslots, greach, gsite, gdead, cnt, dig, total;
+      stab, sstate, cand, sgrain, fgrid, gcnt, fcmin, fcoarse, mslots, greach, gsite, gdead, cnt, bank, dig, total;
 };
 
 uint64_t next_pow2(uint64_t v) {
@@ -128,7 +128,6 @@ Layout layout(const ge_params* p, const Geometry& g) {
   L.spawn = put(4 * cp);
   L.spslot = put(4 * cp);
   L.spawn_cnt = put(4 * ge::STREAM_GRID);
-  L.spawn_off = put(4 * (ge::STREAM_GRID + 1));
   L.newstop = put(4 * cp);
   L.newstop_cnt = put(4 * ge::STREAM_GRID);
   L.S = put(16 * cs);
@@ -175,6 +174,7 @@ Layout layout(const ge_params* p, const Geometry& g) {
   L.gsite = put(4 * (uint64_t)p->cap_grains);
   L.gdead = put(4 * (uint64_t)p->cap_grains);
   L.cnt = put(sizeof(ge::Counters));
+  L.bank = put(sizeof(ge::Bank) * ge::N_BANKS);
   L.dig = put(64);
   L.total = off;
   return L;
@@ -387,6 +387,7 @@ static ge_status reset_device(ge_ctx* c) {
   HIPCHK(c, hipMemsetAsync(w + L.dirkeys, 0xFF, 8 * (g.slots / ge::CLAIM_BLOCK_SLOTS), s));
   HIPCHK(c, hipMemsetAsync(w + L.cbits, 0, 192 * g.slots, s));
   HIPCHK(c, hipMemsetAsync(w + L.cnt, 0, sizeof(ge::Counters), s));
+  HIPCHK(c, hipMemsetAsync(w + L.bank, 0, sizeof(ge::Bank) * ge::N_BANKS, s));
   HIPCHK(c, hipMemsetAsync(w + L.cand, 0, 4 * (uint64_t)std::max(c->p.cap_sites, 1), s));
   HIPCHK(c, hipMemsetAsync(w + L.sgrain, 0xFF, 4 * (uint64_t)std::max(c->p.cap_sites, 1), s));
   HIPCHK(c, hipMemsetAsync(w + L.greach, 0, 4 * (uint64_t)c->p.cap_grains, s));
@@ -516,7 +517,6 @@ ge_status ge_create(const ge_params* p, void* workspace, size_t bytes, void* str
   d.spawn = (uint32_t*)(w + L.spawn);
   d.spslot = (uint32_t*)(w + L.spslot);
   d.spawn_cnt = (uint32_t*)(w + L.spawn_cnt);
-  d.spawn_off = (uint32_t*)(w + L.spawn_off);
   d.newstop = (uint32_t*)(w + L.newstop);
   d.newstop_cnt = (uint32_t*)(w + L.newstop_cnt);
   d.S = (uint4*)(w + L.S);
@@ -558,6 +558,7 @@ ge_status ge_create(const ge_params* p, void* workspace, size_t bytes, void* str
   d.sgrain = (uint32_t*)(w + L.sgrain);
   d.n_sites = 0;
   d.cnt = (ge::Counters*)(w + L.cnt);
+  d.bank = (ge::Bank*)(w + L.bank);
   d.resort_every = c->resort_every;
   ge_status st = hip_check(c, ge::resident_grids(d), "occupancy query");
   if (st == GE_OK) st = sync_dev(c);

@@ -421,3 +421,24 @@ def test_brick_scan_forms_agree():
         batch.step(dt, steps)
         assert all(state(m) == want for m in batch.members)
         batch.close()
+
+
+@pytest.mark.parametrize("blocks", [1, 3, 8, 15, 16, 17, 200])
+def test_few_blocks_per_launch_change_nothing(blocks):
+    """Fewer blocks than banks of per-step sums, as many, one more, and a
+    number that divides into them unevenly: the state and the counters after
+    40 steps of contact are those of the default schedule."""
+    require_gpu()
+    w = _scaled_directional()
+    a, b = context_for(w), context_for(w)
+    names = list(a.schedule())
+    b.set_schedule({n: blocks for n in names})
+    for c in (a, b):
+        c.step(w.dt, 200)
+    sa, sb = a.step(w.dt, 40), b.step(w.dt, 40)
+    sa.pop("pair_tests")
+    sb.pop("pair_tests")
+    assert sa == sb and sa["contained"] > 0 and sa["children"] > 0
+    assert gpu_parts(a)[0].tobytes() == gpu_parts(b)[0].tobytes()
+    a.close()
+    b.close()
