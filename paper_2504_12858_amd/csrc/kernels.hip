@@ -4213,7 +4213,10 @@ void launch_advance(const Dev& d, float dt, hipStream_t s) {
   if (d.periodic) k_advance<Plain, 1><<<d.sched[TK_ADVANCE], TPB, 0, s>>>(Plain{d}, dt);
   else k_advance<Plain, 0><<<d.sched[TK_ADVANCE], TPB, 0, s>>>(Plain{d}, dt);
 }
-void launch_branch(const Dev& d, hipStream_t s) { k_branch<<<d.sched[TK_BRANCH], TPB, 0, s>>>(Plain{d}); }
+// Without branching a step has no spawners.
+void launch_branch(const Dev& d, hipStream_t s) {
+  if (d.branching) k_branch<<<d.sched[TK_BRANCH], TPB, 0, s>>>(Plain{d});
+}
 static void scan_bricks(const Dev& d, int mode, hipStream_t s) {
   const uint32_t ntiles = (uint32_t)((d.n_bricks + SCAN_TILE - 1) / SCAN_TILE);
   if (d.n_bricks <= SCAN_ONE_LAUNCH) {
@@ -4228,7 +4231,7 @@ static void scan_bricks(const Dev& d, int mode, hipStream_t s) {
 void launch_scan(const Dev& d, hipStream_t s) { scan_bricks(d, 0, s); }
 void launch_scatter(const Dev& d, hipStream_t s) { k_scatter<<<d.sched[TK_SCATTER], TPB, 0, s>>>(Plain{d}); }
 void launch_scatter_children(const Dev& d, hipStream_t s) {
-  k_scatter_children<<<d.sched[TK_CHILDREN], TPB, 0, s>>>(Plain{d});
+  if (d.branching) k_scatter_children<<<d.sched[TK_CHILDREN], TPB, 0, s>>>(Plain{d});
 }
 void launch_dirty(const Dev& d, hipStream_t s) {
   k_dirty<<<d.sched[TK_DIRTY], TPB, 0, s>>>(Plain{d});
