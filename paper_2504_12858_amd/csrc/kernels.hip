@@ -634,11 +634,16 @@ __device__ __forceinline__ Run wave_run(uint32_t key) {
   return r;
 }
 
-// Contiguous chunk of [0, n) per block; blocks on one XCD (round-robin
-// dispatch: block b runs on XCD b % 8) get neighbouring chunks so that they
-// share that XCD's L2.
+// Contiguous chunk of [0, n) per block (whole granules), logical block lb of
+// the W that have work.  Blocks are dispatched round-robin (block b runs on
+// XCD b % 8), and an XCD's blocks get neighbouring chunks, so that they share
+// its L2; with fewer chunks than blocks every XCD gets an eighth of the
+// chunks.  (Dealing the blocks out in order of the XCDs whatever their number
+// left most of the chip idle with few chunks: 285k active particles are 1113
+// chunks of 2048 blocks and ran on five of the eight XCDs, the containment
+// of a columnar run took 86 us instead of 52.)
 struct Chunk {
-  uint32_t begin, end;
+  uint32_t begin, end, lb, W;
 };
 // Block index and grid size of a launch as seen by one context: the real
 // ones for a plain launch, the context's share of the blocks for a batched
@@ -646,44 +651,62 @@ struct Chunk {
 struct VGrid {
   uint32_t b, G;
 };
-__device__ __forceinline__ uint32_t logical_block(const VGrid& V) {
-  const uint32_t G = V.G, b = V.b;
-  return ((G & 7u) == 0u) ? (b & 7u) * (G >> 3) + (b >> 3) : b;
+// Logical block, with the first W of the G logical blocks spread evenly over
+// the XCDs in use (a one-to-one map: the blocks without work get the others):
+// one for up to 32 chunks, a block per compute unit of an XCD, then two, four
+// and eight, since few chunks read each other's data from one L2 faster than
+// from memory (4k active particles, all eight XCDs: 3 % slower steps).
+__device__ __forceinline__ uint32_t logical_block(const VGrid& V, uint32_t W) {
+  if (V.G & 7u) return V.b;
+  const uint32_t per = V.G >> 3, x = V.b & 7u, j = V.b >> 3, room = min(32u, per);
+  const uint32_t sh = W <= room ? 0u : W <= 2u * room ? 1u : W <= 4u * room ? 2u : 3u;
+  const uint32_t first = min(x * W >> sh, W), len = min((x + 1u) * W >> sh, W) - first;
+  return j < len ? first + j : W + (x * per - first) + (j - len);
 }
-// Chunk of [0, n) of logical block lb on a grid of G blocks (whole granules).
-__device__ __forceinline__ Chunk chunk_at(uint32_t n, uint32_t granule, uint32_t G, uint32_t lb) {
-  uint32_t per = (n + G - 1u) / G;
-  per = (per + granule - 1u) / granule * granule;
-  const uint64_t b = (uint64_t)lb * per;
+// Chunk length and number of chunks of [0, n) on a grid of G blocks.
+__device__ __forceinline__ uint32_t chunk_len(uint32_t n, uint32_t granule, uint32_t G) {
+  return ((n + G - 1u) / G + granule - 1u) / granule * granule;
+}
+__device__ __forceinline__ uint32_t chunk_count(uint32_t n, uint32_t granule, uint32_t G) {
+  const uint32_t per = chunk_len(n, granule, G);
+  return n ? (n + per - 1u) / per : 0u;
+}
+// First item of chunk lb.
+__device__ __forceinline__ uint32_t chunk_begin(uint32_t n, uint32_t granule, uint32_t G, uint32_t lb) {
+  const uint64_t b = (uint64_t)lb * chunk_len(n, granule, G);
+  return (uint32_t)(b < n ? b : n);
+}
+__device__ __forceinline__ Chunk chunk_of(const VGrid& V, uint32_t n, uint32_t granule) {
+  const uint32_t per = chunk_len(n, granule, V.G);
   Chunk c;
+  c.W = n ? (n + per - 1u) / per : 0u;
+  c.lb = logical_block(V, c.W);
+  const uint64_t b = (uint64_t)c.lb * per, e = b + per;
   c.begin = (uint32_t)(b < n ? b : n);
-  const uint64_t e = b + per;
   c.end = (uint32_t)(e < n ? e : n);
   return c;
 }
-__device__ __forceinline__ Chunk chunk_of(const VGrid& V, uint32_t n, uint32_t granule) {
-  return chunk_at(n, granule, V.G, logical_block(V));
+// Bank of chunk lb of W (consecutive chunks share a bank), and the first
+// chunk of bank q.
+__device__ __forceinline__ uint32_t bank_of(uint32_t lb, uint32_t W) {
+  return lb * N_BANKS / W;  // lb < W <= STREAM_GRID
 }
-// Bank of logical block lb of G blocks, and the first logical block of bank q
-// (consecutive blocks share a bank).
-__device__ __forceinline__ uint32_t bank_of(uint32_t lb, uint32_t G) {
-  return lb * N_BANKS / G;  // G <= STREAM_GRID
+__device__ __forceinline__ uint32_t bank_first(uint32_t q, uint32_t W) {
+  return (q * W + N_BANKS - 1u) / N_BANKS;
 }
-__device__ __forceinline__ uint32_t bank_first(uint32_t q, uint32_t G) {
-  return (q * G + N_BANKS - 1u) / N_BANKS;
-}
+// Bank of a block's sums: any, spread over the blocks.
 __device__ __forceinline__ Bank* block_bank(const Dev& D, const VGrid& V) {
-  return D.bank + bank_of(logical_block(V), V.G);
+  return D.bank + V.b % N_BANKS;
 }
-// Regions of a per-block list written by a kernel of G_w blocks, as read by
-// this block: an even share [lb G_w / G, (lb + 1) G_w / G) of them, so that
-// with grids that are multiples of 8 a region is read on the XCD that wrote it.
-__device__ __forceinline__ Chunk regions_of(const VGrid& V, uint32_t G_w) {
-  const uint64_t lb = logical_block(V), G = V.G;
-  Chunk c;
-  c.begin = (uint32_t)(lb * G_w / G);
-  c.end = (uint32_t)((lb + 1u) * G_w / G);
-  return c;
+// The W_w regions of a per-block list that hold items, as read by this block:
+// an even share [lb W_w / G, (lb + 1) W_w / G) of them, so that with grids
+// that are multiples of 8 a region is read on the XCD that wrote it.
+struct Share {
+  uint32_t begin, end;
+};
+__device__ __forceinline__ Share regions_of(const VGrid& V, uint32_t W_w) {
+  const uint32_t lb = logical_block(V, V.G), G = V.G;
+  return {(uint32_t)((uint64_t)lb * W_w / G), (uint32_t)((uint64_t)(lb + 1u) * W_w / G)};
 }
 
 // A context whose state must not change: a capacity error, or held.
@@ -1161,7 +1184,7 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
     atomicOr(D.cbits + (size_t)slot * 24 + CB_NOW + (b >> 6), 1ull << (b & 63));
   }
   if (threadIdx.x == 0) {
-    D.spawn_cnt[logical_block(V)] = s_nsp;
+    D.spawn_cnt[ch.lb] = s_nsp;
     Bank* bk = block_bank(D, V);
     if (s_nsp) atomicAdd(&bk->n_spawn, s_nsp);
     if (s_adv) atomicAdd(&bk->advanced, (unsigned long long)s_adv);
@@ -1221,7 +1244,7 @@ __device__ __forceinline__ uint32_t spawn_pos(const SpawnView& v, const uint32_t
     if (s_off[mid] <= i) lo = mid;
     else hi = mid;
   }
-  return chunk_at(v.n, TPB, v.G, lo).begin + (i - s_off[lo]);
+  return chunk_begin(v.n, TPB, v.G, lo) + (i - s_off[lo]);
 }
 
 // At most 80 registers, for six waves per SIMD: more waves in flight hide
@@ -1776,6 +1799,7 @@ __global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
   __syncthreads();
   const uint32_t nocc = D.cnt->n_occ;
   const Chunk ch = chunk_of(V, nocc, TPB / 64);
+  if (ch.lb >= ch.W) return;
   const int lane = lane_id();
   const int nbx = D.nb[0], nby = D.nb[1], nbz = D.nb[2];
   // Neighbour bricks the 3x3x3 cells around this lane's cell reach: bit
@@ -1907,10 +1931,9 @@ __global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
   if (threadIdx.x == 0) {
     // The block's stretch of the list, in the stretch of its bank: the list
     // positions that the particles of the bank's bricks have in the store.
-    const uint32_t lb = logical_block(V), q = bank_of(lb, V.G), first = bank_first(q, V.G);
-    const uint32_t k_first = chunk_at(nocc, TPB / 64, V.G, first).begin;
-    const uint32_t b0 = k_first < nocc ? D.binfo[D.occ[k_first]].x : 0u;
-    if (first == lb) D.bank[q].dpart0 = b0;
+    const uint32_t q = bank_of(ch.lb, ch.W), first = bank_first(q, ch.W);
+    const uint32_t b0 = D.binfo[D.occ[chunk_begin(nocc, TPB / 64, V.G, first)]].x;
+    if (first == ch.lb) D.bank[q].dpart0 = b0;
     s_base = b0 + (s_np ? atomicAdd(&D.bank[q].n_dpart, s_np) : 0u);
   }
   __syncthreads();
@@ -2308,6 +2331,7 @@ __device__ __forceinline__ void stencil_entries(const Dev& D, const Stencil& st,
 }
 
 
+constexpr uint32_t CONTAIN_GRANULE = 64;  // particles per chunk: whole waves
 constexpr uint32_t HIT_BUF = 64;  // stops held per wave before they are written out
 struct ContainShared {
   uint32_t n, tests;
@@ -2344,9 +2368,9 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
     }
   }
   __syncthreads();
-  const uint32_t lb = logical_block(V);
   const uint32_t nd = S.pre[N_BANKS];
-  const Chunk ch = chunk_of(V, nd, TPB);
+  const Chunk ch = chunk_of(V, nd, CONTAIN_GRANULE);
+  const uint32_t lb = ch.lb;
   // Entry k of the list, its bank looked for from the chunk's first one.
   uint32_t bank0 = 0;
   while (bank0 + 1u < N_BANKS && ch.begin >= S.pre[bank0 + 1u]) ++bank0;
@@ -2502,14 +2526,15 @@ __global__ __launch_bounds__(TPB) void k_stoplink(Bind Bd) {
   if (dead(D)) return;
   __shared__ uint32_t s_sum[TPB / 64];
   const uint32_t G = D.sched[TK_CONTAIN];
-  const Chunk rr = regions_of(V, G);
+  uint32_t n = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < N_BANKS; ++q) n += D.bank[q].n_dpart;
+  const Share rr = regions_of(V, chunk_count(n, CONTAIN_GRANULE, G));
   uint32_t any = 0;
   for (uint32_t rg = rr.begin; rg < rr.end; ++rg) any |= D.newstop_cnt[rg];
   if (!any) return;
-  uint32_t before = 0, n = 0;
+  uint32_t before = 0;
   for (uint32_t rg = threadIdx.x; rg < rr.begin; rg += TPB) before += D.newstop_cnt[rg];
-#pragma unroll
-  for (uint32_t q = 0; q < N_BANKS; ++q) n += D.bank[q].n_dpart;
   uint32_t wsum;
   (void)wave_excl_scan(before, wsum);
   if (lane_id() == 0) s_sum[threadIdx.x >> 6] = wsum;
@@ -2519,7 +2544,7 @@ __global__ __launch_bounds__(TPB) void k_stoplink(Bind Bd) {
   for (uint32_t w = 0; w < TPB / 64; ++w) base += s_sum[w];
   for (uint32_t rg = rr.begin; rg < rr.end; ++rg) {
     const uint32_t cnt = D.newstop_cnt[rg];
-    const uint32_t beg = chunk_at(n, TPB, G, rg).begin;
+    const uint32_t beg = chunk_begin(n, CONTAIN_GRANULE, G, rg);
     for (uint32_t k = threadIdx.x; k < cnt; k += TPB) {
       const uint32_t i = D.newstop[beg + k];
       const uint4 r = with_fl(D.B[i], ST_STOPPED);
