@@ -456,8 +456,9 @@ ge_status ge_restore_state(ge_ctx* ctx, const void* blob, size_t bytes);
    stops.  ge_profile_read synchronises and returns, per phase, the summed
    GPU time in milliseconds and the number of steps recorded.  Phases: field
    resample, advance (with the reached-site marks), branch, brick and cell
-   scan, scatter, child scatter, dirty-brick pass, containment, stop linking,
-   nucleation, finish, stopped-store re-sort. */
+   scan, scatter (the child scatter runs in its launch), child scatter (no
+   time of its own), dirty-brick pass, containment, stop linking, nucleation,
+   finish, stopped-store re-sort. */
 #define GE_N_PHASES 12
 ge_status ge_profile(ge_ctx* ctx, int32_t on);
 ge_status ge_profile_read(ge_ctx* ctx, double* ms /*[GE_N_PHASES]*/, int64_t* steps);

@@ -288,7 +288,6 @@ void launch_advance(const Dev& d, float dt, hipStream_t s);
 void launch_branch(const Dev& d, hipStream_t s);
 void launch_scan(const Dev& d, hipStream_t s);
 void launch_scatter(const Dev& d, hipStream_t s);
-void launch_scatter_children(const Dev& d, hipStream_t s);
 void launch_dirty(const Dev& d, hipStream_t s);
 void launch_contain(const Dev& d, hipStream_t s);
 void launch_stoplink(const Dev& d, hipStream_t s);
