@@ -2106,47 +2106,6 @@ __device__ bool foreign_within(const Dev& D, uint32_t epoch, P3 p, uint32_t g, u
   return false;
 }
 
-// Owner words of one cell for a particle of grain g: whether the cell holds
-// active (this step) or stopped particles of another grain.  Two independent
-// 8-byte loads: the brick word {step, grain of a single-grain brick or
-// BOWN_CELLS} and the cell word {active owner, stopped owner}.  A brick not
-// occupied this step holds no active particle.
-struct CellOwners {
-  uint32_t ci, b;
-  bool act, stp;
-};
-
-// With periodic axes a stencil cell past a face wraps, and every particle
-// there is a candidate: the owner word cannot tell a particle's own period
-// from the next one.
-// The brick word of the previous cell is reused when the cell lies in the
-// same brick (the cells of a stencil mostly do): brick cb, its word cbw.
-template <bool PER>
-__device__ __forceinline__ CellOwners cell_owners(const Dev& D, uint32_t epoch, int x, int y,
-                                                  int z, uint32_t g, uint32_t& cb, uint2& cbw) {
-  bool cross = false;
-  if constexpr (PER) {
-    const int xw = wrap_cell(x, D.n[0]), yw = wrap_cell(y, D.n[1]), zw = wrap_cell(z, D.n[2]);
-    cross = xw != x || yw != y || zw != z;
-    x = xw;
-    y = yw;
-    z = zw;
-  }
-  CellOwners o;
-  o.b = brick_index(D, x, y, z);
-  o.ci = o.b * (uint32_t)BRICK_CELLS + local_index(x, y, z);
-  if (o.b != cb) {
-    cb = o.b;
-    cbw = D.bown[o.b];
-  }
-  const uint2 bw = cbw;
-  const uint2 cw = D.cown[o.ci];
-  const uint32_t aown = bw.x != epoch ? NIL : (bw.y == BOWN_CELLS ? cw.x : bw.y);
-  o.act = aown != NIL && (cross || aown != g);
-  o.stp = cw.y != NIL && (cross || cw.y != g);
-  return o;
-}
-
 // Candidates Q[st, en) in groups of four independent loads (the tail group
 // repeats its last candidate, which does not change the outcome).
 template <bool PER>
@@ -2167,46 +2126,6 @@ __device__ __forceinline__ bool scan_range(const Dev& D, const float4* __restric
   return false;
 }
 
-// Candidate ranges of one cell: active particles [ast, aen), cell-sorted
-// stopped particles [sst, sen), recent stops from list head hd.
-struct CellRanges {
-  uint32_t ast, aen, sst, sen, hd;
-};
-
-// The brick's end of the active store is read only for its last cell; its
-// stopped-store word is reused from the previous cell of the same brick
-// (brick sb, word sbw).
-__device__ __forceinline__ CellRanges cell_ranges(const Dev& D, const CellOwners& o, uint32_t& sb,
-                                                  uint2& sbw) {
-  CellRanges r = {0u, 0u, 0u, 0u, NIL};
-  const bool last = (o.ci & (uint32_t)(BRICK_CELLS - 1)) == (uint32_t)(BRICK_CELLS - 1);
-  if (o.act) {
-    r.ast = D.cstart[o.ci];
-    if (last) {
-      const uint2 inf = D.binfo[o.b];
-      r.aen = inf.x + inf.y;
-    } else {
-      r.aen = D.cstart[o.ci + 1];
-    }
-  }
-  if (o.stp) {
-    if (o.b != sb) {
-      sb = o.b;
-      sbw = D.bsinfo[o.b];
-    }
-    const uint2 bs = sbw;
-    const uint32_t t0 = D.sstart[o.ci];
-    const uint32_t t1 = last ? 0u : D.sstart[o.ci + 1];
-    const uint32_t hd = D.shead[o.ci];
-    if (bs.y > 0u) {
-      r.sst = t0;
-      r.sen = last ? bs.x + bs.y : t1;
-    }
-    r.hd = hd;
-  }
-  return r;
-}
-
 template <bool PER>
 __device__ __forceinline__ bool walk_recent(const Dev& D, uint32_t j, P3 p, uint32_t g,
                                             uint32_t& tests) {
@@ -2219,34 +2138,27 @@ __device__ __forceinline__ bool walk_recent(const Dev& D, uint32_t j, P3 p, uint
 
 // ----------------------------------------------- wave-shared candidates ---
 // The candidates of a particle are very uneven (from none to long cell lists),
-// and a wave waits for its slowest lane.  The containment therefore lists,
-// for the wave's 64 particles, every candidate source of every stencil cell
-// that holds another grain (a range of the cell-sorted active store, a range
-// of the cell-sorted stopped store, the head of a recent-stop list) in shared
-// memory, and the lanes take the sources in turn, whichever particle they
-// belong to.  Entry: {first index or list head, length, kind << 6 | lane of
-// the particle}.
-constexpr int CE_MAX = 384;  // entries per wave and round
+// and a wave waits for its slowest lane.  The containment therefore lists, for
+// the wave's particles, every stencil cell that holds another grain (a pair of
+// particle and cell), then every candidate source of these cells (a range of
+// the cell-sorted active store, a range of the cell-sorted stopped store, the
+// head of a recent-stop list; empty ones are left out), both in shared memory,
+// and the lanes take pairs and sources in turn, whichever particle they belong
+// to.  Pair: {particle, cell of the stencil << 6, active << 11, stopped << 12}.
+// Source: {first index or list head, length, kind << 6 | particle}.
+constexpr uint32_t PAIR_MAX = 512;  // pairs per wave and round
+constexpr uint32_t CE_MAX = 256;    // sources per wave and round
 constexpr uint32_t CE_ACTIVE = 0u, CE_STOPPED = 1u, CE_RECENT = 2u;
 
-// Cell k of the stencil: S8 (2 x 2 x 2 cells, k < 8) or 3 x 3 x 3 (k < 27).
-// False for a cell outside the clamped stencil (or the repeat of a clamped
-// axis in the 2 x 2 x 2 case).
+// Stencil: 2 x 2 x 2 cells (S8; a clamped axis has one) or 3 x 3 x 3.
 struct Stencil {
   int x0, x1, y0, y1, z0, z1;
 };
+// Cell k of the stencil, relative to (x0, y0, z0).
 template <bool S8>
-__device__ __forceinline__ bool stencil_cell(const Stencil& s, int k, int& x, int& y, int& z) {
-  if (S8) {
-    x = (k & 1) ? s.x1 : s.x0;
-    y = (k & 2) ? s.y1 : s.y0;
-    z = (k & 4) ? s.z1 : s.z0;
-    return !(((k & 1) && s.x1 == s.x0) || ((k & 2) && s.y1 == s.y0) || ((k & 4) && s.z1 == s.z0));
-  }
-  x = s.x0 + k % 3;
-  y = s.y0 + (k / 3) % 3;
-  z = s.z0 + k / 9;
-  return x <= s.x1 && y <= s.y1 && z <= s.z1;
+__device__ __forceinline__ C3 stencil_step(int k) {
+  if (S8) return C3{k & 1, (k >> 1) & 1, k >> 2};
+  return C3{k % 3, (k / 3) % 3, k / 9};
 }
 
 // For the 2 x 2 x 2 stencil: the particle's own cell and, per axis, its
@@ -2300,100 +2212,52 @@ __device__ __forceinline__ bool near_skips(const Near& n, int x, int y, int z) {
   return d2 > n.lim2;
 }
 
-// Foreign-owner bits of the stencil cells (bit k: cell k holds active,
-// resp. stopped particles of another grain).  Owner words are loaded one
-// z-layer of the stencil at a time, all cells of a layer together.  With
-// the 2 x 2 x 2 stencil, cells out of reach (near_skips) are left out, and
-// so are stopped particles whose slabs in their cell lie out of reach
-// (slabs_far).  Both take the stencil cells unwrapped: on a periodic axis
-// a cell past a face is the image of the cell it wraps to, at the distance
-// of that image, and with r_c <= h/2 only the images through the stencil's
-// own side can come within r_c.
-template <bool S8, bool PER>
-__device__ __forceinline__ void stencil_owners(const Dev& D, uint32_t epoch, const Stencil& st,
-                                               const Near& nr, uint32_t g, uint32_t& act,
-                                               uint32_t& stp) {
-  constexpr int NL = S8 ? 2 : 3, PL = S8 ? 4 : 9;
-  act = 0u;
-  stp = 0u;
-  uint32_t cb = NIL;
-  uint2 cbw = make_uint2(0u, 0u);
-  for (int l = 0; l < NL; ++l) {
-#pragma unroll
-    for (int u = 0; u < PL; ++u) {
-      const int k = l * PL + u;
-      int x, y, z;
-      if (!stencil_cell<S8>(st, k, x, y, z)) continue;
-      if (S8 && near_skips(nr, x, y, z)) continue;
-      const CellOwners o = cell_owners<PER>(D, epoch, x, y, z, g, cb, cbw);
-      bool ostp = o.stp;
-      if (S8) {
-        // The slab mask, loaded with the owner words: stopped particles out
-        // of reach are no sources.
-        const uint32_t m = D.smask[o.ci];
-        ostp = ostp && !slabs_far(nr, m, x, y, z);
-      }
-      act |= (uint32_t)o.act << k;
-      stp |= (uint32_t)ostp << k;
-    }
-  }
+// Particles per wave of the containment: 64, or as few as eight where that
+// still leaves waves without any (a power of two).  Each particle then has
+// 64 / P lanes, which share its stencil cells: with 64 particles per wave a
+// state of a few thousand tested particles leaves the chip to a few dozen
+// waves, each working off hundreds of pairs.
+__device__ __forceinline__ uint32_t contain_group(uint32_t nd, uint32_t G) {
+  uint32_t P = 64u;
+  while (P > 8u && (uint64_t)nd <= (uint64_t)G * (TPB / 64) * (P / 2u)) P >>= 1;
+  return P;
 }
 
-// Writes the entries of the cells with bits in act / stp to e[0 ..).
-template <bool S8, bool PER>
-__device__ __forceinline__ void stencil_entries(const Dev& D, const Stencil& st, uint32_t act,
-                                                uint32_t stp, uint32_t lane, uint3* e) {
-  uint32_t n = 0;
-  uint32_t sb = NIL;
-  uint2 sbw = make_uint2(0u, 0u);
-  auto cell = [&](int k) {
-    if (!(((act | stp) >> k) & 1u)) return;
-    int x, y, z;
-    (void)stencil_cell<S8>(st, k, x, y, z);
-    if constexpr (PER) {
-      x = wrap_cell(x, D.n[0]);
-      y = wrap_cell(y, D.n[1]);
-      z = wrap_cell(z, D.n[2]);
-    }
-    CellOwners o;
-    o.b = brick_index(D, x, y, z);
-    o.ci = o.b * (uint32_t)BRICK_CELLS + local_index(x, y, z);
-    o.act = (act >> k) & 1u;
-    o.stp = (stp >> k) & 1u;
-    const CellRanges r = cell_ranges(D, o, sb, sbw);
-    if (o.act) e[n++] = make_uint3(r.ast, r.aen - r.ast, (CE_ACTIVE << 6) | lane);
-    if (o.stp) {
-      e[n++] = make_uint3(r.sst, r.sen - r.sst, (CE_STOPPED << 6) | lane);
-      e[n++] = make_uint3(r.hd, 0u, (CE_RECENT << 6) | lane);
-    }
-  };
-  if constexpr (S8) {
-#pragma unroll 4
-    for (int k = 0; k < 8; ++k) cell(k);
-  } else {
-    for (int k = 0; k < 27; ++k) cell(k);
-  }
-}
-
-
-constexpr uint32_t CONTAIN_GRANULE = 64;  // particles per chunk: whole waves
 constexpr uint32_t HIT_BUF = 64;  // stops held per wave before they are written out
 struct ContainShared {
   uint32_t n, tests;
   uint32_t pre[N_BANKS + 1], dst[N_BANKS];  // entries of dpart before each bank's; their start
   float4 pos[TPB];
+  int3 base[TPB];  // first cell of the stencil
   uint32_t hit[TPB];
+  uint16_t pair[TPB / 64][PAIR_MAX];
   uint3 ent[TPB / 64][CE_MAX];
   uint2 hbuf[TPB / 64][HIT_BUF];  // {position in the block's stop list, particle}
 };
 
 // Containment (particles of two grains that meet stop, Sec. 2.1.2; the
 // neighbour search, Sec. 2.3) of the particles listed in dpart (those of the
-// cells of dirty bricks that can reach another grain), 64 per wave: owner
-// words of the stencil cells per particle, then the wave's candidate sources
-// shared out among its lanes, in rounds of at most CE_MAX entries (a lane's
-// sources stay in one round).  Hits go to the block's region of the stop
-// list.
+// cells of dirty bricks that can reach another grain), P per wave.  Owner words
+// of the stencil cells per particle, several cells' words requested together:
+// the brick word {step, grain of a single-grain brick or BOWN_CELLS} (read once
+// for the cells of the particle's own brick) and the cell word {active owner,
+// stopped owner}.  Then the wave's pairs and sources shared out among its lanes
+// (a lane's pairs stay in one round).  Hits go to the block's region of the
+// stop list.
+//
+// With the 2 x 2 x 2 stencil, cells out of reach (near_skips) are left out, and
+// so are stopped particles whose slabs in their cell lie out of reach
+// (slabs_far).  Both take the stencil cells unwrapped: on a periodic axis a
+// cell past a face is the image of the cell it wraps to, at the distance of
+// that image, and with r_c <= h/2 only the images through the stencil's own
+// side can come within r_c.  Every particle in such a cell is a candidate: the
+// owner word cannot tell a particle's own period from the next one.
+//
+// Bound by the latency of its scattered loads, hence as many of them in flight
+// as the registers of six waves per SIMD hold (U cells).  Against one cell's
+// words at a time, each lane writing the sources of its own cells and 64
+// particles in every wave: 315 -> 261 us at 14M active particles (2 x 2 x 2
+// cells), 52 -> 21 us at 285k and 43 -> 12 us at 4k (3 x 3 x 3).
 template <bool S8, bool PER>
 __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint32_t epoch,
                                              ContainShared& S) {
@@ -2413,9 +2277,9 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
     }
   }
   __syncthreads();
-  const uint32_t nd = S.pre[N_BANKS];
-  const Chunk ch = chunk_of(V, nd, CONTAIN_GRANULE);
-  const uint32_t lb = ch.lb;
+  const uint32_t nd = uniform_u32(S.pre[N_BANKS]);
+  const uint32_t P = contain_group(nd, V.G);
+  const Chunk ch = chunk_of(V, nd, P);
   // Entry k of the list, its bank looked for from the chunk's first one.
   uint32_t bank0 = 0;
   while (bank0 + 1u < N_BANKS && ch.begin >= S.pre[bank0 + 1u]) ++bank0;
@@ -2425,80 +2289,192 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
     return D.dpart[S.dst[q] + (k - S.pre[q])];
   };
   const uint32_t w = threadIdx.x >> 6;
+  const uint32_t lg = (uint32_t)__builtin_ctz(64u / P);  // lanes per particle: 1 << lg
+  const uint32_t slot = lane >> lg, sub = lane & ((1u << lg) - 1u);
+  const uint32_t at = w * 64u + slot;  // the particle's place in LDS
+  const uint32_t stride = (TPB / 64) * P;
+  uint16_t* pair = S.pair[w];
   uint3* ent = S.ent[w];
   uint2* hbuf = S.hbuf[w];
   uint32_t nbuf = 0;  // stops held in hbuf (the same in every lane)
   const float rc2 = D.rc2;
   uint32_t tests = 0;
+  constexpr int NC = S8 ? 8 : 27, U = S8 ? 2 : 3;
   // The particle of the next group is fetched during this one (its list
   // entry two groups ahead), off the critical path.
   uint32_t i1 = 0, i2 = 0;
   float4 q1 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  if (ch.begin + threadIdx.x < ch.end) {
-    i1 = entry(ch.begin + threadIdx.x);
+  const uint32_t kf = ch.begin + w * P + slot;
+  if (kf < ch.end) {
+    i1 = entry(kf);
     q1 = D.P[i1];
   }
-  if (ch.begin + TPB + threadIdx.x < ch.end) i2 = entry(ch.begin + TPB + threadIdx.x);
-  for (uint32_t k0 = ch.begin; k0 < ch.end; k0 += TPB) {
-    const uint32_t k = k0 + threadIdx.x;
+  if (kf + stride < ch.end) i2 = entry(kf + stride);
+  for (uint32_t k0 = ch.begin; k0 < ch.end; k0 += stride) {
+    const uint32_t k = k0 + w * P + slot;
     const uint32_t i = i1;
     const float4 q = q1;
-    if (k + TPB < ch.end) {
+    if (k + stride < ch.end) {
       i1 = i2;
       q1 = D.P[i1];
     }
-    if (k + 2u * TPB < ch.end) i2 = entry(k + 2u * TPB);
+    if (k + 2u * stride < ch.end) i2 = entry(k + 2u * stride);
     uint32_t act = 0u, stp = 0u;
-    Stencil st = {0, 0, 0, 0, 0, 0};
     if (k < ch.end) {
-      S.pos[threadIdx.x] = q;
       const P3 p = p3_of(q);
+      const uint32_t g = grain_of(q);
+      Stencil st;
       stencil_axis(D, p.x, 0, st.x0, st.x1);
       stencil_axis(D, p.y, 1, st.y0, st.y1);
       stencil_axis(D, p.z, 2, st.z0, st.z1);
+      if (sub == 0u) {
+        S.pos[at] = q;
+        S.base[at] = make_int3(st.x0, st.y0, st.z0);
+        S.hit[at] = 0u;
+      }
       Near nr{};
       if (S8) nr = near_of(D, p);
-      stencil_owners<S8, PER>(D, epoch, st, nr, grain_of(q), act, stp);
+      const C3 own = cell_of(D, p);
+      const uint32_t b0 = brick_index(D, own.x, own.y, own.z);
+      const uint2 w0 = D.bown[b0];
+      for (int c0 = (int)sub; c0 < NC; c0 += U << lg) {
+        uint32_t ci[U], sm[U];
+        uint2 bw[U], cw[U];
+        bool ok[U], cross[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int c = c0 + (u << lg);
+          const C3 o = stencil_step<S8>(c);
+          int x = st.x0 + o.x, y = st.y0 + o.y, z = st.z0 + o.z;
+          ok[u] = c < NC && x <= st.x1 && y <= st.y1 && z <= st.z1;
+          if (S8) ok[u] = ok[u] && !near_skips(nr, x, y, z);
+          cross[u] = false;
+          if constexpr (PER) {
+            const int xw = wrap_cell(x, D.n[0]), yw = wrap_cell(y, D.n[1]), zw = wrap_cell(z, D.n[2]);
+            cross[u] = xw != x || yw != y || zw != z;
+            x = xw;
+            y = yw;
+            z = zw;
+          }
+          const uint32_t b = brick_index(D, x, y, z);
+          ci[u] = b * (uint32_t)BRICK_CELLS + local_index(x, y, z);
+          bw[u] = w0;
+          cw[u] = make_uint2(NIL, NIL);
+          sm[u] = 0u;
+          if (ok[u]) {
+            cw[u] = D.cown[ci[u]];
+            if (S8) sm[u] = D.smask[ci[u]];
+            if (b != b0) bw[u] = D.bown[b];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int c = c0 + (u << lg);
+          const uint32_t aown = bw[u].x != epoch ? NIL : (bw[u].y == BOWN_CELLS ? cw[u].x : bw[u].y);
+          bool a = ok[u] && aown != NIL && (cross[u] || aown != g);
+          bool t = ok[u] && cw[u].y != NIL && (cross[u] || cw[u].y != g);
+          if (S8) {
+            const C3 o = stencil_step<S8>(c);
+            t = t && !slabs_far(nr, sm[u], st.x0 + o.x, st.y0 + o.y, st.z0 + o.z);
+          }
+          act |= (uint32_t)a << (c & 31);
+          stp |= (uint32_t)t << (c & 31);
+        }
+      }
     }
-    S.hit[threadIdx.x] = 0u;
-    // Rounds: the lanes whose sources fit after those of the lanes before
-    // them (at most 3 per stencil cell, so every round takes one lane at
-    // least).  Entries, positions and hit flags are the wave's own, so the
+    // Rounds: the lanes whose pairs fit after those of the lanes before them.
+    // Pairs, sources, positions and hit flags are the wave's own, so the
     // rounds order LDS within the wave only and the block's waves run
     // independently.
-    uint32_t ne = (uint32_t)__popc(act) + 2u * (uint32_t)__popc(stp);
+    uint32_t np = (uint32_t)__popc(act | stp);
     for (;;) {
       uint32_t tot;
-      const uint32_t e0 = wave_excl_scan(ne, tot);
-      const bool take = ne > 0u && e0 + ne <= (uint32_t)CE_MAX;
-      uint32_t used;
-      (void)wave_excl_scan(take ? ne : 0u, used);
+      const uint32_t e0 = wave_excl_scan(np, tot);
+      const bool take = np > 0u && e0 + np <= PAIR_MAX;
+      uint32_t used = tot;
+      if (tot > PAIR_MAX) (void)wave_excl_scan(take ? np : 0u, used);
       if (take) {
-        stencil_entries<S8, PER>(D, st, act, stp, lane, ent + e0);
-        ne = 0u;
+        uint32_t e = e0;
+        for (uint32_t m = act | stp; m; m &= m - 1u) {
+          const uint32_t c = (uint32_t)__builtin_ctz(m);
+          pair[e++] = (uint16_t)(slot | (c << 6) | (((act >> c) & 1u) << 11) | (((stp >> c) & 1u) << 12));
+        }
+        np = 0u;
       }
       wave_lds_sync();
-      for (uint32_t t = lane; t < used; t += 64u) {
-        const uint3 en = ent[t];
-        const uint32_t L = w * 64u + (en.z & 63u);
-        if (S.hit[L]) continue;
-        const float4 pq = S.pos[L];
-        const uint32_t kind = en.z >> 6;
-        bool h;
-        if (kind == CE_RECENT)
-          h = walk_recent<PER>(D, en.x, p3_of(pq), grain_of(pq), tests);
-        else
-          h = scan_range<PER>(D, kind == CE_ACTIVE ? D.P : D.PS, en.x, en.x + en.y, p3_of(pq),
-                              grain_of(pq), rc2, tests);
-        if (h) S.hit[L] = 1u;
+      uint32_t ne = 0;  // sources held in ent (the same in every lane)
+      for (uint32_t t0 = 0; t0 < used; t0 += 64u) {
+        // Sources of one pair per lane.
+        uint32_t pt = 0, ast = 0, aen = 0, sst = 0, sen = 0, hd = NIL;
+        if (t0 + lane < used) {
+          pt = pair[t0 + lane];
+          const uint32_t L = w * 64u + (pt & 63u);
+          if (!S.hit[L]) {
+            const int3 bs = S.base[L];
+            const C3 o = stencil_step<S8>((int)((pt >> 6) & 31u));
+            int x = bs.x + o.x, y = bs.y + o.y, z = bs.z + o.z;
+            if constexpr (PER) {
+              x = wrap_cell(x, D.n[0]);
+              y = wrap_cell(y, D.n[1]);
+              z = wrap_cell(z, D.n[2]);
+            }
+            const uint32_t b = brick_index(D, x, y, z), loc = local_index(x, y, z);
+            const uint32_t ci = b * (uint32_t)BRICK_CELLS + loc;
+            // The end of a brick's last cell is the brick's.
+            const bool last = loc == (uint32_t)BRICK_CELLS - 1u;
+            uint2 inf = make_uint2(0u, 0u), sb = make_uint2(0u, 0u);
+            if (pt & (1u << 11)) {
+              ast = D.cstart[ci];
+              if (last) inf = D.binfo[b];
+              else aen = D.cstart[ci + 1];
+            }
+            if (pt & (1u << 12)) {
+              sb = D.bsinfo[b];
+              sst = D.sstart[ci];
+              if (!last) sen = D.sstart[ci + 1];
+              hd = D.shead[ci];
+            }
+            if (last) {
+              aen = inf.x + inf.y;
+              sen = sb.x + sb.y;
+            }
+            if (sb.y == 0u) sst = sen = 0u;
+          }
+        }
+        const uint32_t who = pt & 63u;
+        auto put = [&](bool some, uint32_t first, uint32_t len, uint32_t kind) {
+          const unsigned long long m = __ballot(some);
+          if (some) ent[ne + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = make_uint3(first, len, (kind << 6) | who);
+          ne += (uint32_t)__popcll(m);
+        };
+        put(aen > ast, ast, aen - ast, CE_ACTIVE);
+        put(sen > sst, sst, sen - sst, CE_STOPPED);
+        put(hd != NIL, hd, 0u, CE_RECENT);
+        if (ne <= CE_MAX - 192u && t0 + 64u < used) continue;
+        wave_lds_sync();
+        for (uint32_t t = lane; t < ne; t += 64u) {
+          const uint3 en = ent[t];
+          const uint32_t L = w * 64u + (en.z & 63u);
+          if (S.hit[L]) continue;
+          const float4 pq = S.pos[L];
+          const uint32_t kind = en.z >> 6;
+          bool h;
+          if (kind == CE_RECENT)
+            h = walk_recent<PER>(D, en.x, p3_of(pq), grain_of(pq), tests);
+          else
+            h = scan_range<PER>(D, kind == CE_ACTIVE ? D.P : D.PS, en.x, en.x + en.y, p3_of(pq),
+                                grain_of(pq), rc2, tests);
+          if (h) S.hit[L] = 1u;
+        }
+        wave_lds_sync();
+        ne = 0;
       }
-      wave_lds_sync();
-      if (!__any(ne > 0u)) break;
+      if (!__any(np > 0u)) break;
     }
     // Stops are held in LDS and written out a few groups at a time: a wave's
     // memory operations retire in order, so a store here would hold back the
     // first loads of the next group.
-    const bool hit = k < ch.end && S.hit[threadIdx.x] != 0u;
+    const bool hit = sub == 0u && k < ch.end && S.hit[at] != 0u;
     const unsigned long long m = __ballot(hit);
     if (m) {
       const uint32_t c = (uint32_t)__popcll(m);
@@ -2516,6 +2492,7 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
       if (hit) hbuf[nbuf + r] = make_uint2(wb + r, i);
       nbuf += c;
     }
+    wave_lds_sync();
   }
   wave_lds_sync();
   for (uint32_t t = lane; t < nbuf; t += 64u) D.newstop[ch.begin + hbuf[t].x] = hbuf[t].y;
@@ -2525,11 +2502,11 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
   if (lane == 0u && wtests) atomicAdd(&S.tests, wtests);
   __syncthreads();
   if (threadIdx.x == 0) {
-    D.newstop_cnt[lb] = S.n;
+    D.newstop_cnt[ch.lb] = S.n;
     Bank* bk = block_bank(D, V);
     if (S.n) atomicAdd(&bk->n_newstop, S.n);
     if (S.tests) atomicAdd(&bk->pair_tests, (unsigned long long)S.tests);
-    if (lb == 0) atomicAdd(&D.cnt->dirty_tests, (unsigned long long)nd);
+    if (ch.lb == 0) atomicAdd(&D.cnt->dirty_tests, (unsigned long long)nd);
   }
 }
 
@@ -2574,7 +2551,8 @@ __global__ __launch_bounds__(TPB) void k_stoplink(Bind Bd) {
   uint32_t n = 0;
 #pragma unroll
   for (uint32_t q = 0; q < N_BANKS; ++q) n += D.bank[q].n_dpart;
-  const Share rr = regions_of(V, chunk_count(n, CONTAIN_GRANULE, G));
+  const uint32_t P = contain_group(n, G);
+  const Share rr = regions_of(V, chunk_count(n, P, G));
   uint32_t any = 0;
   for (uint32_t rg = rr.begin; rg < rr.end; ++rg) any |= D.newstop_cnt[rg];
   if (!any) return;
@@ -2589,7 +2567,7 @@ __global__ __launch_bounds__(TPB) void k_stoplink(Bind Bd) {
   for (uint32_t w = 0; w < TPB / 64; ++w) base += s_sum[w];
   for (uint32_t rg = rr.begin; rg < rr.end; ++rg) {
     const uint32_t cnt = D.newstop_cnt[rg];
-    const uint32_t beg = chunk_begin(n, CONTAIN_GRANULE, G, rg);
+    const uint32_t beg = chunk_begin(n, P, G, rg);
     for (uint32_t k = threadIdx.x; k < cnt; k += TPB) {
       const uint32_t i = D.newstop[beg + k];
       const uint4 r = with_fl(D.B[i], ST_STOPPED);

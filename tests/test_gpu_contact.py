@@ -95,6 +95,34 @@ def test_single_step_contact_parity(seed, n_grains, per_grain, m, spread, h_fact
     assert len(mism) <= 2
 
 
+@pytest.mark.parametrize("blocks", [1, 8, 100, 2048])
+@pytest.mark.parametrize("seed,n_grains,per_grain,m,spread,h_factor", [
+    (1, 6, 400, 4, 30e-6, 1.0), (3, 40, 3000, 12, 150e-6, 1.0), (5, 40, 3000, 12, 150e-6, 2.0)])
+def test_particles_per_wave_change_no_decision(seed, n_grains, per_grain, m, spread, h_factor, blocks):
+    """Crowded clouds (most stencil cells of a particle hold other grains)
+    with 8 to 64 particles per wave of the containment, by the blocks of its
+    launch, and with more pairs per wave than one round takes: the decisions
+    equal the FP32 checker's."""
+    require_gpu()
+    lam, dt = 5e-6, 1e-4
+    centre, quat, parts = _cloud(seed, n_grains, per_grain, lam, m, 0.3, spread)
+    p = B.make_params((0, 0, 0), (1e-3,) * 3, lam, h_factor * lam, lam, W.KIN_A, W.KIN_B,
+                      branching=0, cap_particles=1 << 18, cap_stopped=1 << 18, cap_grains=64,
+                      cap_claim_bricks=1 << 12)
+    ctx = B.Context(p)
+    ctx.set_schedule({"contain": blocks})
+    ctx.set_thermal_field(W.Field(W.FIELD_UNIFORM, dT=3.0))
+    ctx.load_state(centre, quat, parts, EMPTY_CLAIMS, np.zeros(0, np.int32), 0.0, 0)
+    ctx.step(dt, 1)
+    g, key = gpu_parts(ctx)
+    order = np.argsort(ident(parts["grain"], parts["site"], parts["dir"]))
+    pre_state = parts["state"][order]
+    dec = f32_contain(np.stack([g["x"], g["y"], g["z"]], 1), g["grain"].astype(np.int32),
+                      np.where(pre_state == 0, 1, 2).astype(np.uint8), np.float32(lam * lam))
+    np.testing.assert_array_equal(((pre_state == 0) & (g["state"] == 1)).astype(np.uint8), dec)
+    ctx.close()
+
+
 def test_stopped_particles_block_and_survive_steps():
     """A stopped wall of grain 0 stops grain 1's particles arriving later."""
     require_gpu()
