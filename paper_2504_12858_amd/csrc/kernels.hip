@@ -1240,9 +1240,16 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
 // thread), which takes less than the launch of a kernel that formed it once
 // (4.6 us) while the blocks without a share leave at once (all blocks forming
 // it cost a small state as much as the launch).
+//
+// With SHARED, few spawners (up to one round of eight per wave) are taken
+// eight per wave, with eight lanes each, one per direction: 64 per wave leave a
+// state with a few thousand spawners to a few dozen waves, each working off the
+// directions of 64 spawners one after another.
 struct SpawnView {
   uint32_t n, G, begin, end;
+  bool shared;  // eight lanes per spawner
 };
+template <bool SHARED>
 __device__ __forceinline__ SpawnView spawn_view(const Dev& D, const VGrid& V, uint32_t* s_off) {
   constexpr uint32_t RUN = (uint32_t)STREAM_GRID / TPB;  // regions per thread, G <= STREAM_GRID
   __shared__ uint32_t wsum[TPB / 64];
@@ -1250,7 +1257,9 @@ __device__ __forceinline__ SpawnView spawn_view(const Dev& D, const VGrid& V, ui
   uint32_t n_spawn = 0;
 #pragma unroll
   for (uint32_t q = 0; q < N_BANKS; ++q) n_spawn += D.bank[q].n_spawn;
-  const Chunk it = chunk_of(V, uniform_u32(n_spawn), 64u);
+  n_spawn = uniform_u32(n_spawn);
+  v.shared = SHARED && n_spawn <= V.G * (TPB / 8);
+  const Chunk it = chunk_of(V, n_spawn, v.shared ? TPB / 8u : 64u);
   v.begin = it.begin;
   v.end = it.end;
   v.n = uniform_u32(D.cnt->n_active);
@@ -1286,24 +1295,99 @@ __device__ __forceinline__ uint32_t spawn_pos(const SpawnView& v, const uint32_t
   return chunk_begin(v.n, TPB, v.G, lo) + (i - s_off[lo]);
 }
 
-// At most 80 registers, for six waves per SIMD: more waves in flight hide
-// more of the latency of the branching's loads and atomics.
-template <class Bind>
-__global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
-  Dev D;
-  VGrid V;
-  Bd.bind(D, V);
-  if (dead(D)) return;
-  __shared__ uint32_t s_sp, s_ch;
-  if (threadIdx.x == 0) {
-    s_sp = 0;
-    s_ch = 0;
+// Slot of site (x, y, z) for a reader who knows the slot `slot` of site S's
+// brick (key ks): -1 if the site's block of slot bricks holds no claim.  A slot
+// that was never taken has all its words zero.
+__device__ __forceinline__ int64_t slot_near(const Dev& D, uint64_t ks, uint32_t slot, uint64_t key) {
+  if (slot != NIL && claim_block_key(key) == claim_block_key(ks))
+    return (int64_t)(slot - (uint32_t)claim_fine(ks) + (uint32_t)claim_fine(key));
+  const int64_t blk = block_find<true>(D, claim_block_key(key));
+  return blk < 0 ? -1 : blk * (int64_t)CLAIM_BLOCK_SLOTS + (int64_t)claim_fine(key);
+}
+
+// The branching with eight lanes per spawner, lane dd of a group testing and
+// claiming direction dd (see k_branch for the rules).
+__device__ __forceinline__ void branch_shared(const Dev& D, const SpawnView& it, const uint32_t* s_off,
+                                              uint32_t& nsp, uint32_t& nch) {
+  const uint32_t lane = (uint32_t)lane_id();
+  const int dd = (int)(lane & 7u);
+  for (uint32_t k = it.begin + (threadIdx.x >> 3); k - (lane >> 3) < it.end; k += TPB / 8) {
+    const bool on = k < it.end;
+    uint32_t i = 0, slot = NIL;
+    uint4 r = make_uint4(0u, 0u, 0u, 0u);
+    if (on) {
+      const uint32_t np = spawn_pos(it, s_off, k);
+      i = D.spawn[np];
+      slot = D.spslot[np];
+      r = D.A[i];
+    }
+    const uint32_t g = rec_grain(r);
+    const int d = rec_dir(r), step = (d & 1) ? -1 : 1;
+    const int S[3] = {rec_sx(r) + ((d >> 1) == 0 ? step : 0), rec_sy(r) + ((d >> 1) == 1 ? step : 0),
+                      rec_sz(r) + ((d >> 1) == 2 ? step : 0)};
+    const uint64_t ks = claim_key(g, S[0], S[1], S[2]);
+    const int a = dd >> 1, sg = (dd & 1) ? -1 : 1;
+    const int T[3] = {S[0] + (a == 0 ? sg : 0), S[1] + (a == 1 ? sg : 0), S[2] + (a == 2 ? sg : 0)};
+    bool win = on && dd < 6 && sg * (a == 0 ? S[0] : a == 1 ? S[1] : S[2]) >= 0;
+    if (win) {
+      // The words of the target and of the sites from which a lower direction
+      // would reach it, all requested before the first is used.
+      const int64_t ts = slot_near(D, ks, slot, claim_key(g, T[0], T[1], T[2]));
+      const uint32_t tb = site_bit(T[0], T[1], T[2]);
+      const unsigned long long* tw = D.cbits + (ts < 0 ? 0 : ts) * 24 + (tb >> 6);
+      unsigned long long taken = 0, now[5];
+      if (ts >= 0) taken = load_cached(tw + CB_CLAIMED) | load_cached(tw + CB_REACHED) | load_cached(tw + CB_NOW);
+#pragma unroll
+      for (int d2 = 0; d2 < 5; ++d2) {
+        const int a2 = d2 >> 1, sg2 = (d2 & 1) ? -1 : 1;
+        const int ux = T[0] - (a2 == 0 ? sg2 : 0), uy = T[1] - (a2 == 1 ? sg2 : 0),
+                  uz = T[2] - (a2 == 2 ? sg2 : 0);
+        now[d2] = 0;
+        if (d2 >= dd || sg2 * (a2 == 0 ? ux : a2 == 1 ? uy : uz) < 0) continue;
+        const int64_t us = slot_near(D, ks, slot, claim_key(g, ux, uy, uz));
+        const uint32_t ub = site_bit(ux, uy, uz);
+        if (us >= 0) now[d2] = load_cached(D.cbits + us * 24 + CB_NOW + (ub >> 6)) >> (ub & 63u);
+      }
+      win = !((taken >> (tb & 63u)) & 1ull) && !((now[0] | now[1] | now[2] | now[3] | now[4]) & 1ull);
+    }
+    const uint32_t mask = (uint32_t)(__ballot(win) >> (lane & 56u)) & 63u;
+    // A winner's place, its cell and its claim slot, before the atomics.
+    uint32_t ci = 0;
+    int64_t cs = -1;
+    if (win) {
+      const SiteFrame F = site_frame(load_grow(D.gtab + (size_t)g * GT_STRIDE), S[0], S[1], S[2]);
+      const P3 x = place(D, frame_pos(F, dd, rec_s(r) - D.lambda0)).p;
+      const C3 c = cell_of(D, x);
+      ci = cell_index(D, c.x, c.y, c.z);
+      const uint64_t kt = claim_key(g, T[0], T[1], T[2]);
+      cs = kt == ks && slot != NIL ? (int64_t)slot : claim_get(D, kt);
+    }
+    if (on && dd == 0) {
+      D.A[i] = with_fl(r, ST_RETIRED | FL_SPAWN | (mask << 8));
+      SlotCache wc{ks, slot == NIL ? -1 : (int64_t)slot};
+      cached_or(D, wc, g, S[0], S[1], S[2], M_REACHED);
+      const int lo[3] = {S[0] - (int)((mask >> 1) & 1u), S[1] - (int)((mask >> 3) & 1u), S[2] - (int)((mask >> 5) & 1u)};
+      const int hi[3] = {S[0] + (int)(mask & 1u), S[1] + (int)((mask >> 2) & 1u), S[2] + (int)((mask >> 4) & 1u)};
+      bbox_add_box(D, g, lo, hi);
+      if (D.gcnt) deposit_site(D, D.gtab + (size_t)g * GT_STRIDE, S[0], S[1], S[2]);
+      if (D.melting) atomicAdd(&D.greach[g], 1u);
+      nsp += 1;
+    }
+    if (win) {
+      atomicAdd(&D.ccnt[ci], 1u);
+      atomicAdd(&D.bcnt[ci / (uint32_t)BRICK_CELLS], 1u);
+      if (cs >= 0) {
+        const uint32_t b = site_bit(T[0], T[1], T[2]);
+        atomicOr(D.cbits + (size_t)cs * 24 + CB_CLAIMED + (b >> 6), 1ull << (b & 63u));
+      }
+      nch += 1;
+    }
   }
-  __syncthreads();
-  __shared__ uint32_t s_off[STREAM_GRID + 1];
-  const SpawnView it = spawn_view(D, V, s_off);
-  if (it.begin >= it.end) return;
-  uint32_t nsp = 0, nch = 0;
+}
+
+// The branching with one lane per spawner.
+__device__ __forceinline__ void branch_alone(const Dev& D, const SpawnView& it, const uint32_t* s_off,
+                                             uint32_t& nsp, uint32_t& nch) {
   // The next round's spawner (index, record, claim slot) is loaded during
   // this round, off the chain of dependent loads.  Each record is read and
   // written only in its own spawner's round.
@@ -1345,7 +1429,11 @@ __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
       S[0] = rec_sx(r) + ((d >> 1) == 0 ? dstep : 0);
       S[1] = rec_sy(r) + ((d >> 1) == 1 ? dstep : 0);
       S[2] = rec_sz(r) + ((d >> 1) == 2 ? dstep : 0);
+      // The block of the reached site's slot is known.
       BlockCache sc{~0ull, -1};
+      if (slot != NIL)
+        sc = BlockCache{claim_block_key(claim_key(g, S[0], S[1], S[2])),
+                        (int64_t)(slot / (uint32_t)CLAIM_BLOCK_SLOTS)};
       const SlotWin win = load_win(D, slot, S[0], S[1], S[2]);
       for (int dd = 0; dd < 6; ++dd) {
         const int a = dd >> 1;
@@ -1421,6 +1509,28 @@ __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
       if (rg != NIL && run.off == 0) atomicAdd(&D.greach[rg], (uint32_t)run.len);
     }
   }
+}
+
+// At most 80 registers, for six waves per SIMD: more waves in flight hide
+// more of the latency of the branching's loads and atomics.
+template <class Bind>
+__global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
+  Dev D;
+  VGrid V;
+  Bd.bind(D, V);
+  if (dead(D)) return;
+  __shared__ uint32_t s_sp, s_ch;
+  if (threadIdx.x == 0) {
+    s_sp = 0;
+    s_ch = 0;
+  }
+  __syncthreads();
+  __shared__ uint32_t s_off[STREAM_GRID + 1];
+  const SpawnView it = spawn_view<true>(D, V, s_off);
+  if (it.begin >= it.end) return;
+  uint32_t nsp = 0, nch = 0;
+  if (it.shared) branch_shared(D, it, s_off, nsp, nch);
+  else branch_alone(D, it, s_off, nsp, nch);
   if (nsp) atomicAdd(&s_sp, nsp);
   if (nch) atomicAdd(&s_ch, nch);
   __syncthreads();
@@ -1761,7 +1871,7 @@ __device__ __forceinline__ void scatter_kept(const Dev& D, const VGrid& V) {
 // slots; clears the spawners' marks of the current step.
 __device__ __forceinline__ void scatter_children(const Dev& D, const VGrid& V) {
   __shared__ uint32_t s_off[STREAM_GRID + 1];
-  const SpawnView it = spawn_view(D, V, s_off);
+  const SpawnView it = spawn_view<false>(D, V, s_off);
   for (uint32_t k = it.begin + threadIdx.x; k < it.end; k += TPB) {
     const uint32_t kp = spawn_pos(it, s_off, k);
     const uint4 r = D.A[D.spawn[kp]];
