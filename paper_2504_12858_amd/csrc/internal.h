@@ -188,18 +188,22 @@ struct Dev {
   uint32_t* sstart;    // [cells]
   uint2* bsinfo;       // [bricks] start, count of the sorted stopped particles
   // per-step cell list of the active particles
-  uint32_t* ccnt;      // [cells] counts, back to zero after the scatter
-  uint32_t* cstart;    // [cells]
-  uint32_t* bcnt;      // [bricks] counts, reset by the scan
+  uint32_t* ccnt;      // [cells] counts of a re-sort, back to zero after its scatter
+  uint32_t* cstart;    // [cells] of dirty bricks: start of the cell's particles in Pd
+  uint32_t* dend;      // [bricks] dirty bricks: end of the last cell's
+  uint32_t* bcnt;      // [bricks] counts, back to zero after the scatter (resp. the re-sort's scan)
   uint2* binfo;        // [bricks] start, count of the step's active particles
   uint4* bmeta;        // [bricks] {step at which the brick was last occupied by active
-                       //  particles, their least and greatest owner word that step,
-                       //  owner word of the stopped particles}: what the neighbour
-                       //  tests read, in one 16-byte load
-  uint32_t* dlist;     // [bricks] dirty bricks, per-block regions of the occupied list
-  uint32_t* dlist_cnt; // [STREAM_GRID]
-  uint32_t* dpart;     // [cap_p] particles of dirty bricks (indices into B, P)
-  unsigned long long* dmask;  // [bricks] per listed brick: cells whose particles need the test
+                       //  particles, owner word of the stopped particles, bits set and
+                       //  bits clear in any owner word of the active ones}: what the
+                       //  neighbour tests read, in one 16-byte load
+  float4* Pd;          // [cap_p] positions of the particles that can meet another grain,
+                       //  in cell order at the start of their brick's stretch of the store
+  uint32_t* pidx;      // [cap_p] their indices into B, P (the array of spawn, which the
+                       //  step no longer reads by then)
+  uint32_t* dpart;     // [cap_p] the particles to test (places in Pd)
+  uint2* drange;       // [bricks] per listed dirty brick, per-block regions of the occupied
+                       //  list: first place in Pd, particles
   uint32_t* doff;      // [bricks] per listed brick: offset in the block's stretch of dpart
   uint2* bown;         // [bricks] {step, owner word of the active particles: the grain of a
                        //  single-grain brick, or BOWN_CELLS for a dirty brick}
@@ -253,7 +257,7 @@ struct Dev {
 #define GE_DEV_POINTERS(X)                                                                   \
   X(fgrid) X(gcnt) X(fcmin) X(fcoarse) X(mslots) X(greach) X(gsite) X(gdead) X(gtab) X(gbox) X(A) X(B) X(P) X(spawn) X(spslot) X(spawn_cnt) X(newstop)      \
   X(newstop_cnt) X(S) X(PS) X(S2) X(PS2) X(snext) X(shead) X(sstart) X(bsinfo)      \
-  X(ccnt) X(cstart) X(bcnt) X(binfo) X(bmeta) X(dlist) X(dlist_cnt) X(dpart) X(dmask)       \
+  X(ccnt) X(cstart) X(dend) X(bcnt) X(binfo) X(bmeta) X(Pd) X(pidx) X(dpart) X(drange)       \
   X(doff) X(bown)                                                                             \
   X(cown) X(smask) X(occ) X(scan_tmp) X(ckeys) X(cbits) X(clist) X(dirkeys) X(stab) X(sstate) X(cand) X(sgrain) X(cnt) X(bank) X(tagA)      \
   X(tagB) X(adj_rec) X(adj_nact) X(adj_sfin) X(adj_ck) X(adj_linc)

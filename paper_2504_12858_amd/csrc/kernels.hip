@@ -5,24 +5,24 @@
 //   k_resample   moving point-source field sampled onto the node grid
 //   k_melt_*, k_walkback   melting by walk-back, when enabled (Sec. 2.1.3)
 //   k_advance    undercooling at each active particle, kinetic law Eq. (2),
-//                advance along R e_d, box exit, spawner list, per-cell and
-//                per-brick counts of the particles that stay active; marks
-//                each spawner's reached site as reached this step
+//                advance along R e_d, box exit, spawner list, per-brick
+//                counts of the particles that stay active; marks each
+//                spawner's reached site as reached this step
 //   k_branch     outer directions of each spawner against the grain's claims;
 //                same-step competitors for one target resolved by lowest
 //                direction; counts of the children
 //   k_scan, k_scan_*   scan of brick counts -> brick starts, occupied list
-//   k_cellscan   one wave per occupied brick, one lane per cell: cell starts
-//   k_scatter    records and positions -> cell-sorted arrays (ranks from
-//                wave-aggregated decrements of the cell counts)
-//   k_dirty      bricks whose particles can meet another grain; their cells'
-//                owner words and the list of particles to test
+//   k_scatter    records and positions -> brick-sorted arrays (ranks from
+//                wave-aggregated decrements of the brick counts)
+//   k_dirty      bricks whose particles can meet another grain; their particles
+//                in cell order, their cells' owner words and the list of
+//                particles to test
 //   k_contain    cell-stencil test against other grains' particles
 //   k_stoplink   moves newly stopped particles to the stopped store
 //   k_nuc_test / k_nuc_fire   nucleation of liquid sites past threshold
 //   k_finish     counters for the next step
 // Every few steps the stopped store is re-sorted by cell with the same
-// counting machinery (k_srb_*), so that containment reads it as contiguous
+// brick scan (k_srb_*, k_cellscan), so that containment reads it as contiguous
 // cell ranges; particles stopped since the last re-sort sit in short linked
 // cell lists.
 //
@@ -127,6 +127,17 @@ __device__ __forceinline__ P3 frame_pos(const SiteFrame& f, int d, float s) {
   const int a = d >> 1;
   const float ss = (d & 1) ? -s : s;
   return {fmaf(ss, f.e[a], f.o.x), fmaf(ss, f.e[3 + a], f.o.y), fmaf(ss, f.e[6 + a], f.o.z)};
+}
+
+// The same for a direction that differs between the lanes: the axis is chosen
+// in registers.
+__device__ __forceinline__ P3 frame_pos_any(const SiteFrame& f, int d, float s) {
+  const float e0 = f.e[0], e1 = f.e[1], e2 = f.e[2], e3 = f.e[3], e4 = f.e[4], e5 = f.e[5],
+              e6 = f.e[6], e7 = f.e[7], e8 = f.e[8];
+  const int a = d >> 1;
+  const float ss = (d & 1) ? -s : s;
+  return {fmaf(ss, a == 0 ? e0 : a == 1 ? e1 : e2, f.o.x), fmaf(ss, a == 0 ? e3 : a == 1 ? e4 : e5, f.o.y),
+          fmaf(ss, a == 0 ? e6 : a == 1 ? e7 : e8, f.o.z)};
 }
 
 __device__ __forceinline__ P3 rec_pos(const Dev& D, uint4 r) {
@@ -614,23 +625,57 @@ __device__ __forceinline__ uint32_t wave_append(bool pred, uint32_t* counter) {
   return pred ? base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)) : NIL;
 }
 
-// Groups runs of equal keys in consecutive lanes.
+// The value of the lane before (first for lane 0), in one instruction where a
+// shuffle goes through LDS.
+__device__ __forceinline__ uint32_t lane_before(uint32_t v, uint32_t first) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
+}
+
+// Inclusive sum over the lanes of a wave: within rows of 16 lanes, then the
+// rows before.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+  v += dpp_or_zero<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8
+  v += dpp_or_zero<0x112, 0xF>(v);
+  v += dpp_or_zero<0x114, 0xF>(v);
+  v += dpp_or_zero<0x118, 0xF>(v);
+  v += dpp_or_zero<0x142, 0xA>(v);  // lane 15 of a row to the next row
+  v += dpp_or_zero<0x143, 0xC>(v);  // lane 31 to the upper rows
+  return v;
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_or_zero64(unsigned long long v) {
+  return ((unsigned long long)dpp_or_zero<CTRL, ROWS>((uint32_t)(v >> 32)) << 32) |
+         dpp_or_zero<CTRL, ROWS>((uint32_t)v);
+}
+__device__ __forceinline__ unsigned long long wave_incl_scan64(unsigned long long v) {
+  v += dpp_or_zero64<0x111, 0xF>(v);
+  v += dpp_or_zero64<0x112, 0xF>(v);
+  v += dpp_or_zero64<0x114, 0xF>(v);
+  v += dpp_or_zero64<0x118, 0xF>(v);
+  v += dpp_or_zero64<0x142, 0xA>(v);
+  v += dpp_or_zero64<0x143, 0xC>(v);
+  return v;
+}
+
+// Groups runs of equal keys in consecutive lanes: the run's first lane, the
+// lane's place in the run, and the lanes from this one to the run's end.
 struct Run {
-  int head, off, len;
+  int head, off, rest;
 };
 __device__ __forceinline__ Run wave_run(uint32_t key) {
   const int lane = lane_id();
-  const uint32_t prev = __shfl_up(key, 1u);
-  const bool head = (lane == 0) || (prev != key);
+  const uint32_t prev = lane_before(key, 0u);  // every lane takes part
+  const bool head = lane == 0 || prev != key;
   const unsigned long long H = __ballot(head);
-  const unsigned long long upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
-  const unsigned long long below = H & upto;
-  const unsigned long long above = H & ~upto;
   Run r;
-  r.head = 63 - __clzll((long long)below);
-  const int next = above ? (__ffsll((long long)above) - 1) : 64;
-  r.len = next - r.head;
-  r.off = lane - r.head;
+  r.off = __clzll((long long)(H << (63 - lane)));
+  r.head = lane - r.off;
+  const unsigned long long above = (H >> lane) >> 1;
+  r.rest = above ? __ffsll((long long)above) : 64 - lane;
   return r;
 }
 
@@ -837,12 +882,7 @@ __device__ __forceinline__ bool resort_due(const Dev& D) {
 // Block-wide exclusive scan of one uint32 per thread (TPB threads).
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wsum, uint32_t& total) {
   const int lane = lane_id(), wid = (int)(threadIdx.x >> 6);
-  uint32_t incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t y = __shfl_up(incl, (unsigned)o);
-    if (lane >= o) incl += y;
-  }
+  const uint32_t incl = wave_incl_scan(v);
   if (lane == 63) wsum[wid] = incl;
   __syncthreads();
   uint32_t off = 0, tot = 0;
@@ -861,12 +901,7 @@ __device__ __forceinline__ unsigned long long block_excl_scan64(unsigned long lo
                                                                 unsigned long long* wsum,
                                                                 unsigned long long& total) {
   const int lane = lane_id(), wid = (int)(threadIdx.x >> 6);
-  unsigned long long incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    unsigned long long y = __shfl_up(incl, (unsigned)o);
-    if (lane >= o) incl += y;
-  }
+  const unsigned long long incl = wave_incl_scan64(v);
   if (lane == 63) wsum[wid] = incl;
   __syncthreads();
   unsigned long long off = 0, tot = 0;
@@ -891,14 +926,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 // Exclusive scan over the 64 lanes of a wave.
 __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t& total) {
-  const int lane = lane_id();
-  uint32_t incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t y = __shfl_up(incl, (unsigned)o);
-    if (lane >= o) incl += y;
-  }
-  total = __shfl(incl, 63);
+  const uint32_t incl = wave_incl_scan(v);
+  total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
   return incl - v;
 }
 
@@ -1065,7 +1094,7 @@ __device__ __forceinline__ void stopped_put(const Dev& D, uint32_t j, uint4 r, f
     own = prev;
   }
   // The same for the brick's stopped owner word.
-  uint32_t* bown_s = &D.bmeta[ci / (uint32_t)BRICK_CELLS].w;
+  uint32_t* bown_s = &D.bmeta[ci / (uint32_t)BRICK_CELLS].y;
   own = *bown_s;
   for (;;) {
     const uint32_t nw = owner_merge(own, g);
@@ -1118,7 +1147,7 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
     const bool valid = i < ch.end;
     uint4 r = valid ? D.A[i] : make_uint4(0u, 0u, 0u, 0u);
     const bool act = valid && ((rec_fl(r) & 3u) == ST_ACTIVE);
-    uint32_t ckey = NIL, bkey = NIL;
+    uint32_t bkey = NIL;
     bool spawn = false, exited = false;
     P3 x2 = {0.0f, 0.0f, 0.0f};
     uint32_t tag = NIL;
@@ -1181,18 +1210,15 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
       } else {
         fl = ST_ACTIVE | FL_KEEP;
         const C3 c = cell_of(D, PM == 0 ? x2 : place(D, x2).p);
-        ckey = cell_index(D, c.x, c.y, c.z);
-        bkey = ckey / (uint32_t)BRICK_CELLS;
+        bkey = brick_index(D, c.x, c.y, c.z);
       }
       r = make_rec(s2, g, d, sx, sy, sz, fl);
       D.A[i] = r;
     }
-    // Cell and brick counts of the particles that stay active: one atomic
-    // per run of equal keys in consecutive lanes (the input is cell-sorted).
-    const Run rc = wave_run(ckey);
-    if (ckey != NIL && rc.off == 0) atomicAdd(&D.ccnt[ckey], (uint32_t)rc.len);
+    // Brick counts of the particles that stay active: one atomic per run of
+    // equal keys in consecutive lanes (the input is brick-sorted).
     const Run rb = wave_run(bkey);
-    if (bkey != NIL && rb.off == 0) atomicAdd(&D.bcnt[bkey], (uint32_t)rb.len);
+    if (bkey != NIL && rb.off == 0) atomicAdd(&D.bcnt[bkey], (uint32_t)rb.rest);
     // Spawners go to the block's region of the spawner list.
     const unsigned long long m = __ballot(spawn);
     if (m) {
@@ -1372,14 +1398,14 @@ __device__ __forceinline__ void branch_shared(const Dev& D, const SpawnView& it,
       win = !((taken >> (tb & 63u)) & 1ull) && !((now[0] | now[1] | now[2] | now[3] | now[4]) & 1ull);
     }
     const uint32_t mask = (uint32_t)(__ballot(win) >> (lane & 56u)) & 63u;
-    // A winner's place, its cell and its claim slot, before the atomics.
-    uint32_t ci = 0;
+    // A winner's place, its brick and its claim slot, before the atomics.
+    uint32_t bk = 0;
     int64_t cs = -1;
     if (win) {
       const SiteFrame F = site_frame(load_grow(D.gtab + (size_t)g * GT_STRIDE), S[0], S[1], S[2]);
-      const P3 x = place(D, frame_pos(F, dd, rec_s(r) - D.lambda0)).p;
+      const P3 x = place(D, frame_pos_any(F, dd, rec_s(r) - D.lambda0)).p;
       const C3 c = cell_of(D, x);
-      ci = cell_index(D, c.x, c.y, c.z);
+      bk = brick_index(D, c.x, c.y, c.z);
       const uint64_t kt = claim_key(g, T[0], T[1], T[2]);
       cs = kt == ks && slot != NIL ? (int64_t)slot : claim_get(D, kt);
     }
@@ -1395,8 +1421,7 @@ __device__ __forceinline__ void branch_shared(const Dev& D, const SpawnView& it,
       nsp += 1;
     }
     if (win) {
-      atomicAdd(&D.ccnt[ci], 1u);
-      atomicAdd(&D.bcnt[ci / (uint32_t)BRICK_CELLS], 1u);
+      atomicAdd(&D.bcnt[bk], 1u);
       if (cs >= 0) {
         const uint32_t b = site_bit(T[0], T[1], T[2]);
         atomicOr(D.cbits + (size_t)cs * 24 + CB_CLAIMED + (b >> 6), 1ull << (b & 63u));
@@ -1504,30 +1529,27 @@ __device__ __forceinline__ void branch_alone(const Dev& D, const SpawnView& it, 
       nsp += 1;
     }
     for (int dd = 0; dd < 6; ++dd) {
-      uint32_t ci = NIL;
+      uint32_t bk = NIL;
       if ((mask >> dd) & 1u) {
         const P3 xc = place(D, frame_pos(F, dd, sc2)).p;
         const C3 c = cell_of(D, xc);
-        ci = cell_index(D, c.x, c.y, c.z);
+        bk = brick_index(D, c.x, c.y, c.z);
         const int ta = dd >> 1, ts = (dd & 1) ? -1 : 1;
         const int tx = S[0] + (ta == 0 ? ts : 0), ty = S[1] + (ta == 1 ? ts : 0),
                   tz = S[2] + (ta == 2 ? ts : 0);
         cached_or(D, wc, g, tx, ty, tz, M_CLAIMED);
         nch += 1;
       }
-      const Run rc = wave_run(ci);
-      if (ci != NIL && rc.off == 0) atomicAdd(&D.ccnt[ci], (uint32_t)rc.len);
-      const uint32_t bk = ci == NIL ? NIL : ci / (uint32_t)BRICK_CELLS;
       const Run rb = wave_run(bk);
-      if (bk != NIL && rb.off == 0) atomicAdd(&D.bcnt[bk], (uint32_t)rb.len);
+      if (bk != NIL && rb.off == 0) atomicAdd(&D.bcnt[bk], (uint32_t)rb.rest);
     }
     if (D.gcnt) {
       const Run run = wave_run(dep);
-      if (dep != NIL && run.off == 0) atomicAdd(&D.gcnt[dep], (uint32_t)run.len);
+      if (dep != NIL && run.off == 0) atomicAdd(&D.gcnt[dep], (uint32_t)run.rest);
     }
     if (D.melting) {
       const Run run = wave_run(rg);
-      if (rg != NIL && run.off == 0) atomicAdd(&D.greach[rg], (uint32_t)run.len);
+      if (rg != NIL && run.off == 0) atomicAdd(&D.greach[rg], (uint32_t)run.rest);
     }
   }
 }
@@ -1638,9 +1660,10 @@ __global__ __launch_bounds__(TPB) void k_scan(Bind Bd, int mode) {
   }
   __syncthreads();
   if (total) ex += s_base;
-  // Counts back to zero: the eight at once when they all exist.
+  // The re-sort's counts back to zero, the eight at once when they all exist (a
+  // step's are counted down by the scatter).
   const bool whole = b0 + 8u <= D.n_bricks;
-  if (whole && any) {
+  if (mode == 1 && whole && any) {
     *reinterpret_cast<uint4*>(D.bcnt + b0) = make_uint4(0u, 0u, 0u, 0u);
     *reinterpret_cast<uint4*>(D.bcnt + b0 + 4) = make_uint4(0u, 0u, 0u, 0u);
   }
@@ -1654,14 +1677,13 @@ __global__ __launch_bounds__(TPB) void k_scan(Bind Bd, int mode) {
       if (c[k] > 0u) {
         if (mode == 0) {
           D.binfo[b] = make_uint2(start, c[k]);
-          // Step stamp and an empty owner range; the stopped owner word (.w)
-          // is kept.
-          uint4* m = D.bmeta + b;
-          *reinterpret_cast<uint2*>(m) = make_uint2(epoch, NIL);
-          reinterpret_cast<uint32_t*>(m)[2] = 0u;
+          // Step stamp and no owner bits; the stopped owner word (.y) is kept.
+          uint32_t* m = reinterpret_cast<uint32_t*>(D.bmeta + b);
+          m[0] = epoch;
+          *reinterpret_cast<unsigned long long*>(m + 2) = 0ull;
         }
         D.occ[occ] = (uint32_t)b;
-        if (!whole) D.bcnt[b] = 0u;
+        if (mode == 1 && !whole) D.bcnt[b] = 0u;
       }
       ex += (unsigned long long)c[k] | ((unsigned long long)(c[k] > 0u) << 32);
     }
@@ -1763,9 +1785,10 @@ __global__ __launch_bounds__(TPB) void k_scan_write(Bind Bd, int mode) {
   }
   unsigned long long total;
   unsigned long long ex = block_excl_scan64(v, wsum, total) + D.scan_tmp[V.b];
-  // Counts back to zero: the eight at once when they all exist.
+  // The re-sort's counts back to zero, the eight at once when they all exist (a
+  // step's are counted down by the scatter).
   const bool whole = b0 + 8u <= D.n_bricks;
-  if (whole && any) {
+  if (mode == 1 && whole && any) {
     *reinterpret_cast<uint4*>(D.bcnt + b0) = make_uint4(0u, 0u, 0u, 0u);
     *reinterpret_cast<uint4*>(D.bcnt + b0 + 4) = make_uint4(0u, 0u, 0u, 0u);
   }
@@ -1779,29 +1802,29 @@ __global__ __launch_bounds__(TPB) void k_scan_write(Bind Bd, int mode) {
       if (c[k] > 0u) {
         if (mode == 0) {
           D.binfo[b] = make_uint2(start, c[k]);
-          // Step stamp and an empty owner range; the stopped owner word (.w)
-          // is kept.
-          uint4* m = D.bmeta + b;
-          *reinterpret_cast<uint2*>(m) = make_uint2(epoch, NIL);
-          reinterpret_cast<uint32_t*>(m)[2] = 0u;
+          // Step stamp and no owner bits; the stopped owner word (.y) is kept.
+          uint32_t* m = reinterpret_cast<uint32_t*>(D.bmeta + b);
+          m[0] = epoch;
+          *reinterpret_cast<unsigned long long*>(m + 2) = 0ull;
         }
         D.occ[occ] = (uint32_t)b;
-        if (!whole) D.bcnt[b] = 0u;
+        if (mode == 1 && !whole) D.bcnt[b] = 0u;
       }
       ex += (unsigned long long)c[k] | ((unsigned long long)(c[k] > 0u) << 32);
     }
   }
 }
 
-// One wave per occupied brick, one lane per cell: cell starts from the
-// brick start and an exclusive scan of the 64 cell counts.
+// Cell starts of the re-sorted stopped store, one wave per occupied brick and
+// one lane per cell: the brick start and an exclusive scan of the 64 cell
+// counts.
 template <class Bind>
-__global__ __launch_bounds__(TPB) void k_cellscan(Bind Bd, int mode) {
+__global__ __launch_bounds__(TPB) void k_cellscan(Bind Bd) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
-  if (dead(D) || (mode == 1 && !resort_due(D))) return;
-  const uint32_t nocc = mode == 0 ? D.cnt->n_occ : D.cnt->n_socc;
+  if (dead(D) || !resort_due(D)) return;
+  const uint32_t nocc = D.cnt->n_socc;
   const uint32_t waves = V.G * (TPB / 64);
   const uint32_t lane = (uint32_t)lane_id();
   // Software pipeline: the next brick's start and counts are loaded during
@@ -1811,51 +1834,52 @@ __global__ __launch_bounds__(TPB) void k_cellscan(Bind Bd, int mode) {
   uint32_t b2 = k + waves < nocc ? D.occ[k + waves] : 0u;
   uint32_t start1 = 0u, cnt1 = 0u;
   if (k < nocc) {
-    start1 = mode == 0 ? D.binfo[b1].x : D.bsinfo[b1].x;
+    start1 = D.bsinfo[b1].x;
     cnt1 = D.ccnt[b1 * (uint32_t)BRICK_CELLS + lane];
   }
   for (; k < nocc; k += waves) {
     const uint32_t b = b1, start = start1, cnt = cnt1;
     if (k + waves < nocc) {
       b1 = b2;
-      start1 = mode == 0 ? D.binfo[b1].x : D.bsinfo[b1].x;
+      start1 = D.bsinfo[b1].x;
       cnt1 = D.ccnt[b1 * (uint32_t)BRICK_CELLS + lane];
     }
     if (k + 2u * waves < nocc) b2 = D.occ[k + 2u * waves];
     const uint32_t ci = b * (uint32_t)BRICK_CELLS + lane;
     uint32_t tot;
     const uint32_t ex = wave_excl_scan(cnt, tot);
-    if (mode == 0) D.cstart[ci] = start + ex;
-    else D.sstart[ci] = start + ex;
+    D.sstart[ci] = start + ex;
   }
 }
 
 // ------------------------------------------------------------- scatter ----
-// Grain range of a brick (one update per run of equal (brick, grain) lanes).
-__device__ __forceinline__ void note_grain(const Dev& D, uint32_t b, uint32_t g) {
-  atomicMin(&D.bmeta[b].y, g);
-  atomicMax(&D.bmeta[b].z, g);
+// The owner words of a brick's particles as one word that an atomic OR forms:
+// the bits set in any of them and, above, the bits clear in any of them.  The
+// brick holds one grain if no bit is both.  The word as it was read before
+// (`seen`) only lacks bits, so a read served by a cache can only cost an atomic
+// that changes nothing; most particles add nothing to it.
+__device__ __forceinline__ unsigned long long owner_bits(uint32_t g) {
+  return (unsigned long long)g | ((unsigned long long)~g << 32);
 }
-// The same for children, which arrive in no order: the range is read first
-// (by the caller, clo and chi), an atomic only when it grows (most children
-// join a grain already noted in their brick).  The range only grows, so a read served by the cache (the
-// range as it was at the kernel's start, or wider) can only cost an atomic
-// that changes nothing.
-__device__ __forceinline__ void note_grain_seen(uint32_t* range, uint32_t clo, uint32_t chi,
-                                                uint32_t g) {
-  if (g < clo) atomicMin(range, g);
-  if (g > chi) atomicMax(range + 1, g);
+__device__ __forceinline__ unsigned long long* brick_owners(const Dev& D, uint32_t b) {
+  return reinterpret_cast<unsigned long long*>(&D.bmeta[b].z);
+}
+__device__ __forceinline__ void note_grain(unsigned long long* owners, unsigned long long seen, uint32_t g) {
+  const unsigned long long w = owner_bits(g);
+  if ((seen & w) != w) atomicOr(owners, w);
 }
 
 __device__ __forceinline__ void scatter_kept(const Dev& D, const VGrid& V) {
   const uint32_t n = D.cnt->n_active;
   const Chunk ch = chunk_of(V, n, TPB);
+  uint4 next = make_uint4(0u, 0u, 0u, 0u);
+  if (ch.begin + threadIdx.x < ch.end) next = D.A[ch.begin + threadIdx.x];
   for (uint32_t base = ch.begin; base < ch.end; base += TPB) {
     const uint32_t i = base + threadIdx.x;
     const bool valid = i < ch.end;
-    const uint4 r = valid ? D.A[i] : make_uint4(0u, 0u, 0u, 0u);
+    const uint4 r = next;
     const uint32_t fl = valid ? rec_fl(r) : 0u;
-    uint32_t ckey = NIL;
+    uint32_t bkey = NIL;
     uint32_t g = NIL;
     P3 p = {0.0f, 0.0f, 0.0f};
     if (fl & FL_KEEP) {
@@ -1863,33 +1887,41 @@ __device__ __forceinline__ void scatter_kept(const Dev& D, const VGrid& V) {
       g = owner_id(rec_grain(r), pl.code);
       p = pl.p;
       const C3 c = cell_of(D, p);
-      ckey = cell_index(D, c.x, c.y, c.z);
+      bkey = brick_index(D, c.x, c.y, c.z);
     }
-    // Ranks within the cell: one decrement per run of equal cells; the cell
-    // counts return to zero once every particle has been placed.
-    const Run run = wave_run(ckey);
+    // Ranks within the brick: one decrement per run of equal bricks; the
+    // counts return to zero once every particle has been placed.  The brick's
+    // start is read before the rank atomic: a wave's memory operations retire
+    // in order, so a load issued after it would wait for its round trip.  So is
+    // the next particle's record.
+    uint32_t start = 0;
+    unsigned long long seen = 0;
+    if (bkey != NIL) {
+      start = D.binfo[bkey].x;
+      seen = *brick_owners(D, bkey);
+    }
+    if (i + TPB < ch.end) next = D.A[i + TPB];
+    const Run run = wave_run(bkey);
     uint32_t rbase = 0;
-    if (ckey != NIL && run.off == 0) rbase = atomicSub(&D.ccnt[ckey], (uint32_t)run.len);
+    if (bkey != NIL && run.off == 0) rbase = atomicSub(&D.bcnt[bkey], (uint32_t)run.rest);
     rbase = __shfl(rbase, run.head);
-    // Grain range per brick: one update per run of equal (brick, grain).
-    const uint32_t bkey = ckey == NIL ? NIL : ckey / (uint32_t)BRICK_CELLS;
-    const uint32_t pb = __shfl_up(bkey, 1u), pg = __shfl_up(g, 1u);
-    const bool head = lane_id() == 0 || pb != bkey || pg != g;
-    if (ckey != NIL) {
-      const uint32_t rank = rbase - (uint32_t)run.len + (uint32_t)run.off;
-      const uint32_t dst = D.cstart[ckey] + rank;
+    // Owner bits of the brick: at most one update per run of equal (brick, grain).
+    const uint32_t pg = lane_before(g, NIL);
+    const bool head = run.off == 0 || pg != g;
+    if (bkey != NIL) {
+      const uint32_t dst = start + rbase - (uint32_t)run.rest;
       if (dst < D.cap_p) {
         D.B[dst] = with_fl(r, ST_ACTIVE);
         D.P[dst] = pos4(p, g);
         if (D.tagA) D.tagB[dst] = D.tagA[i];
       }
-      if (head) note_grain(D, bkey, g);
+      if (head) note_grain(brick_owners(D, bkey), seen, g);
     }
   }
 }
 
-// Children of the spawners (from the per-block spawner lists) to their cell
-// slots; clears the spawners' marks of the current step.
+// Children of the spawners (from the per-block spawner lists) to their bricks;
+// clears the spawners' marks of the current step.
 __device__ __forceinline__ void scatter_children(const Dev& D, const VGrid& V) {
   __shared__ uint32_t s_off[STREAM_GRID + 1];
   const SpawnView it = spawn_view<false>(D, V, s_off);
@@ -1899,8 +1931,9 @@ __device__ __forceinline__ void scatter_children(const Dev& D, const VGrid& V) {
     const uint32_t fl = rec_fl(r);
     const uint32_t gs = rec_grain(r);
     const int d = rec_dir(r);
-    int S[3] = {rec_sx(r), rec_sy(r), rec_sz(r)};
-    S[d >> 1] += (d & 1) ? -1 : 1;
+    const int ra = d >> 1, re = (d & 1) ? -1 : 1;
+    const int S[3] = {rec_sx(r) + (ra == 0 ? re : 0), rec_sy(r) + (ra == 1 ? re : 0),
+                      rec_sz(r) + (ra == 2 ? re : 0)};
     const uint32_t slot = D.spslot[kp];
     const uint32_t mask = (fl >> 8) & 63u;
     // The grain row for the children's positions, loaded before the atomics.
@@ -1912,31 +1945,31 @@ __device__ __forceinline__ void scatter_children(const Dev& D, const VGrid& V) {
     }
     if (!mask) continue;
     const float sc = rec_s(r) - D.lambda0;
-    for (int dd = 0; dd < 6; ++dd) {
-      if (!(mask & (1u << dd))) continue;
-      const float4 xc = placed4(D, frame_pos(F, dd, sc), gs);
+    // One child per lane and round, whichever its direction: a wave takes as
+    // many rounds as the spawner with the most children has.
+    for (uint32_t m = mask; m; m &= m - 1u) {
+      const int dd = __builtin_ctz(m);
+      const float4 xc = placed4(D, frame_pos_any(F, dd, sc), gs);
       const C3 c = cell_of(D, p3_of(xc));
-      const uint32_t ci = cell_index(D, c.x, c.y, c.z);
-      // The cell start and the brick's grain range are read before the rank
-      // atomic: a wave's memory operations retire in order, so a load issued
-      // after it would wait for its round trip.
-      uint32_t* range = &D.bmeta[ci / (uint32_t)BRICK_CELLS].y;
-      const uint32_t cs = D.cstart[ci], rlo = range[0], rhi = range[1];
-      const uint32_t rank = atomicSub(&D.ccnt[ci], 1u) - 1u;
-      const uint32_t dst = cs + rank;
+      const uint32_t b = brick_index(D, c.x, c.y, c.z);
+      // The brick's start and its owner bits before the rank atomic, as above.
+      unsigned long long* owners = brick_owners(D, b);
+      const uint32_t start = D.binfo[b].x;
+      const unsigned long long seen = *owners;
+      const uint32_t dst = start + atomicSub(&D.bcnt[b], 1u) - 1u;
       if (dst < D.cap_p) {
         D.B[dst] = make_rec(sc, gs, dd, S[0], S[1], S[2], ST_ACTIVE);
         D.P[dst] = xc;
         if (D.tagA) D.tagB[dst] = NIL;
       }
-      note_grain_seen(range, rlo, rhi, grain_of(xc));
+      note_grain(owners, seen, grain_of(xc));
     }
   }
 }
 
 // Both scatters in one launch: they write different places and share no other
 // state.  On a large state the children's blocks follow those of the kept
-// particles and fill the chip as these end, finding the cells' words in the
+// particles and fill the chip as these end, finding the bricks' words in the
 // caches (14M active particles: 421 us, as two launches 451; with the children
 // first 495, alternating 518).  On a small one the blocks of the two alternate
 // (285k active particles: 15 us, one after the other 20, as two launches 24).
@@ -1956,10 +1989,22 @@ __global__ __launch_bounds__(TPB, 8) void k_scatter(Pair<Bind> Bd, uint32_t n_ke
 // A particle's contact stencil lies inside the 3x3x3 cells around its cell,
 // so it can meet another grain only if those cells reach a flagged brick:
 // every cell of a brick flagged itself, and otherwise the cells on the faces,
-// edges and corners that border a flagged neighbour.  Dirty bricks get the
-// owner words of their cells (read by the containment of their neighbours);
-// the particles of the cells that need the test go to one contiguous stretch
-// of the global list `dpart` per block.
+// edges and corners that border a flagged neighbour.  The particles of these
+// cells are what the containment tests and what it meets (a cell whose stencil
+// reaches another grain is in the other's stencil as well): they are copied in
+// cell order (Pd, with their place in the store) to the start of the brick's
+// own stretch, and cstart and dend hold the cells' ranges there.  Dirty bricks
+// also get the owner words of their cells; the list `dpart` of the particles
+// to test is one contiguous stretch per block.
+//
+// The store itself is sorted by brick alone: about half of the occupied bricks
+// of a grown structure are dirty, and sorting 27 particles in LDS costs less
+// than a count and a rank atomic per cell and a scan of every brick's cells.
+// Bound by instruction issue on a large state (hence the scalar arithmetic of
+// the brick's coordinates), by latency on a small one.  Advance, branching,
+// cell scan, scatter and this kernel together, sorted by cell and by brick: 1232
+// and 1106 us at 14M active particles (this kernel 231 and 234), 88 and 68 us at
+// 285k, 45 and 37 at 4k in a periodic box.
 template <class Bind>
 __global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
   Dev D;
@@ -1968,6 +2013,9 @@ __global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
   const uint32_t epoch = step_epoch(D);
   if (dead(D)) return;
   __shared__ uint32_t s_n, s_np, s_base;
+  // Per cell of the wave's brick: particles (then places), least and greatest
+  // owner word.
+  __shared__ uint32_t s_cell[TPB / 64][BRICK_CELLS], s_lo[TPB / 64][BRICK_CELLS], s_hi[TPB / 64][BRICK_CELLS];
   if (threadIdx.x == 0) {
     s_n = 0;
     s_np = 0;
@@ -1991,29 +2039,32 @@ __global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
     if (rx && ry && rz) reach |= 1u << t;
   }
   // Summary of one neighbour brick per lane (lanes < 27; lane 13 is the
-  // brick itself): {step stamp, owner range of the step's active particles,
-  // stopped owner word}, one 16-byte load.
+  // brick itself): {step stamp, stopped owner word, owner bits of the step's
+  // active particles}, one 16-byte load.  The brick's index and coordinates
+  // are the wave's, so their arithmetic is left to the scalar unit.
+  const int ox = lane % 3 - 1, oy = (lane / 3) % 3 - 1, oz = lane / 9 - 1;
+  const uint32_t ob = (uint32_t)((oz * nby + oy) * nbx + ox);
+  auto coords = [&](uint32_t b) {
+    const uint32_t row = b / (uint32_t)nbx;
+    return C3{(int)(b % (uint32_t)nbx), (int)(row % (uint32_t)nby), (int)(row / (uint32_t)nby)};
+  };
   auto fetch = [&](uint32_t b, uint4& n) {
-    n = make_uint4(0u, 0u, 0u, NIL);
-    if (lane < 27) {
-      const int bx = (int)(b % (uint32_t)nbx) + lane % 3 - 1;
-      const int by = (int)((b / (uint32_t)nbx) % (uint32_t)nby) + (lane / 3) % 3 - 1;
-      const int bz = (int)(b / ((uint32_t)nbx * (uint32_t)nby)) + lane / 9 - 1;
-      if (bx >= 0 && by >= 0 && bz >= 0 && bx < nbx && by < nby && bz < nbz) {
-        const uint32_t nb = ((uint32_t)bz * (uint32_t)nby + (uint32_t)by) * (uint32_t)nbx + (uint32_t)bx;
-        n = D.bmeta[nb];
-      }
-    }
+    n = make_uint4(0u, NIL, 0u, 0u);
+    const C3 c = coords(b);
+    if (lane < 27 && (uint32_t)(c.x + ox) < (uint32_t)nbx && (uint32_t)(c.y + oy) < (uint32_t)nby &&
+        (uint32_t)(c.z + oz) < (uint32_t)nbz)
+      n = D.bmeta[b + ob];
   };
   // Software pipeline: the words of the next brick of the wave are loaded
   // during this one, and its index one brick earlier.
   const uint32_t W = TPB / 64;
-  const uint32_t k0 = ch.begin + (threadIdx.x >> 6);
+  const uint32_t k0 = uniform_u32(ch.begin + (threadIdx.x >> 6));
   uint32_t b1 = k0 < ch.end ? D.occ[k0] : 0u;
   uint32_t b2 = k0 + W < ch.end ? D.occ[k0 + W] : 0u;
   uint2 own1 = make_uint2(0u, 0u);
-  uint4 n1 = make_uint4(0u, 0u, 0u, NIL);
+  uint4 n1 = make_uint4(0u, NIL, 0u, 0u);
   if (k0 < ch.end) {
+    b1 = uniform_u32(b1);
     own1 = D.binfo[b1];
     fetch(b1, n1);
   }
@@ -2022,83 +2073,132 @@ __global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
   // at the end of an iteration would be waited for before the next one.
   uint32_t pb = NIL;         // brick with stores pending (the same in every lane)
   uint32_t pbown = 0u;       // its owner word
-  bool pcells = false;       // its cell owner words are pending (a dirty brick)
+  bool pcells = false;       // its cell words are pending (a dirty brick)
   uint32_t powner = 0u;      // this lane's cell owner word
+  uint32_t pstart = 0u, pend = 0u;  // this lane's cell start, the brick's end
   bool plist = false;        // its list entry is pending (lane 0)
-  uint32_t pslot = 0u, poff = 0u;
-  unsigned long long pmask = 0ull;
+  uint32_t pslot = 0u, poff = 0u, pfirst = 0u;
+  uint32_t pput = NIL, pidx = 0u;   // this lane's copied particle: its place
+  float4 pq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   auto flush = [&]() {
     if (pb == NIL) return;
     if (lane == 0) D.bown[pb] = make_uint2(epoch, pbown);
-    if (pcells) D.cown[pb * (uint32_t)BRICK_CELLS + (uint32_t)lane].x = powner;
+    if (pcells) {
+      const uint32_t ci = pb * (uint32_t)BRICK_CELLS + (uint32_t)lane;
+      D.cown[ci].x = powner;
+      D.cstart[ci] = pstart;
+      if (lane == 0) D.dend[pb] = pend;
+      if (pput != NIL) {
+        D.Pd[pput] = pq;
+        D.pidx[pput] = pidx;
+      }
+    }
     if (plist) {
-      D.dlist[ch.begin + pslot] = pb;
-      D.dmask[ch.begin + pslot] = pmask;
+      D.drange[ch.begin + pslot] = make_uint2(pfirst, pend - pfirst);
       D.doff[ch.begin + pslot] = poff;
     }
     pb = NIL;
   };
+  uint32_t* cells = s_cell[threadIdx.x >> 6];
+  uint32_t* clo = s_lo[threadIdx.x >> 6];
+  uint32_t* chi = s_hi[threadIdx.x >> 6];
+  auto cell_in_brick = [&](float4 q) {
+    const C3 c = cell_of(D, p3_of(q));
+    return local_index(c.x, c.y, c.z);
+  };
   for (uint32_t k = k0; k < ch.end; k += W) {
     const uint32_t b = b1;
-    const uint2 own = own1;
+    const uint32_t st0 = uniform_u32(own1.x), n = uniform_u32(own1.y);
     const uint4 nn = n1;
     if (k + W < ch.end) {
-      b1 = b2;
+      b1 = uniform_u32(b2);
       own1 = D.binfo[b1];
       fetch(b1, n1);
     }
     if (k + 2u * W < ch.end) b2 = D.occ[k + 2u * W];
-    // The brick's own owner range (lane 13).
-    const uint32_t g = (uint32_t)__shfl((int)nn.y, 13);
-    const uint32_t gmax = (uint32_t)__shfl((int)nn.z, 13);
-    flush();
-    const bool foreign = (nn.x == epoch && !(nn.y == g && nn.z == g)) ||
-                         (nn.w != NIL && nn.w != g);
+    // The brick's own owner bits (lane 13).
+    const uint32_t g = (uint32_t)__builtin_amdgcn_readlane((int)nn.z, 13);
+    const bool several = (g & (uint32_t)__builtin_amdgcn_readlane((int)nn.w, 13)) != 0u;
+    const bool foreign = (nn.x == epoch && !(nn.z == g && nn.w == ~g)) ||
+                         (nn.y != NIL && nn.y != g);
     // Flagged bricks; the brick itself (bit 13) when it holds several grains
     // or lies on a periodic face (its cells' stencils wrap, and owner words
     // do not tell the periods apart).
     bool face = false;
     if (D.periodic) {
-      const int cx = (int)(b % (uint32_t)nbx), cy = (int)((b / (uint32_t)nbx) % (uint32_t)nby),
-                cz = (int)(b / ((uint32_t)nbx * (uint32_t)nby));
-      face = ((D.periodic & 1) && (cx == 0 || cx == nbx - 1)) ||
-             ((D.periodic & 2) && (cy == 0 || cy == nby - 1)) ||
-             ((D.periodic & 4) && (cz == 0 || cz == nbz - 1));
+      const C3 c = coords(b);
+      face = ((D.periodic & 1) && (c.x == 0 || c.x == nbx - 1)) ||
+             ((D.periodic & 2) && (c.y == 0 || c.y == nby - 1)) ||
+             ((D.periodic & 4) && (c.z == 0 || c.z == nbz - 1));
     }
     const uint32_t flags =
-        (uint32_t)__ballot(foreign) | (g != gmax || face ? (1u << 13) : 0u);
+        (uint32_t)__ballot(foreign) | (several || face ? (1u << 13) : 0u);
     const bool dirty = flags != 0u;
+    // The first 64 particles of a dirty brick are requested before the stores
+    // of the last brick.
+    float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (dirty && (uint32_t)lane < n) q = D.P[st0 + (uint32_t)lane];
+    flush();
     pb = b;
     pbown = dirty ? BOWN_CELLS : g;
-    pcells = false;
+    pcells = dirty;
     plist = false;
+    pput = NIL;
     if (!dirty) continue;
-    // Owner grain of the active particles of each of the brick's 64 cells
-    // (one lane per cell): the brick's one grain, unless it holds several.
-    const uint32_t ci = b * (uint32_t)BRICK_CELLS + (uint32_t)lane;
-    const uint32_t st = D.cstart[ci];
-    const uint32_t en = lane + 1 < BRICK_CELLS ? D.cstart[ci + 1] : own.x + own.y;
-    // Four independent loads per round (the tail round repeats the last
-    // particle, which leaves the owner unchanged).
-    uint32_t owner = g == gmax && en > st ? g : NIL;
-    for (uint32_t j = st; g != gmax && j < en; j += 4u) {
-      const uint32_t l = en - 1u;
-      const uint32_t g0 = grain_of(D.P[j]), g1 = grain_of(D.P[min(j + 1u, l)]);
-      const uint32_t g2 = grain_of(D.P[min(j + 2u, l)]), g3 = grain_of(D.P[min(j + 3u, l)]);
-      owner = owner_merge(owner_merge(owner_merge(owner_merge(owner, g0), g1), g2), g3);
+    cells[lane] = 0u;
+    if (several) {
+      clo[lane] = NIL;
+      chi[lane] = 0u;
     }
-    pcells = true;
-    powner = owner;
+    wave_lds_sync();
+    auto note = [&](float4 x, uint32_t& c) {
+      c = cell_in_brick(x);
+      if (several) {
+        atomicMin(&clo[c], grain_of(x));
+        atomicMax(&chi[c], grain_of(x));
+      }
+      return atomicAdd(&cells[c], 1u);
+    };
+    uint32_t loc = 0, rank = 0;
+    if ((uint32_t)lane < n) rank = note(q, loc);
+    for (uint32_t j = 64u + (uint32_t)lane; j < n; j += 64u) {
+      uint32_t c;
+      (void)note(D.P[st0 + j], c);
+    }
+    wave_lds_sync();
+    const uint32_t held = cells[lane];
+    // Owner grain of the active particles of each of the brick's 64 cells.
+    powner = held == 0u ? NIL : !several ? g : clo[lane] == chi[lane] ? clo[lane] : MIXED;
     const bool need = (flags & (1u << 13)) != 0u || (flags & reach) != 0u;
-    const uint32_t cnt = need ? en - st : 0u;
-    const unsigned long long mask = __ballot(cnt > 0u);
-    if (!mask) continue;
+    const unsigned long long needs = __ballot(need);
     uint32_t tot;
-    (void)wave_excl_scan(cnt, tot);
+    const uint32_t ex = wave_excl_scan(need ? held : 0u, tot);
+    pstart = st0 + ex;
+    pfirst = st0;
+    pend = st0 + tot;
+    if (!tot) continue;
+    cells[lane] = pstart;
+    wave_lds_sync();
+    if (n <= 64u) {
+      if ((uint32_t)lane < n && ((needs >> loc) & 1ull)) {
+        pput = cells[loc] + rank;
+        pidx = st0 + (uint32_t)lane;
+        pq = q;
+      }
+    } else {
+      for (uint32_t j = (uint32_t)lane; j < n; j += 64u) {
+        const float4 x = j < 64u ? q : D.P[st0 + j];
+        const uint32_t c = cell_in_brick(x);
+        if (!((needs >> c) & 1ull)) continue;
+        const uint32_t to = atomicAdd(&cells[c], 1u);
+        D.Pd[to] = x;
+        D.pidx[to] = st0 + j;
+      }
+    }
+    wave_lds_sync();
     if (lane == 0) {
       plist = true;
       pslot = atomicAdd(&s_n, 1u);
-      pmask = mask;
       poff = atomicAdd(&s_np, tot);
     }
   }
@@ -2116,32 +2216,20 @@ __global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
   const uint32_t nd = s_n, base = s_base;
   // The next dirty brick's list entry is loaded during this one.
   uint32_t k = threadIdx.x >> 6;
-  uint32_t nb = 0, noff = 0;
-  unsigned long long nmask = 0;
+  uint2 nr = make_uint2(0u, 0u);
+  uint32_t noff = 0;
   if (k < nd) {
-    nb = D.dlist[ch.begin + k];
-    nmask = D.dmask[ch.begin + k];
+    nr = D.drange[ch.begin + k];
     noff = D.doff[ch.begin + k];
   }
   for (; k < nd; k += TPB / 64) {
-    const uint32_t b = nb, off = noff;
-    const unsigned long long mask = nmask;
+    const uint2 rg = nr;
+    const uint32_t off = noff;
     if (k + TPB / 64 < nd) {
-      nb = D.dlist[ch.begin + k + TPB / 64];
-      nmask = D.dmask[ch.begin + k + TPB / 64];
+      nr = D.drange[ch.begin + k + TPB / 64];
       noff = D.doff[ch.begin + k + TPB / 64];
     }
-    const uint32_t ci = b * (uint32_t)BRICK_CELLS + (uint32_t)lane;
-    uint32_t st = 0, cnt = 0;
-    if ((mask >> lane) & 1ull) {
-      const uint2 inf = D.binfo[b];
-      st = D.cstart[ci];
-      const uint32_t en = lane + 1 < BRICK_CELLS ? D.cstart[ci + 1] : inf.x + inf.y;
-      cnt = en - st;
-    }
-    uint32_t tot;
-    const uint32_t ex = wave_excl_scan(cnt, tot);
-    for (uint32_t j = 0; j < cnt; ++j) D.dpart[base + off + ex + j] = st + j;
+    for (uint32_t j = (uint32_t)lane; j < rg.y; j += 64u) D.dpart[base + off + j] = rg.x + j;
   }
 }
 
@@ -2183,10 +2271,20 @@ __device__ __forceinline__ bool meets_any(const Dev& D, float4 q, P3 p, uint32_t
   return D.periodic ? meets_periodic(D, q, p, g, rc2) : meets<false>(D, q, p, g, rc2);
 }
 
-// True if a particle of a grain other than g (g = NIL: of any grain) lies
-// within rc of p, among this step's active particles and the stopped ones.
-// `tests` counts the candidate particles examined (diagnostics).
-__device__ bool foreign_within(const Dev& D, uint32_t epoch, P3 p, uint32_t g, uint32_t& tests) {
+// Cell coordinate c of an axis with n cells lies in the stencil [lo, hi], whose
+// ends run past the faces of a periodic axis.
+__device__ __forceinline__ bool in_stencil(int c, int lo, int hi, int n) {
+  int d = c - lo;
+  if (d >= n) d -= n;
+  if (d < 0) d += n;
+  return d <= hi - lo;
+}
+
+// True if a particle of any grain lies within rc of p, among this step's active
+// particles and the stopped ones.  The active ones are sorted by brick: each
+// brick of the stencil is read whole (some bricks are met twice where a
+// periodic axis is shorter than two bricks).
+__device__ bool any_within(const Dev& D, uint32_t epoch, P3 p) {
   int x0, x1, y0, y1, z0, z1;
   stencil_axis(D, p.x, 0, x0, x1);
   stencil_axis(D, p.y, 1, y0, y1);
@@ -2195,43 +2293,39 @@ __device__ bool foreign_within(const Dev& D, uint32_t epoch, P3 p, uint32_t g, u
     for (int ys = y0; ys <= y1; ++ys)
       for (int xs = x0; xs <= x1; ++xs) {
         const int x = wrap_cell(xs, D.n[0]), y = wrap_cell(ys, D.n[1]), z = wrap_cell(zs, D.n[2]);
-        const bool cross = x != xs || y != ys || z != zs;
         const uint32_t b = brick_index(D, x, y, z);
-        const uint32_t loc = local_index(x, y, z);
-        const uint32_t ci = b * (uint32_t)BRICK_CELLS + loc;
-        // Brick summaries: a source whose brick holds grain g only (or
-        // nothing) cannot hold a foreign particle.
+        const uint32_t ci = b * (uint32_t)BRICK_CELLS + local_index(x, y, z);
         const uint4 meta = D.bmeta[b];
-        if (meta.x == epoch) {
-          if (cross || !(meta.y == g && meta.z == g)) {
-            const uint2 inf = D.binfo[b];
-            const uint32_t st = D.cstart[ci];
-            const uint32_t en =
-                (loc + 1u < (uint32_t)BRICK_CELLS) ? D.cstart[ci + 1] : inf.x + inf.y;
-            for (uint32_t j = st; j < en; ++j) {
-              const float4 q = D.P[j];
-              ++tests;
-              if (meets_any(D, q, p, g, D.rc2)) return true;
+        const bool enters = (xs == x0 || (x & 3) == 0) && (ys == y0 || (y & 3) == 0) &&
+                            (zs == z0 || (z & 3) == 0);
+        if (enters && meta.x == epoch) {
+          const uint2 inf = D.binfo[b];
+          for (uint32_t j = 0; j < inf.y; j += 4u) {
+            const uint32_t l = inf.y - 1u;
+            const float4 q[4] = {D.P[inf.x + j], D.P[inf.x + min(j + 1u, l)],
+                                 D.P[inf.x + min(j + 2u, l)], D.P[inf.x + min(j + 3u, l)]};
+            bool m = false;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const C3 c = cell_of(D, p3_of(q[u]));
+              m |= in_stencil(c.x, x0, x1, D.n[0]) && in_stencil(c.y, y0, y1, D.n[1]) &&
+                   in_stencil(c.z, z0, z1, D.n[2]) && meets_any(D, q[u], p, NIL, D.rc2);
             }
+            if (m) return true;
           }
         }
-        if (meta.w != NIL && (cross || meta.w != g)) {
+        if (meta.y != NIL) {
           const uint2 bs = D.bsinfo[b];
           if (bs.y > 0u) {
+            const uint32_t loc = ci & (uint32_t)(BRICK_CELLS - 1);
             const uint32_t st = D.sstart[ci];
             const uint32_t en =
                 (loc + 1u < (uint32_t)BRICK_CELLS) ? D.sstart[ci + 1] : bs.x + bs.y;
-            for (uint32_t j = st; j < en; ++j) {
-              const float4 q = D.PS[j];
-              ++tests;
-              if (meets_any(D, q, p, g, D.rc2)) return true;
-            }
+            for (uint32_t j = st; j < en; ++j)
+              if (meets_any(D, D.PS[j], p, NIL, D.rc2)) return true;
           }
-          for (uint32_t j = D.shead[ci]; j != NIL; j = D.snext[j]) {
-            const float4 q = D.PS[j];
-            ++tests;
-            if (meets_any(D, q, p, g, D.rc2)) return true;
-          }
+          for (uint32_t j = D.shead[ci]; j != NIL; j = D.snext[j])
+            if (meets_any(D, D.PS[j], p, NIL, D.rc2)) return true;
         }
       }
   return false;
@@ -2272,7 +2366,7 @@ __device__ __forceinline__ bool walk_recent(const Dev& D, uint32_t j, P3 p, uint
 // and a wave waits for its slowest lane.  The containment therefore lists, for
 // the wave's particles, every stencil cell that holds another grain (a pair of
 // particle and cell), then every candidate source of these cells (a range of
-// the cell-sorted active store, a range of the cell-sorted stopped store, the
+// the cell-ordered active particles Pd, a range of the cell-sorted stopped store, the
 // head of a recent-stop list; empty ones are left out), both in shared memory,
 // and the lanes take pairs and sources in turn, whichever particle they belong
 // to.  Pair: {particle, cell of the stencil << 6, active << 11, stopped << 12}.
@@ -2363,7 +2457,7 @@ struct ContainShared {
   uint32_t hit[TPB];
   uint16_t pair[TPB / 64][PAIR_MAX];
   uint3 ent[TPB / 64][CE_MAX];
-  uint2 hbuf[TPB / 64][HIT_BUF];  // {position in the block's stop list, particle}
+  uint2 hbuf[TPB / 64][HIT_BUF];  // {position in the block's stop list, place in Pd}
 };
 
 // Containment (particles of two grains that meet stop, Sec. 2.1.2; the
@@ -2438,7 +2532,7 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
   const uint32_t kf = ch.begin + w * P + slot;
   if (kf < ch.end) {
     i1 = entry(kf);
-    q1 = D.P[i1];
+    q1 = D.Pd[i1];
   }
   if (kf + stride < ch.end) i2 = entry(kf + stride);
   for (uint32_t k0 = ch.begin; k0 < ch.end; k0 += stride) {
@@ -2447,7 +2541,7 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
     const float4 q = q1;
     if (k + stride < ch.end) {
       i1 = i2;
-      q1 = D.P[i1];
+      q1 = D.Pd[i1];
     }
     if (k + 2u * stride < ch.end) i2 = entry(k + 2u * stride);
     uint32_t act = 0u, stp = 0u;
@@ -2553,11 +2647,10 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
             const uint32_t ci = b * (uint32_t)BRICK_CELLS + loc;
             // The end of a brick's last cell is the brick's.
             const bool last = loc == (uint32_t)BRICK_CELLS - 1u;
-            uint2 inf = make_uint2(0u, 0u), sb = make_uint2(0u, 0u);
+            uint2 sb = make_uint2(0u, 0u);
             if (pt & (1u << 11)) {
               ast = D.cstart[ci];
-              if (last) inf = D.binfo[b];
-              else aen = D.cstart[ci + 1];
+              aen = last ? D.dend[b] : D.cstart[ci + 1];
             }
             if (pt & (1u << 12)) {
               sb = D.bsinfo[b];
@@ -2565,10 +2658,7 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
               if (!last) sen = D.sstart[ci + 1];
               hd = D.shead[ci];
             }
-            if (last) {
-              aen = inf.x + inf.y;
-              sen = sb.x + sb.y;
-            }
+            if (last) sen = sb.x + sb.y;
             if (sb.y == 0u) sst = sen = 0u;
           }
         }
@@ -2593,7 +2683,7 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
           if (kind == CE_RECENT)
             h = walk_recent<PER>(D, en.x, p3_of(pq), grain_of(pq), tests);
           else
-            h = scan_range<PER>(D, kind == CE_ACTIVE ? D.P : D.PS, en.x, en.x + en.y, p3_of(pq),
+            h = scan_range<PER>(D, kind == CE_ACTIVE ? D.Pd : D.PS, en.x, en.x + en.y, p3_of(pq),
                                 grain_of(pq), rc2, tests);
           if (h) S.hit[L] = 1u;
         }
@@ -2611,7 +2701,7 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
       const uint32_t c = (uint32_t)__popcll(m);
       if (nbuf + c > HIT_BUF) {
         wave_lds_sync();
-        for (uint32_t t = lane; t < nbuf; t += 64u) D.newstop[ch.begin + hbuf[t].x] = hbuf[t].y;
+        for (uint32_t t = lane; t < nbuf; t += 64u) D.newstop[ch.begin + hbuf[t].x] = D.pidx[hbuf[t].y];
         wave_lds_sync();
         nbuf = 0;
       }
@@ -2626,7 +2716,7 @@ __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint3
     wave_lds_sync();
   }
   wave_lds_sync();
-  for (uint32_t t = lane; t < nbuf; t += 64u) D.newstop[ch.begin + hbuf[t].x] = hbuf[t].y;
+  for (uint32_t t = lane; t < nbuf; t += 64u) D.newstop[ch.begin + hbuf[t].x] = D.pidx[hbuf[t].y];
   // Pair tests: one shared-memory add per wave, one global add per block.
   uint32_t wtests;
   (void)wave_excl_scan(tests, wtests);
@@ -2783,8 +2873,7 @@ __global__ __launch_bounds__(TPB) void k_nuc_test(Bind Bd) {
       else D.sgrain[i] = g;
       continue;
     }
-    uint32_t tests = 0;
-    if (foreign_within(D, epoch, y, NIL, tests)) continue;
+    if (any_within(D, epoch, y)) continue;
     D.cand[i] = 1u;
     atomicAdd(&D.cnt->n_cand, 1u);
   }
@@ -2971,10 +3060,10 @@ __global__ __launch_bounds__(TPB) void k_srb_count(Bind Bd) {
       if (gone) ckey = NIL;
     }
     const Run rc = wave_run(ckey);
-    if (ckey != NIL && rc.off == 0) atomicAdd(&D.ccnt[ckey], (uint32_t)rc.len);
+    if (ckey != NIL && rc.off == 0) atomicAdd(&D.ccnt[ckey], (uint32_t)rc.rest);
     const uint32_t bkey = ckey == NIL ? NIL : ckey / (uint32_t)BRICK_CELLS;
     const Run rb = wave_run(bkey);
-    if (bkey != NIL && rb.off == 0) atomicAdd(&D.bcnt[bkey], (uint32_t)rb.len);
+    if (bkey != NIL && rb.off == 0) atomicAdd(&D.bcnt[bkey], (uint32_t)rb.rest);
   }
 }
 
@@ -3005,10 +3094,10 @@ __global__ __launch_bounds__(TPB) void k_srb_scatter(Bind Bd) {
     const uint32_t cs = ckey != NIL ? D.sstart[ckey] : 0u;
     const Run run = wave_run(ckey);
     uint32_t rbase = 0;
-    if (ckey != NIL && run.off == 0) rbase = atomicSub(&D.ccnt[ckey], (uint32_t)run.len);
+    if (ckey != NIL && run.off == 0) rbase = atomicSub(&D.ccnt[ckey], (uint32_t)run.rest);
     rbase = __shfl(rbase, run.head);
     if (ckey != NIL) {
-      const uint32_t dst = cs + rbase - (uint32_t)run.len + (uint32_t)run.off;
+      const uint32_t dst = cs + rbase - (uint32_t)run.rest;
       if (dst < D.cap_s) {
         D.S2[dst] = r;
         D.PS2[dst] = q;
@@ -3493,7 +3582,7 @@ __global__ __launch_bounds__(TPB) void k_fill_bmeta(Bind Bd) {
   if (V.b == 0 && threadIdx.x == 0) D.cnt->epoch = 1u;
   for (uint64_t b = (uint64_t)V.b * TPB + threadIdx.x; b < D.n_bricks;
        b += (uint64_t)V.G * TPB)
-    D.bmeta[b] = make_uint4(0u, NIL, 0u, NIL);
+    D.bmeta[b] = make_uint4(0u, NIL, 0u, 0u);
 }
 
 // New records A[first, first+count): those marked stopped, and (with box
@@ -4414,7 +4503,7 @@ static void scan_bricks(const Dev& d, int mode, hipStream_t s) {
     k_scan_top<<<1, TPB, 0, s>>>(Plain{d}, mode);
     k_scan_write<<<ntiles, TPB, 0, s>>>(Plain{d}, mode);
   }
-  k_cellscan<<<mode == 0 ? d.sched[TK_CELLSCAN] : (uint32_t)STREAM_GRID, TPB, 0, s>>>(Plain{d}, mode);
+  if (mode == 1) k_cellscan<<<d.sched[TK_CELLSCAN], TPB, 0, s>>>(Plain{d});
 }
 void launch_scan(const Dev& d, hipStream_t s) { scan_bricks(d, 0, s); }
 // Without branching there are no children.
@@ -4633,7 +4722,6 @@ void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s) {
     k_advance<Batch, 0, false, false><<<L.site[BS_ADVANCE].total, TPB, 0, s>>>(bind_of(L, BS_ADVANCE), (float)dt);
   k_branch<<<L.site[BS_BRANCH].total, TPB, 0, s>>>(bind_of(L, BS_BRANCH));
   batch_scan(0);
-  k_cellscan<<<L.site[BS_CELLSCAN].total, TPB, 0, s>>>(bind_of(L, BS_CELLSCAN), 0);
   const uint32_t n_kept = L.site[BS_SCATTER].total, n_born = L.site[BS_CHILDREN].total;
   k_scatter<<<n_kept + n_born, TPB, 0, s>>>(Pair<Batch>{bind_of(L, BS_SCATTER), bind_of(L, BS_CHILDREN)},
                                           n_kept, n_born);
@@ -4648,7 +4736,7 @@ void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s) {
   k_finish<<<one, 64, 0, s>>>(bind_of(L, BS_ONE), dt);
   k_srb_count<<<L.site[BS_RESORT].total, TPB, 0, s>>>(bind_of(L, BS_RESORT));
   batch_scan(1);
-  k_cellscan<<<L.site[BS_RESORT].total, TPB, 0, s>>>(bind_of(L, BS_RESORT), 1);
+  k_cellscan<<<L.site[BS_CELLSCAN].total, TPB, 0, s>>>(bind_of(L, BS_CELLSCAN));
   k_srb_scatter<<<L.site[BS_RESORT].total, TPB, 0, s>>>(bind_of(L, BS_RESORT));
   k_srb_finish<<<one, 1, 0, s>>>(bind_of(L, BS_ONE));
 }

@@ -33,7 +33,7 @@ struct Geometry {
 
 struct Layout {
   size_t A, B, P, spawn, spslot, spawn_cnt, newstop, newstop_cnt, S, PS, S2, PS2, snext, shead, sstart,
-      bsinfo, ccnt, cstart, bcnt, binfo, bmeta, dlist, dlist_cnt, dpart, dmask, doff, bown, cown, smask, occ, scan_tmp, ckeys, cbits, clist, dirkeys, gtab, gbox,
+      bsinfo, ccnt, cstart, bcnt, binfo, bmeta, dend, Pd, dpart, drange, doff, bown, cown, smask, occ, scan_tmp, ckeys, cbits, clist, dirkeys, gtab, gbox,
       stab, sstate, cand, sgrain, fgrid, gcnt, fcmin, fcoarse, mslots, greach, gsite, gdead, cnt, bank, dig, total;
 };
 
@@ -143,11 +143,11 @@ Layout layout(const ge_params* p, const Geometry& g) {
   L.bcnt = put(4 * g.n_bricks);
   L.binfo = put(8 * g.n_bricks);
   L.bmeta = put(16 * g.n_bricks);
-  L.dlist = put(4 * g.n_bricks);
-  L.dlist_cnt = put(4 * ge::STREAM_GRID);
+  L.dend = put(4 * g.n_bricks);
+  L.Pd = put(16 * cp);
   L.dpart = put(4 * cp);
   L.bown = put(8 * g.n_bricks);
-  L.dmask = put(8 * g.n_bricks);
+  L.drange = put(8 * g.n_bricks);
   L.doff = put(4 * g.n_bricks);
   L.cown = put(8 * g.n_cells);
   L.smask = put(4 * g.n_cells);
@@ -376,7 +376,6 @@ static ge_status reset_device(ge_ctx* c) {
   HIPCHK(c, hipMemsetAsync(w + L.shead, 0xFF, 4 * g.n_cells, s));
   HIPCHK(c, hipMemsetAsync(w + L.ccnt, 0, 4 * g.n_cells, s));
   HIPCHK(c, hipMemsetAsync(w + L.bcnt, 0, 4 * g.n_bricks, s));
-  HIPCHK(c, hipMemsetAsync(w + L.dlist_cnt, 0, 4 * ge::STREAM_GRID, s));
   HIPCHK(c, hipMemsetAsync(w + L.bown, 0, 8 * g.n_bricks, s));
   HIPCHK(c, hipMemsetAsync(w + L.cown, 0xFF, 8 * g.n_cells, s));
   HIPCHK(c, hipMemsetAsync(w + L.smask, 0, 4 * g.n_cells, s));
@@ -533,11 +532,12 @@ ge_status ge_create(const ge_params* p, void* workspace, size_t bytes, void* str
   d.bcnt = (uint32_t*)(w + L.bcnt);
   d.binfo = (uint2*)(w + L.binfo);
   d.bmeta = (uint4*)(w + L.bmeta);
-  d.dlist = (uint32_t*)(w + L.dlist);
-  d.dlist_cnt = (uint32_t*)(w + L.dlist_cnt);
+  d.dend = (uint32_t*)(w + L.dend);
+  d.Pd = (float4*)(w + L.Pd);
+  d.pidx = d.spawn;
   d.dpart = (uint32_t*)(w + L.dpart);
   d.bown = (uint2*)(w + L.bown);
-  d.dmask = (unsigned long long*)(w + L.dmask);
+  d.drange = (uint2*)(w + L.drange);
   d.doff = (uint32_t*)(w + L.doff);
   d.cown = (uint2*)(w + L.cown);
   d.smask = (uint32_t*)(w + L.smask);

@@ -144,3 +144,48 @@ def test_stopped_particles_block_and_survive_steps():
     ctx.step(1e-4, 1)
     st = ctx.counts()
     assert st["n_active"] == 0 and st["n_stopped"] == 2
+
+
+@pytest.mark.parametrize("seed,n_grains,per_grain,m,spread,h_factor,periodic", [
+    (6, 12, 60, 6, 120e-6, 1.0, 0), (7, 12, 60, 6, 120e-6, 2.0, 0),   # several bricks per stencil
+    (8, 40, 400, 8, 150e-6, 2.0, 0),                                  # crowded bricks
+    (9, 12, 60, 6, 120e-6, 1.0, 7), (10, 12, 60, 6, 120e-6, 2.0, 7)])  # around a periodic corner
+def test_sites_near_particles_do_not_fire(seed, n_grains, per_grain, m, spread, h_factor, periodic):
+    """Sites of a cloud without claims: one fires unless a particle or an
+    earlier site fired in the step lies within rc, in the FP32 arithmetic of
+    the step on its own exported positions."""
+    require_gpu()
+    lam = 5e-6
+    f4 = np.float32
+    centre, quat, parts = _cloud(seed, n_grains, per_grain, lam, m, 0.3, spread)
+    g = W.rng(seed + 100)
+    sites = 5e-4 + (g.random((600, 3)) - 0.5) * (spread + 2 * m * lam)
+    if periodic:
+        centre, sites = centre - 5e-4, np.mod(sites - 5e-4, 1e-3)
+    p = B.make_params((0, 0, 0), (1e-3,) * 3, lam, h_factor * lam, lam, W.KIN_A, W.KIN_B,
+                      branching=0, cap_particles=1 << 16, cap_stopped=1 << 16, cap_grains=1024,
+                      cap_claim_bricks=1 << 12, cap_sites=1024, periodic=periodic)
+    ctx = B.Context(p)
+    ctx.set_thermal_field(W.Field(W.FIELD_UNIFORM, dT=3.0))
+    ctx.load_state(centre, quat, parts, EMPTY_CLAIMS, np.zeros(0, np.int32), 0.0, 0)
+    ctx.nucleate(sites, np.zeros(len(sites)), W.shoemake_quaternions(g, len(sites)))
+    ctx.step(1e-4, 1)
+    q = ctx.particles()
+    q = q[q["grain"] < n_grains]
+    x = np.stack([q["x"], q["y"], q["z"]], 1).astype(f4)
+    y = sites.astype(f4)
+    L = f4(1e-3)
+
+    def near(a, b):
+        d = a - b
+        if periodic:  # nearest images; the product is exact in FP64, so one rounding
+            k = np.rint(d * (f4(1) / L))
+            d = (d.astype(np.float64) - k.astype(np.float64) * np.float64(L)).astype(f4)
+        return (d[..., 0] * d[..., 0] + d[..., 1] * d[..., 1]) + d[..., 2] * d[..., 2] < f4(lam * lam)
+
+    want = np.zeros(len(y), bool)
+    for i in range(len(y)):
+        want[i] = not near(y[i], x).any() and not (want.any() and near(y[i], y[want]).any())
+    assert 20 < want.sum() < len(y) - 20
+    np.testing.assert_array_equal(ctx.site_states() == 1, want)
+    ctx.close()
