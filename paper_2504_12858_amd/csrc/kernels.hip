@@ -248,6 +248,11 @@ __device__ __forceinline__ uint32_t cell_index(const Dev& D, int cx, int cy, int
   return brick_index(D, cx, cy, cz) * (uint32_t)BRICK_CELLS + local_index(cx, cy, cz);
 }
 
+__device__ __forceinline__ uint32_t brick_of(const Dev& D, P3 p) {
+  const C3 c = cell_of(D, p);
+  return brick_index(D, c.x, c.y, c.z);
+}
+
 __device__ __forceinline__ float dist2(P3 a, P3 b) {
   float dx = a.x - b.x, dy = a.y - b.y, dz = a.z - b.z;
   return (dx * dx + dy * dy) + dz * dz;
@@ -677,6 +682,21 @@ __device__ __forceinline__ Run wave_run(uint32_t key) {
   const unsigned long long above = (H >> lane) >> 1;
   r.rest = above ? __ffsll((long long)above) : 64 - lane;
   return r;
+}
+
+// Scattered atomics come to 27 per ns on the whole chip, returning or not,
+// whatever the footprint (lanes on different words of a 64-byte line are one
+// access, lanes on one word are not), so runs are made long: lanes that count
+// nothing carry the key of where they are and do not end a run.
+//
+// Counting lanes (`mine` as a ballot) from this lane to the end of its run.
+__device__ __forceinline__ uint32_t run_rest(const Run& r, unsigned long long mine) {
+  return (uint32_t)__popcll((mine >> lane_id()) & (~0ull >> (64 - r.rest)));
+}
+// The same for counts: sum of n from this lane to the end of its run.
+__device__ __forceinline__ uint32_t run_rest_sum(const Run& r, uint32_t n) {
+  const uint32_t incl = wave_incl_scan(n);
+  return (uint32_t)__shfl((int)incl, lane_id() + r.rest - 1) - incl + n;
 }
 
 // Contiguous chunk of [0, n) per block (whole granules), logical block lb of
@@ -1148,7 +1168,7 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
     uint4 r = valid ? D.A[i] : make_uint4(0u, 0u, 0u, 0u);
     const bool act = valid && ((rec_fl(r) & 3u) == ST_ACTIVE);
     uint32_t bkey = NIL;
-    bool spawn = false, exited = false;
+    bool spawn = false, exited = false, keep = false;
     P3 x2 = {0.0f, 0.0f, 0.0f};
     uint32_t tag = NIL;
     bool gone = false;
@@ -1209,16 +1229,18 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
         if (s2 >= 2.0f * D.lambda0) bad |= ERR_CFL;
       } else {
         fl = ST_ACTIVE | FL_KEEP;
-        const C3 c = cell_of(D, PM == 0 ? x2 : place(D, x2).p);
-        bkey = brick_index(D, c.x, c.y, c.z);
+        keep = true;
       }
+      const C3 c = cell_of(D, PM == 0 ? x2 : place(D, x2).p);
+      bkey = brick_index(D, c.x, c.y, c.z);
       r = make_rec(s2, g, d, sx, sy, sz, fl);
       D.A[i] = r;
     }
     // Brick counts of the particles that stay active: one atomic per run of
-    // equal keys in consecutive lanes (the input is brick-sorted).
+    // equal bricks (the input is brick-sorted).
     const Run rb = wave_run(bkey);
-    if (bkey != NIL && rb.off == 0) atomicAdd(&D.bcnt[bkey], (uint32_t)rb.rest);
+    const uint32_t stay = run_rest(rb, __ballot(keep));
+    if (rb.off == 0 && stay > 0u) atomicAdd(&D.bcnt[bkey], stay);
     // Spawners go to the block's region of the spawner list.
     const unsigned long long m = __ballot(spawn);
     if (m) {
@@ -1459,9 +1481,9 @@ __device__ __forceinline__ void branch_alone(const Dev& D, const SpawnView& it, 
     }
     uint32_t dep = NIL, rg = NIL;
     // Children of this lane's spawner (mask 0 past the range), placed after
-    // the tests so that the cell and brick counts of a direction are added
-    // once per run of equal keys of the wave.
-    uint32_t mask = 0, g = 0;
+    // the tests: nearly all start in the brick of the reached site (`home`),
+    // whose count gets one atomic per run of spawners of equal bricks.
+    uint32_t mask = 0, g = 0, home = NIL;
     int S[3] = {0, 0, 0};
     float sc2 = 0.0f;
     SlotCache wc{~0ull, -1};
@@ -1506,7 +1528,8 @@ __device__ __forceinline__ void branch_alone(const Dev& D, const SpawnView& it, 
       }
       // The grain row for the children's positions, loaded before the
       // round's atomics.
-      if (mask) F = site_frame(load_grow(D.gtab + (size_t)g * GT_STRIDE), S[0], S[1], S[2]);
+      F = site_frame(load_grow(D.gtab + (size_t)g * GT_STRIDE), S[0], S[1], S[2]);
+      home = brick_of(D, place(D, F.o).p);
       // The parent retires whether or not a child survives: without one, every
       // outer neighbour of S already belongs to the grain (interior point).
       D.A[i] = with_fl(r, ST_RETIRED | FL_SPAWN | (mask << 8));
@@ -1528,21 +1551,27 @@ __device__ __forceinline__ void branch_alone(const Dev& D, const SpawnView& it, 
       if (D.melting) rg = g;
       nsp += 1;
     }
+    uint32_t nh = 0;
+    unsigned long long level = 0;  // claims in the word of the reached site's level
     for (int dd = 0; dd < 6; ++dd) {
-      uint32_t bk = NIL;
-      if ((mask >> dd) & 1u) {
-        const P3 xc = place(D, frame_pos(F, dd, sc2)).p;
-        const C3 c = cell_of(D, xc);
-        bk = brick_index(D, c.x, c.y, c.z);
-        const int ta = dd >> 1, ts = (dd & 1) ? -1 : 1;
-        const int tx = S[0] + (ta == 0 ? ts : 0), ty = S[1] + (ta == 1 ? ts : 0),
-                  tz = S[2] + (ta == 2 ? ts : 0);
+      if (!((mask >> dd) & 1u)) continue;
+      const uint32_t bk = brick_of(D, place(D, frame_pos(F, dd, sc2)).p);
+      if (bk == home) nh += 1;
+      else atomicAdd(&D.bcnt[bk], 1u);
+      const int ta = dd >> 1, ts = (dd & 1) ? -1 : 1;
+      const int tx = S[0] + (ta == 0 ? ts : 0), ty = S[1] + (ta == 1 ? ts : 0),
+                tz = S[2] + (ta == 2 ? ts : 0);
+      if (dd < 4 && slot != NIL && (tx >> 3) == (S[0] >> 3) && (ty >> 3) == (S[1] >> 3))
+        level |= 1ull << (site_bit(tx, ty, tz) & 63u);
+      else
         cached_or(D, wc, g, tx, ty, tz, M_CLAIMED);
-        nch += 1;
-      }
-      const Run rb = wave_run(bk);
-      if (bk != NIL && rb.off == 0) atomicAdd(&D.bcnt[bk], (uint32_t)rb.rest);
+      nch += 1;
     }
+    if (level)
+      atomicOr(D.cbits + (size_t)slot * 24 + CB_CLAIMED + (site_bit(S[0], S[1], S[2]) >> 6), level);
+    const Run hr = wave_run(home);
+    const uint32_t born = run_rest_sum(hr, nh);
+    if (hr.off == 0 && born > 0u) atomicAdd(&D.bcnt[home], born);
     if (D.gcnt) {
       const Run run = wave_run(dep);
       if (dep != NIL && run.off == 0) atomicAdd(&D.gcnt[dep], (uint32_t)run.rest);
@@ -1878,44 +1907,46 @@ __device__ __forceinline__ void scatter_kept(const Dev& D, const VGrid& V) {
     const uint32_t i = base + threadIdx.x;
     const bool valid = i < ch.end;
     const uint4 r = next;
-    const uint32_t fl = valid ? rec_fl(r) : 0u;
+    const bool keep = valid && (rec_fl(r) & FL_KEEP);
     uint32_t bkey = NIL;
     uint32_t g = NIL;
     P3 p = {0.0f, 0.0f, 0.0f};
-    if (fl & FL_KEEP) {
+    // The brick's start and owner bits, and the next particle's record, are
+    // read before the rank atomic: a wave's memory operations retire in order,
+    // so a load issued after it would wait for its round trip.
+    uint32_t start = 0;
+    unsigned long long seen = 0;
+    if (valid) {
       const Placed pl = place(D, rec_pos(D, r));
       g = owner_id(rec_grain(r), pl.code);
       p = pl.p;
-      const C3 c = cell_of(D, p);
-      bkey = brick_index(D, c.x, c.y, c.z);
-    }
-    // Ranks within the brick: one decrement per run of equal bricks; the
-    // counts return to zero once every particle has been placed.  The brick's
-    // start is read before the rank atomic: a wave's memory operations retire
-    // in order, so a load issued after it would wait for its round trip.  So is
-    // the next particle's record.
-    uint32_t start = 0;
-    unsigned long long seen = 0;
-    if (bkey != NIL) {
+      bkey = brick_of(D, p);
       start = D.binfo[bkey].x;
       seen = *brick_owners(D, bkey);
     }
     if (i + TPB < ch.end) next = D.A[i + TPB];
+    // Ranks within the brick: one decrement per run of equal bricks; the
+    // counts return to zero once every particle has been placed.
     const Run run = wave_run(bkey);
+    const unsigned long long kept = __ballot(keep);
+    const uint32_t rest = run_rest(run, kept);
     uint32_t rbase = 0;
-    if (bkey != NIL && run.off == 0) rbase = atomicSub(&D.bcnt[bkey], (uint32_t)run.rest);
+    if (run.off == 0 && rest > 0u) rbase = atomicSub(&D.bcnt[bkey], rest);
     rbase = __shfl(rbase, run.head);
-    // Owner bits of the brick: at most one update per run of equal (brick, grain).
-    const uint32_t pg = lane_before(g, NIL);
-    const bool head = run.off == 0 || pg != g;
-    if (bkey != NIL) {
-      const uint32_t dst = start + rbase - (uint32_t)run.rest;
+    // Owner bits of the brick: from the first kept particle of a run, and from
+    // those of another grain that follow another.
+    const unsigned long long first = (kept >> run.head) & (~0ull >> (64 - run.off - run.rest));
+    const int at = first ? run.head + __ffsll((long long)first) - 1 : run.head;
+    const uint32_t g0 = __shfl(g, at), pg = lane_before(g, NIL);
+    const bool same = run.off > 0 && ((kept >> (lane_id() - 1)) & 1ull) && pg == g;
+    if (keep) {
+      const uint32_t dst = start + rbase - rest;
       if (dst < D.cap_p) {
         D.B[dst] = with_fl(r, ST_ACTIVE);
         D.P[dst] = pos4(p, g);
         if (D.tagA) D.tagB[dst] = D.tagA[i];
       }
-      if (head) note_grain(brick_owners(D, bkey), seen, g);
+      if (lane_id() == at || (g != g0 && !same)) note_grain(brick_owners(D, bkey), seen, g);
     }
   }
 }
@@ -1925,44 +1956,72 @@ __device__ __forceinline__ void scatter_kept(const Dev& D, const VGrid& V) {
 __device__ __forceinline__ void scatter_children(const Dev& D, const VGrid& V) {
   __shared__ uint32_t s_off[STREAM_GRID + 1];
   const SpawnView it = spawn_view<false>(D, V, s_off);
-  for (uint32_t k = it.begin + threadIdx.x; k < it.end; k += TPB) {
-    const uint32_t kp = spawn_pos(it, s_off, k);
-    const uint4 r = D.A[D.spawn[kp]];
-    const uint32_t fl = rec_fl(r);
+  for (uint32_t k0 = it.begin; k0 < it.end; k0 += TPB) {
+    const uint32_t k = k0 + threadIdx.x;
+    const bool on = k < it.end;
+    uint4 r = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t slot = NIL;
+    if (on) {
+      const uint32_t kp = spawn_pos(it, s_off, k);
+      r = D.A[D.spawn[kp]];
+      slot = D.spslot[kp];
+    }
     const uint32_t gs = rec_grain(r);
-    const int d = rec_dir(r);
-    const int ra = d >> 1, re = (d & 1) ? -1 : 1;
+    const int d = rec_dir(r), ra = d >> 1, re = (d & 1) ? -1 : 1;
     const int S[3] = {rec_sx(r) + (ra == 0 ? re : 0), rec_sy(r) + (ra == 1 ? re : 0),
                       rec_sz(r) + (ra == 2 ? re : 0)};
-    const uint32_t slot = D.spslot[kp];
-    const uint32_t mask = (fl >> 8) & 63u;
-    // The grain row for the children's positions, loaded before the atomics.
+    const uint32_t mask = (rec_fl(r) >> 8) & 63u;
+    // Nearly all children start in the brick of the reached site (`home`): they
+    // take their ranks with one atomic per run of spawners of equal bricks.
+    // The brick's start and owner bits are read before the atomics, as above.
+    uint32_t home = NIL, start = 0;
+    unsigned long long seen = 0;
     SiteFrame F{};
-    if (mask) F = site_frame(load_grow(D.gtab + (size_t)gs * GT_STRIDE), S[0], S[1], S[2]);
+    if (on) {
+      F = site_frame(load_grow(D.gtab + (size_t)gs * GT_STRIDE), S[0], S[1], S[2]);
+      home = brick_of(D, place(D, F.o).p);
+      start = D.binfo[home].x;
+      seen = *brick_owners(D, home);
+    }
     if (slot != NIL) {
       const uint32_t b = site_bit(S[0], S[1], S[2]);
       atomicAnd(D.cbits + (size_t)slot * 24 + CB_NOW + (b >> 6), ~(1ull << (b & 63)));
     }
-    if (!mask) continue;
     const float sc = rec_s(r) - D.lambda0;
     // One child per lane and round, whichever its direction: a wave takes as
     // many rounds as the spawner with the most children has.
+    uint32_t nh = 0, own = NIL;  // children at home, the first one's owner word
+    for (uint32_t m = mask; m; m &= m - 1u) {
+      const float4 xc = placed4(D, frame_pos_any(F, __builtin_ctz(m), sc), gs);
+      if (brick_of(D, p3_of(xc)) != home) continue;
+      if (nh == 0u) own = grain_of(xc);
+      nh += 1;
+    }
+    const Run run = wave_run(home);
+    const uint32_t rest = run_rest_sum(run, nh);
+    uint32_t base = 0;
+    if (run.off == 0 && rest > 0u) base = atomicSub(&D.bcnt[home], rest);
+    base = __shfl(base, run.head);
+    const uint32_t before = lane_before(own, NIL);
+    if (nh > 0u && (run.off == 0 || before != own)) note_grain(brick_owners(D, home), seen, own);
+    uint32_t to = start + base - rest;
     for (uint32_t m = mask; m; m &= m - 1u) {
       const int dd = __builtin_ctz(m);
       const float4 xc = placed4(D, frame_pos_any(F, dd, sc), gs);
-      const C3 c = cell_of(D, p3_of(xc));
-      const uint32_t b = brick_index(D, c.x, c.y, c.z);
-      // The brick's start and its owner bits before the rank atomic, as above.
-      unsigned long long* owners = brick_owners(D, b);
-      const uint32_t start = D.binfo[b].x;
-      const unsigned long long seen = *owners;
-      const uint32_t dst = start + atomicSub(&D.bcnt[b], 1u) - 1u;
+      const uint32_t b = brick_of(D, p3_of(xc));
+      uint32_t dst;
+      if (b == home) {
+        dst = to++;
+        if (grain_of(xc) != own) note_grain(brick_owners(D, home), seen, grain_of(xc));
+      } else {
+        dst = D.binfo[b].x + atomicSub(&D.bcnt[b], 1u) - 1u;
+        note_grain(brick_owners(D, b), 0ull, grain_of(xc));
+      }
       if (dst < D.cap_p) {
         D.B[dst] = make_rec(sc, gs, dd, S[0], S[1], S[2], ST_ACTIVE);
         D.P[dst] = xc;
         if (D.tagA) D.tagB[dst] = NIL;
       }
-      note_grain(owners, seen, grain_of(xc));
     }
   }
 }
@@ -1970,9 +2029,12 @@ __device__ __forceinline__ void scatter_children(const Dev& D, const VGrid& V) {
 // Both scatters in one launch: they write different places and share no other
 // state.  On a large state the children's blocks follow those of the kept
 // particles and fill the chip as these end, finding the bricks' words in the
-// caches (14M active particles: 421 us, as two launches 451; with the children
-// first 495, alternating 518).  On a small one the blocks of the two alternate
-// (285k active particles: 15 us, one after the other 20, as two launches 24).
+// caches (14M active particles: 423 us, as two launches 432; with the children
+// first and alternating another 70 and 100).  On a small one the blocks of the
+// two alternate (285k active particles: 15 us, one after the other 20, as two
+// launches 24).  Bound by scattered atomics and partly written lines: with runs
+// that spawners end and one atomic per child the 14M took 423 us, with long runs
+// 286.
 template <class Bind>
 __global__ __launch_bounds__(TPB, 8) void k_scatter(Pair<Bind> Bd, uint32_t n_kept, uint32_t n_born) {
   Dev D;
