@@ -233,6 +233,7 @@ struct Dev {
   uint32_t n_sites;
   // counters
   Counters* cnt;
+  Counters* hcnt;  // the context's pinned copy (host memory, written by k_publish)
   Bank* bank;  // [N_BANKS]
   // adjoint recording (all null when off): tags travel with the records of
   // A and B (tag = index into the tracked set, NIL for untracked particles)
@@ -298,6 +299,7 @@ void launch_stoplink(const Dev& d, hipStream_t s);
 void launch_nucleate(const Dev& d, hipStream_t s);
 void launch_finish(const Dev& d, double dt, hipStream_t s);
 void launch_reset_stats(const Dev& d, hipStream_t s);
+void launch_publish(const Dev& d, hipStream_t s);  // counters to the pinned copy
 void launch_stopped_rebuild(const Dev& d, hipStream_t s);  // S -> S2 (caller swaps)
 void launch_resample(const Dev& d, hipStream_t s);
 // Melting by walk-back, run at the start of a step when enabled: least node
@@ -344,6 +346,7 @@ void launch_export_claims(const Dev& d, uint32_t* counter, void* out, uint32_t c
 void launch_grain_map(const Dev& d, const int32_t n[3], const float origin[3],
                       const float spacing[3], uint32_t* out, hipStream_t s);
 void launch_batch_reset_stats(const BatchLaunch& L, hipStream_t s);
+void launch_batch_publish(const BatchLaunch& L, hipStream_t s);
 void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s);
 void launch_digest(const Dev& d, unsigned long long* out /*[3], zeroed*/, hipStream_t s);
 void launch_adj_init(const Dev& d, uint32_t n, int32_t n_steps, hipStream_t s);

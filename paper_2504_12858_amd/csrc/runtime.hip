@@ -230,6 +230,13 @@ struct ge_ctx {
   hipGraphExec_t gexec = nullptr;
   uint64_t gversion = 0;
   double gdt = 0.0;
+  // one recorded step that is not followed by a re-sort, for calls of a few
+  // steps; recorded once STEP_SEEN such steps in a row had the same arguments
+  hipGraphExec_t g1exec = nullptr;
+  bool g1_valid = false;
+  uint64_t g1version = 0;
+  double g1dt = 0.0;
+  int32_t g1_seen = 0;
   hipStream_t cap_stream = nullptr;  // capture stream (the context's stream may be the null stream)
   // mushy-zone deposition grid (nodes 0: off) and the volume of its cells
   uint64_t dep_nodes = 0;
@@ -345,8 +352,8 @@ static ge_status hip_check(ge_ctx* c, hipError_t e, const char* what) {
   } while (0)
 
 static ge_status read_counters(ge_ctx* c) {
-  HIPCHK(c, hipMemcpyAsync(c->host_cnt, c->d.cnt, sizeof(ge::Counters), hipMemcpyDeviceToHost,
-                           c->stream));
+  ge::launch_publish(c->d, c->stream);
+  HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return GE_OK;
 }
@@ -407,6 +414,7 @@ static ge_status sync_dev(ge_ctx* c) {
 static void step_once(ge_ctx* c, double dt);
 static ge_status sync_dev(ge_ctx* c);
 static ge_status ensure_graph(ge_ctx* c, double dt);
+static ge_status step_alone(ge_ctx* c, double dt);
 
 extern "C" {
 
@@ -471,6 +479,14 @@ ge_status ge_create(const ge_params* p, void* workspace, size_t bytes, void* str
   char* w = c->ws;
   Dev& d = c->d;
   std::memset(&d, 0, sizeof(Dev));
+  if (const hipError_t e = hipHostGetDevicePointer((void**)&d.hcnt, c->host_cnt, 0); e != hipSuccess) {
+    g_create_err = "pinned counters: " + std::string(hipGetErrorString(e));
+    (void)hipGetLastError();
+    (void)hipHostFree(c->host_word);
+    (void)hipHostFree(c->host_cnt);
+    delete c;
+    return GE_EDEVICE;
+  }
   for (int a = 0; a < 3; ++a) {
     d.lo[a] = (float)p->lo[a];
     d.hi[a] = (float)p->hi[a];
@@ -579,6 +595,7 @@ ge_status ge_destroy(ge_ctx* c) {
   if (!c) return GE_EINVAL;
   (void)hipStreamSynchronize(c->stream);
   if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
+  if (c->g1exec) (void)hipGraphExecDestroy(c->g1exec);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   (void)hipHostFree(c->host_cnt);
@@ -841,7 +858,8 @@ ge_status ge_step(ge_ctx* c, double dt, int32_t n_steps, ge_step_stats* stats) {
     // Plain steps up to a multiple of resort_every, then whole recorded
     // sequences of resort_every steps, then the rest plain.
     while (k < n_steps && c->hstep % (uint64_t)R != 0) {
-      step_once(c, dt);
+      ge_status st = step_alone(c, dt);
+      if (st != GE_OK) return st;
       ++k;
     }
     const int32_t reps = (n_steps - k) / R;
@@ -853,7 +871,10 @@ ge_status ge_step(ge_ctx* c, double dt, int32_t n_steps, ge_step_stats* stats) {
       c->hstep += (uint64_t)reps * (uint64_t)R;
     }
   }
-  for (; k < n_steps; ++k) step_once(c, dt);
+  for (; k < n_steps; ++k) {
+    ge_status st = step_alone(c, dt);
+    if (st != GE_OK) return st;
+  }
   HIPCHK(c, hipGetLastError());
   if (!stats) return GE_OK;
   ge_status st = read_counters(c);
@@ -903,36 +924,80 @@ static void step_once(ge_ctx* c, double dt) {
   prof_mark(c, 11);
 }
 
-// Records resort_every steps from a step count that is a multiple of
-// resort_every (nothing runs during the recording) and instantiates them.
-static ge_status ensure_graph(ge_ctx* c, double dt) {
-  if (c->graph_valid && c->gversion == c->dev_version && c->gdt == dt) return GE_OK;
-  if (c->gexec) {
-    HIPCHK(c, hipGraphExecDestroy(c->gexec));
-    c->gexec = nullptr;
+// Records n steps of the context from step count h and instantiates them
+// (nothing runs during the recording).
+static ge_status record_steps(ge_ctx* c, double dt, int32_t n, uint64_t h, hipGraphExec_t* out) {
+  if (*out) {
+    HIPCHK(c, hipGraphExecDestroy(*out));
+    *out = nullptr;
   }
-  c->graph_valid = false;
   if (!c->cap_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
   const uint64_t h0 = c->hstep;
   hipStream_t user = c->stream;
   c->stream = c->cap_stream;
+  c->hstep = h;
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
     c->capturing = true;
-    for (int32_t k = 0; k < c->resort_every; ++k) step_once(c, dt);
+    for (int32_t k = 0; k < n; ++k) step_once(c, dt);
     c->capturing = false;
     e = hipStreamEndCapture(c->cap_stream, &g);
   }
   c->stream = user;
   c->hstep = h0;
   HIPCHK(c, e);
-  e = hipGraphInstantiate(&c->gexec, g, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
   (void)hipGraphDestroy(g);
   HIPCHK(c, e);
+  return GE_OK;
+}
+
+// The recorded sequence of resort_every steps, from a step count that is a
+// multiple of resort_every.
+static ge_status ensure_graph(ge_ctx* c, double dt) {
+  if (c->graph_valid && c->gversion == c->dev_version && c->gdt == dt) return GE_OK;
+  c->graph_valid = false;
+  ge_status st = record_steps(c, dt, c->resort_every, 0, &c->gexec);
+  if (st != GE_OK) return st;
   c->graph_valid = true;
   c->gversion = c->dev_version;
   c->gdt = dt;
+  return GE_OK;
+}
+
+// One step by itself: replayed where the same step has come STEP_SEEN times in
+// a row, else launched.  A small state's step takes 34 us on the device, and a
+// call of one step with its counters took 68 us launched and takes 53 replayed.
+// Recording costs a few steps' time and a coupled solver's fields change every
+// few steps, hence the count.
+static ge_status step_alone(ge_ctx* c, double dt) {
+  constexpr int32_t STEP_SEEN = 8;
+  const bool resorts = (c->hstep + 1) % (uint64_t)c->resort_every == 0;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (c->use_graphs && !c->prof_on && c->prof_one < 0 && !resorts) {
+    const hipError_t e = hipStreamIsCapturing(c->stream, &cap);
+    if (e != hipSuccess) (void)hipGetLastError();
+    if (e == hipSuccess && cap == hipStreamCaptureStatusNone) {
+      if (c->g1version != c->dev_version || c->g1dt != dt) {
+        c->g1_valid = false;
+        c->g1_seen = 0;
+        c->g1version = c->dev_version;
+        c->g1dt = dt;
+      }
+      if (!c->g1_valid && ++c->g1_seen > STEP_SEEN) {
+        ge_status st = record_steps(c, dt, 1, 0, &c->g1exec);
+        if (st != GE_OK) return st;
+        c->g1_valid = true;
+      }
+      if (c->g1_valid) {
+        HIPCHK(c, hipGraphLaunch(c->g1exec, c->stream));
+        c->hstep += 1;
+        return GE_OK;
+      }
+    }
+  }
+  step_once(c, dt);
   return GE_OK;
 }
 
@@ -1979,8 +2044,13 @@ ge_status batch_bind(ge_batch* b) {
   for (uint32_t m = 0; m < n; ++m) {
     ge_ctx* c = b->mem[m];
     if (c->dead) return bfail(b, GE_ESTATE, "a member context is unusable after an earlier error");
-    ge_status st = read_counters(c);
-    if (st != GE_OK) return bfail(b, st, c->err);
+    ge::launch_publish(c->d, c->stream);
+  }
+  if (hipGetLastError() != hipSuccess) return bfail(b, GE_EDEVICE, "batch launch");
+  for (uint32_t m = 0; m < n; ++m) {
+    ge_ctx* c = b->mem[m];
+    if (hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize") != GE_OK)
+      return bfail(b, GE_EDEVICE, c->err);
     w[m] = (double)c->host_cnt->n_active + 64.0;
     wsum += w[m];
   }
@@ -2187,12 +2257,13 @@ ge_status ge_batch_step(ge_batch* b, double dt, int32_t n_steps, ge_step_stats* 
     k = reps * b->R;
   }
   for (; k < n_steps; ++k) ge::launch_batch_step(b->L, dt, s);
+  ge::launch_batch_publish(b->L, s);
   if (hipGetLastError() != hipSuccess) return bfail(b, GE_EDEVICE, "batch launch");
+  const hipError_t done = hipStreamSynchronize(s);
   ge_status worst = GE_OK;
   for (size_t m = 0; m < b->mem.size(); ++m) {
     ge_ctx* c = b->mem[m];
-    st = read_counters(c);
-    if (st != GE_OK) return bfail(b, st, c->err);
+    if ((st = hip_check(c, done, "hipStreamSynchronize")) != GE_OK) return bfail(b, st, c->err);
     c->hstep = c->host_cnt->step;
     if (stats) fill_stats(c, &stats[m]);
     st = error_status(c, c->host_cnt->err);

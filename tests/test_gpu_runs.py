@@ -442,3 +442,35 @@ def test_few_blocks_per_launch_change_nothing(blocks):
     assert gpu_parts(a)[0].tobytes() == gpu_parts(b)[0].tobytes()
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("resort_every", [1, 2, 16])
+def test_single_step_calls_replayed_or_launched(resort_every):
+    """Calls of one step (replayed after a while, launched around re-sorts and
+    after a change of the time step or the field) leave the state of one call
+    for all, and each call's counters are its own step's."""
+    require_gpu()
+    w = W.directional(seed=5, n_grains=4, size=(2e-4, 2e-4, 4e-4), dT0=10.0, dt=5e-4)
+
+    def make(graphs):
+        ctx = B.Context.from_workload(w, cap_particles=1 << 16, cap_stopped=1 << 16, cap_grains=64,
+                                      cap_claim_bricks=1 << 12, resort_every=resort_every)
+        ctx.use_graphs(graphs)
+        return ctx
+    a, b = make(True), make(False)
+    adv = 0
+    for dt, dT in ((w.dt, 10.0), (w.dt / 2, 10.0), (w.dt / 2, 11.0)):
+        f = W.Field(W.FIELD_UNIFORM, dT=dT)
+        a.set_thermal_field(f)
+        b.set_thermal_field(f)
+        one = [a.step(dt, 1) for _ in range(37)]
+        all_ = b.step(dt, 37)
+        assert [s["step"] for s in one] == list(range(one[0]["step"], one[0]["step"] + 37))
+        for key in ("advanced", "spawners", "children", "contained"):
+            assert sum(s[key] for s in one) == all_[key]
+        adv += all_["advanced"]
+        assert a.digest() == b.digest()
+        assert a.counts() == b.counts()
+    assert adv > 0
+    a.close()
+    b.close()
