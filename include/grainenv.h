@@ -493,9 +493,10 @@ ge_status ge_hold(ge_ctx* ctx, int32_t on);
 
 /* Launch schedule: the number of thread blocks (256 threads each) of every
    tunable kernel of ge_step.  Kernels: advance, branch, cell scan, scatter,
-   child scatter, dirty-brick pass, containment, stop linking.  The schedule changes only speed, never results.  The default,
-   set by ge_create, is the number of blocks the device keeps resident at
-   once for each kernel.
+   child scatter, dirty-brick pass, containment, stop linking.  The schedule
+   changes only speed, never results.  The default, set by ge_create, is the
+   number of blocks the device keeps resident at once for each kernel, at most
+   one per 256 particles of cap_particles.
    ge_get_schedule writes the current schedule.  ge_set_schedule takes a new
    one; an entry of 0 keeps the current value; EINVAL for an entry outside
    [1, GE_MAX_BLOCKS].

@@ -288,7 +288,8 @@ struct BatchLaunch {
 };
 
 // -------------------------------------------------- host-side launchers --
-hipError_t resident_grids(Dev& d);  // default schedule for the current device
+// Default schedule for the current device (shared: of the launches of a batch).
+hipError_t resident_grids(Dev& d, bool shared);
 void launch_advance(const Dev& d, float dt, hipStream_t s);
 void launch_branch(const Dev& d, hipStream_t s);
 void launch_scan(const Dev& d, hipStream_t s);

@@ -576,7 +576,7 @@ ge_status ge_create(const ge_params* p, void* workspace, size_t bytes, void* str
   d.cnt = (ge::Counters*)(w + L.cnt);
   d.bank = (ge::Bank*)(w + L.bank);
   d.resort_every = c->resort_every;
-  ge_status st = hip_check(c, ge::resident_grids(d), "occupancy query");
+  ge_status st = hip_check(c, ge::resident_grids(d, false), "occupancy query");
   if (st == GE_OK) st = sync_dev(c);
   if (st == GE_OK) st = reset_device(c);
   if (st == GE_OK) st = hip_check(c, hipStreamSynchronize(c->stream), "create");
@@ -2189,12 +2189,18 @@ ge_status ge_batch_create(int32_t n, const ge_params* params, void* workspace, s
     b->mem_off.push_back(B.mem_off[i]);
   }
   b->off_tab = B.off_tab;
+  Dev all = b->mem[0]->d;
+  if (hip_check(b->mem[0], ge::resident_grids(all, true), "occupancy query") != GE_OK) {
+    g_create_err = b->mem[0]->err;
+    ge_batch_destroy(b);
+    return GE_EDEVICE;
+  }
   for (int k = 0; k < ge::BS_N; ++k) {
     b->off_map[k] = B.off_map[k];
     b->off_gsz[k] = B.off_gsz[k];
     b->cap[k] = B.cap[k];
     const int tk = SITE_TK[k];
-    b->T[k] = tk >= 0 ? b->mem[0]->d.sched[tk] : (k == ge::BS_RESORT ? ge::STREAM_GRID : 0);
+    b->T[k] = tk >= 0 ? all.sched[tk] : (k == ge::BS_RESORT ? ge::STREAM_GRID : 0);
   }
   // One host staging array for all maps, in the workspace's order.
   b->hmap.assign((b->off_map[ge::BS_N - 1] - b->off_map[0]) / 4 + b->cap[ge::BS_N - 1], 0u);
