@@ -1628,16 +1628,17 @@ __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
 // (tile sums, their scan by one block, starts).
 //
 // Bound by launches on small grids (4.5 us each), by the counts on large ones;
-// the single launch by its atomics as well, about 25 ns each on one word, and
-// the order of the tiles costs the later kernels some of the locality between
-// tiles.  2M bricks, a third of them occupied: 7.5 us against 15 us in three
-// launches, but k_dirty 69 against 64 us and the whole step the same; 7.8M
-// bricks in 3800 tiles: 99 us against 39 us.  Hence the line at 512 tiles.
+// the single launch by its atomics as well, about 25 ns each on one word for
+// every tile with particles.  2M bricks, few of them occupied: 8.8 us (two tiles
+// per block) against 15 us in three launches; 7.8M bricks in 3800 tiles, most
+// with particles: 99 us against 39 us.  Hence the lines at 512 blocks, which cost
+// 13 us at most.
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = TPB * SCAN_ITEMS;
 static_assert(SCAN_TILE == (int)SCAN_TILE_HOST, "brick-scan tile of the host launchers");
 static_assert(SCAN_ITEMS == 8, "two 16-byte loads per thread");
 constexpr uint32_t SCAN_ONE_LAUNCH = 512u * (uint32_t)SCAN_TILE;
+constexpr uint32_t SCAN_ONE_WIDE = 2u * SCAN_ONE_LAUNCH;  // with two tiles per block (not in a batch)
 
 // The counts of bricks b0 .. b0 + 7 (zero past the last brick): two 16-byte
 // loads when all eight exist (b0 is a multiple of eight and the count array
@@ -1660,7 +1661,8 @@ __device__ __forceinline__ void load_counts8(const Dev& D, uint64_t b0, uint32_t
   }
 }
 
-template <class Bind>
+// ITEMS: bricks per thread.
+template <class Bind, int ITEMS>
 __global__ __launch_bounds__(TPB) void k_scan(Bind Bd, int mode) {
   Dev D;
   VGrid V;
@@ -1668,13 +1670,14 @@ __global__ __launch_bounds__(TPB) void k_scan(Bind Bd, int mode) {
   if (dead(D) || (mode == 1 && !resort_due(D))) return;
   const uint32_t epoch = step_epoch(D);
   __shared__ unsigned long long wsum[TPB / 64], s_base;
-  const uint64_t b0 = (uint64_t)V.b * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
-  uint32_t c[SCAN_ITEMS];
-  load_counts8(D, b0, c);
+  const uint64_t b0 = ((uint64_t)V.b * TPB + threadIdx.x) * ITEMS;
+  uint32_t c[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; k += 8) load_counts8(D, b0 + k, c + k);
   unsigned long long v = 0;
   uint32_t any = 0;
 #pragma unroll
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
+  for (int k = 0; k < ITEMS; ++k) {
     v += (unsigned long long)c[k] | ((unsigned long long)(c[k] > 0u) << 32);
     any |= c[k];
   }
@@ -1689,15 +1692,19 @@ __global__ __launch_bounds__(TPB) void k_scan(Bind Bd, int mode) {
   }
   __syncthreads();
   if (total) ex += s_base;
-  // The re-sort's counts back to zero, the eight at once when they all exist (a
+  // The re-sort's counts back to zero, eight at once when they all exist (a
   // step's are counted down by the scatter).
-  const bool whole = b0 + 8u <= D.n_bricks;
-  if (mode == 1 && whole && any) {
-    *reinterpret_cast<uint4*>(D.bcnt + b0) = make_uint4(0u, 0u, 0u, 0u);
-    *reinterpret_cast<uint4*>(D.bcnt + b0 + 4) = make_uint4(0u, 0u, 0u, 0u);
-  }
+  if (mode == 1 && any) {
 #pragma unroll
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
+    for (int k = 0; k < ITEMS; k += 8)
+      if (b0 + k + 8u <= D.n_bricks) {
+        *reinterpret_cast<uint4*>(D.bcnt + b0 + k) = make_uint4(0u, 0u, 0u, 0u);
+        *reinterpret_cast<uint4*>(D.bcnt + b0 + k + 4) = make_uint4(0u, 0u, 0u, 0u);
+      }
+  }
+  const uint64_t whole = D.n_bricks & ~7ull;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
     const uint64_t b = b0 + k;
     if (b < D.n_bricks) {
       const uint32_t start = (uint32_t)(ex & 0xFFFFFFFFull);
@@ -1712,7 +1719,7 @@ __global__ __launch_bounds__(TPB) void k_scan(Bind Bd, int mode) {
           *reinterpret_cast<unsigned long long*>(m + 2) = 0ull;
         }
         D.occ[occ] = (uint32_t)b;
-        if (mode == 1 && !whole) D.bcnt[b] = 0u;
+        if (mode == 1 && b >= whole) D.bcnt[b] = 0u;
       }
       ex += (unsigned long long)c[k] | ((unsigned long long)(c[k] > 0u) << 32);
     }
@@ -4600,7 +4607,9 @@ void launch_branch(const Dev& d, hipStream_t s) {
 static void scan_bricks(const Dev& d, int mode, hipStream_t s) {
   const uint32_t ntiles = (uint32_t)((d.n_bricks + SCAN_TILE - 1) / SCAN_TILE);
   if (d.n_bricks <= SCAN_ONE_LAUNCH) {
-    k_scan<<<ntiles, TPB, 0, s>>>(Plain{d}, mode);
+    k_scan<Plain, SCAN_ITEMS><<<ntiles, TPB, 0, s>>>(Plain{d}, mode);
+  } else if (d.n_bricks <= SCAN_ONE_WIDE) {
+    k_scan<Plain, 2 * SCAN_ITEMS><<<(ntiles + 1u) / 2u, TPB, 0, s>>>(Plain{d}, mode);
   } else {
     k_scan_reduce<<<ntiles, TPB, 0, s>>>(Plain{d}, mode);
     k_scan_top<<<1, TPB, 0, s>>>(Plain{d}, mode);
@@ -4814,7 +4823,7 @@ void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s) {
   const uint32_t one = L.site[BS_ONE].total, tiles = L.site[BS_TILES].total;
   auto batch_scan = [&](int mode) {
     if (L.max_bricks <= SCAN_ONE_LAUNCH) {
-      k_scan<<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), mode);
+      k_scan<Batch, SCAN_ITEMS><<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), mode);
       return;
     }
     k_scan_reduce<<<tiles, TPB, 0, s>>>(bind_of(L, BS_TILES), mode);

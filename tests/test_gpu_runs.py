@@ -380,8 +380,8 @@ def test_graph_replays_equal_plain_steps():
 
 def test_brick_scan_forms_agree():
     """Two grains grow into each other near a corner of boxes from 512 to
-    1.3M bricks (part of a tile of the brick scan, whole tiles, tile sums in a
-    launch of their own), past two re-sorts: the particles and claims are the
+    2.2M bricks (part of a tile of the brick scan, whole tiles, two tiles per
+    block, tile sums in a launch of their own), past two re-sorts: the particles and claims are the
     same, bit for bit, and so are those of batches with and without the
     largest."""
     require_gpu()
@@ -389,7 +389,7 @@ def test_brick_scan_forms_agree():
     c = np.array([[6e-5, 7e-5, 7e-5], [1e-4, 8.5e-5, 8e-5]])
     q = W.shoemake_quaternions(W.rng(8), 2)
     shells = np.array([4, 3], np.int32)
-    sizes = (1.6e-4, 1e-3, 2.2e-3)
+    sizes = (1.6e-4, 1e-3, 2.2e-3, 2.14e-3, 2.6e-3)  # 107^3 bricks: the last eight are not whole
 
     def params(L):
         return B.make_params((0, 0, 0), (L, L, L), lam, lam, lam, W.KIN_A, W.KIN_B,
