@@ -80,7 +80,6 @@ struct Counters {
   uint32_t err;        // sticky error bits
   uint32_t n_cand;     // nucleation candidates this step
   uint32_t max_step;   // float bits of max v dt (non-negative floats order as uints)
-  uint32_t n_fired;    // sites fired this step
   uint32_t n_live;     // active particles (A also holds records stopped at the end of a step)
   unsigned long long advanced, exited, spawners, children, contained, nucleated;
   unsigned long long pair_tests;  // candidate particles examined by containment
@@ -269,7 +268,7 @@ constexpr uintptr_t NULL_OFFSET = ~(uintptr_t)0;
 // blocks; total: blocks of the launch).
 enum : int {
   BS_RESAMPLE = 0, BS_ADVANCE, BS_ONE, BS_BRANCH, BS_TILES, BS_CELLSCAN,
-  BS_SCATTER, BS_CHILDREN, BS_DIRTY, BS_CONTAIN, BS_STOPLINK, BS_NUCTEST, BS_NUCFIRE,
+  BS_SCATTER, BS_CHILDREN, BS_DIRTY, BS_CONTAIN, BS_STOPLINK, BS_NUCTEST,
   BS_RESORT, BS_N
 };
 constexpr uint32_t BATCH_MAX = 4096;  // contexts per batch (12 bits of a map entry)

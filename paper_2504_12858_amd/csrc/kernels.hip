@@ -19,8 +19,8 @@
 //                particles to test
 //   k_contain    cell-stencil test against other grains' particles
 //   k_stoplink   moves newly stopped particles to the stopped store
-//   k_nuc_test / k_nuc_fire   nucleation of liquid sites past threshold
-//   k_finish     counters for the next step
+//   k_nuc_test   liquid sites past their threshold
+//   k_finish     nucleation of those sites; counters for the next step
 // Every few steps the stopped store is re-sorted by cell with the same
 // brick scan (k_srb_*, k_cellscan), so that containment reads it as contiguous
 // cell ranges; particles stopped since the last re-sort sit in short linked
@@ -2951,13 +2951,8 @@ __global__ __launch_bounds__(TPB) void k_nuc_test(Bind Bd) {
 // One block: candidates in site order; a candidate is blocked by a site fired
 // earlier in the same step when it lies within rc of that site or rounds to
 // that grain's origin site.
-template <class Bind>
-__global__ __launch_bounds__(TPB) void k_nuc_fire(Bind Bd) {
-  Dev D;
-  VGrid V;
-  Bd.bind(D, V);
-  if (dead(D)) return;
-  if (D.cnt->n_cand == 0u) return;
+// Returns the sites fired; *err gets the error of a full store.
+__device__ uint32_t fire_candidates(const Dev& D, uint32_t* err) {
   __shared__ uint32_t list[TPB];
   __shared__ uint32_t wsum[TPB / 64];
   __shared__ uint32_t s_nlist, s_nfired, s_blocked;
@@ -3004,6 +2999,7 @@ __global__ __launch_bounds__(TPB) void k_nuc_fire(Bind Bd) {
         const uint32_t g = ng0 + nf;
         if (g >= D.cap_grains || (uint64_t)n_out + 6ull * (nf + 1) > (uint64_t)D.cap_p) {
           atomicOr(&D.cnt->err, ERR_CAPACITY);
+          *err = ERR_CAPACITY;
         } else {
           float* Gd = D.gtab + (size_t)g * GT_STRIDE;
           for (int k = 0; k < GT_STRIDE; ++k) Gd[k] = T[k];
@@ -3027,10 +3023,10 @@ __global__ __launch_bounds__(TPB) void k_nuc_fire(Bind Bd) {
     }
   }
   if (threadIdx.x == 0) {
-    D.cnt->n_fired = s_nfired;
     D.cnt->n_grains = ng0 + s_nfired;
     D.cnt->nucleated += s_nfired;
   }
+  return s_nfired;
 }
 
 template <class T>
@@ -3039,13 +3035,18 @@ __device__ __forceinline__ T bank_sum(T v) {
   for (int o = 1; o < (int)N_BANKS; o <<= 1) v += __shfl_xor(v, o);
   return v;
 }
-// One wave: the first N_BANKS lanes read a bank each.
+// The end of a step: the candidate sites fire (one block; with sites it has TPB
+// threads), then one wave adds the step's sums, its first N_BANKS lanes a bank
+// each.  Bound by its launch: 3.8 us, as two launches 6.2.
 template <class Bind>
-__global__ __launch_bounds__(64) void k_finish(Bind Bd, double dt) {
+__global__ __launch_bounds__(TPB) void k_finish(Bind Bd, double dt) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
   Counters* c = D.cnt;
+  uint32_t fired = 0, err = c->err;
+  if (D.n_sites != 0u && c->n_cand != 0u && !dead(D)) fired = fire_candidates(D, &err);
+  if (threadIdx.x >= 64u) return;
   Bank b = {};
   if (threadIdx.x < N_BANKS) {
     b = D.bank[threadIdx.x];
@@ -3066,18 +3067,17 @@ __global__ __launch_bounds__(64) void k_finish(Bind Bd, double dt) {
   c->pair_tests += pair_tests;
   c->n_stopped += n_newstop;
   if (max_step > c->max_step) c->max_step = max_step;
-  if (c->err & (ERR_CAPACITY | HOLD)) return;
+  if (err & (ERR_CAPACITY | HOLD)) return;
   // The step's sorted output becomes the next step's input; the step ends.
   c->par ^= 1u;
   c->t = c->t + dt;
   c->step += 1ull;
   c->epoch += 1u;
   if (c->epoch == 0u) c->err |= ERR_CAPACITY;  // brick step stamps exhausted (2^32 steps)
-  c->n_active = c->n_out + 6u * c->n_fired;
-  c->n_live = c->n_out - n_newstop + 6u * c->n_fired;
+  c->n_active = c->n_out + 6u * fired;
+  c->n_live = c->n_out - n_newstop + 6u * fired;
   c->contained += n_newstop;
   c->n_cand = 0;
-  c->n_fired = 0;
 }
 
 template <class Bind>
@@ -4636,9 +4636,10 @@ void launch_stoplink(const Dev& d, hipStream_t s) {
 void launch_nucleate(const Dev& d, hipStream_t s) {
   if (d.n_sites == 0) return;
   k_nuc_test<<<grid_for(d.n_sites, 1024), TPB, 0, s>>>(Plain{d});
-  k_nuc_fire<<<1, TPB, 0, s>>>(Plain{d});
 }
-void launch_finish(const Dev& d, double dt, hipStream_t s) { k_finish<<<1, 64, 0, s>>>(Plain{d}, dt); }
+void launch_finish(const Dev& d, double dt, hipStream_t s) {
+  k_finish<<<1, d.n_sites ? TPB : 64, 0, s>>>(Plain{d}, dt);
+}
 void launch_reset_stats(const Dev& d, hipStream_t s) { k_reset_stats<<<1, 1, 0, s>>>(Plain{d}); }
 void launch_publish(const Dev& d, hipStream_t s) { k_publish<<<1, 64, 0, s>>>(Plain{d}); }
 void launch_stopped_rebuild(const Dev& d, hipStream_t s) {
@@ -4847,9 +4848,8 @@ void launch_batch_step(const BatchLaunch& L, double dt, hipStream_t s) {
   k_stoplink<<<L.site[BS_STOPLINK].total, TPB, 0, s>>>(bind_of(L, BS_STOPLINK));
   if (L.site[BS_NUCTEST].total) {
     k_nuc_test<<<L.site[BS_NUCTEST].total, TPB, 0, s>>>(bind_of(L, BS_NUCTEST));
-    k_nuc_fire<<<L.site[BS_NUCFIRE].total, TPB, 0, s>>>(bind_of(L, BS_NUCFIRE));
   }
-  k_finish<<<one, 64, 0, s>>>(bind_of(L, BS_ONE), dt);
+  k_finish<<<one, L.site[BS_NUCTEST].total ? TPB : 64, 0, s>>>(bind_of(L, BS_ONE), dt);
   k_srb_count<<<L.site[BS_RESORT].total, TPB, 0, s>>>(bind_of(L, BS_RESORT));
   batch_scan(1);
   k_cellscan<<<L.site[BS_CELLSCAN].total, TPB, 0, s>>>(bind_of(L, BS_CELLSCAN));

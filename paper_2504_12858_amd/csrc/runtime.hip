@@ -1976,7 +1976,7 @@ constexpr uint32_t BATCH_MAX_BLOCKS = 65536;  // blocks of one shared launch
 // Tunable kernel of each shared site (-1: fixed site).
 const int SITE_TK[ge::BS_N] = {-1, ge::TK_ADVANCE, -1, ge::TK_BRANCH, -1,
                                ge::TK_CELLSCAN, ge::TK_SCATTER, ge::TK_CHILDREN, ge::TK_DIRTY,
-                               ge::TK_CONTAIN, ge::TK_STOPLINK, -1, -1, -1};
+                               ge::TK_CONTAIN, ge::TK_STOPLINK, -1, -1};
 
 uint32_t tiles_of(const Dev& d) {
   return (uint32_t)((d.n_bricks + ge::SCAN_TILE_HOST - 1) / ge::SCAN_TILE_HOST);
@@ -2013,7 +2013,6 @@ const char* batch_layout(int32_t n, const ge_params* params, BatchLayout& B) {
   const uint32_t share = std::max<uint32_t>(BATCH_MAX_BLOCKS, 8u * (uint32_t)n);
   for (int k = 0; k < ge::BS_N; ++k) B.cap[k] = share;
   B.cap[ge::BS_ONE] = (uint32_t)n;
-  B.cap[ge::BS_NUCFIRE] = (uint32_t)n;
   B.cap[ge::BS_TILES] = (uint32_t)tiles;
   B.cap[ge::BS_RESAMPLE] = (uint32_t)std::max<uint64_t>(resample, 1);
   B.cap[ge::BS_NUCTEST] = (uint32_t)std::max<uint64_t>(nuc, 1);
@@ -2067,7 +2066,6 @@ ge_status batch_bind(ge_batch* b) {
                   ? grid_cap((uint64_t)d.fn[0] * d.fn[1] * d.fn[2], 8192) : 0;
           break;
         case ge::BS_NUCTEST: v = d.n_sites ? grid_cap(d.n_sites, 1024) : 0; break;
-        case ge::BS_NUCFIRE: v = d.n_sites ? 1 : 0; break;
         default: break;
       }
       g[m] = v;
