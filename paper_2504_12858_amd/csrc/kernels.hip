@@ -2044,7 +2044,7 @@ __device__ __forceinline__ void scatter_children(const Dev& D, const VGrid& V) {
 // two alternate (285k active particles: 15 us, one after the other 20, as two
 // launches 24).  Bound by scattered atomics and partly written lines: with runs
 // that spawners end and one atomic per child the 14M took 423 us, with long runs
-// 286.
+// 273.
 template <class Bind>
 __global__ __launch_bounds__(TPB, 8) void k_scatter(Pair<Bind> Bd, uint32_t n_kept, uint32_t n_born) {
   Dev D;
