@@ -492,7 +492,8 @@ ge_status ge_prepare_step(ge_ctx* ctx, double dt);
 ge_status ge_hold(ge_ctx* ctx, int32_t on);
 
 /* Launch schedule: the number of thread blocks (256 threads each) of every
-   tunable kernel of ge_step.  Kernels: advance, branch, cell scan, scatter,
+   tunable kernel of ge_step.  Kernels: advance, branch, cell scan of the
+   stopped store's re-sort, scatter,
    child scatter, dirty-brick pass, containment, stop linking.  The schedule
    changes only speed, never results.  The default, set by ge_create, is the
    number of blocks the device keeps resident at once for each kernel, at most

@@ -163,7 +163,7 @@ struct Dev {
   float* gtab;     // [cap_grains][GT_STRIDE]
   int32_t* gbox;   // [cap_grains][6] lattice bbox of claims: lo xyz, hi xyz
   uint32_t cap_grains;
-  // active store: A is this step's input, B its cell-sorted output, P the
+  // active store: A is this step's input, B its brick-sorted output, P the
   // positions (xyz, grain bits) of B
   uint4* A;
   uint4* B;

@@ -3120,7 +3120,7 @@ __global__ __launch_bounds__(64) void k_publish(Bind Bd) {
 
 // ------------------------------------------------ stopped-store re-sort ---
 // Counting sort of S[0, n_stopped) by cell into S2: counts, brick scan
-// (mode 1), cell scan (mode 1), scatter.  Clears the recent-particle lists.
+// (mode 1), cell scan, scatter.  Clears the recent-particle lists.
 template <class Bind>
 __global__ __launch_bounds__(TPB) void k_srb_count(Bind Bd) {
   Dev D;
