@@ -2833,17 +2833,25 @@ __global__ __launch_bounds__(TPB, 6) void k_contain(Bind Bd) {
 // adds the step's).  A block with stops sums the counts of the regions before
 // its own; one atomic per region on the store's length took 20 ns each, one
 // after another (46 us for 1536 regions at 14M active particles, now 19 us).
+//
+// The blocks leave by the step's count of stops, which this launch does not
+// change and which is zero for a context held or in error, and not by the
+// error word: a full store raises it here, and a block that then left would
+// leave places of the store unwritten that the queries read as records.
 template <class Bind>
 __global__ __launch_bounds__(TPB) void k_stoplink(Bind Bd) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
-  if (dead(D)) return;
   __shared__ uint32_t s_sum[TPB / 64];
   const uint32_t G = D.sched[TK_CONTAIN];
-  uint32_t n = 0;
+  uint32_t n = 0, stops = 0;
 #pragma unroll
-  for (uint32_t q = 0; q < N_BANKS; ++q) n += D.bank[q].n_dpart;
+  for (uint32_t q = 0; q < N_BANKS; ++q) {
+    n += D.bank[q].n_dpart;
+    stops += D.bank[q].n_newstop;
+  }
+  if (!stops) return;
   const uint32_t P = contain_group(n, G);
   const Share rr = regions_of(V, chunk_count(n, P, G));
   uint32_t any = 0;

@@ -123,6 +123,47 @@ def test_particles_per_wave_change_no_decision(seed, n_grains, per_grain, m, spr
     ctx.close()
 
 
+@pytest.mark.parametrize("blocks", [8, 200, 2048])
+def test_full_stopped_store_holds_written_records(blocks):
+    """A step that stops twice as many particles as the stopped store has room
+    for: the error is reported, and the store is full of particles that were
+    stopped before or by this step, each once."""
+    require_gpu()
+    lam = 5e-6
+    centre, quat, parts = _cloud(5, 40, 3000, lam, 12, 0.3, 150e-6)
+    loaded = int((parts["state"] == 1).sum())
+
+    def start(cap):
+        ctx = B.Context(B.make_params((0, 0, 0), (1e-3,) * 3, lam, 2 * lam, lam, W.KIN_A, W.KIN_B,
+                                      branching=0, cap_particles=1 << 18, cap_stopped=cap,
+                                      cap_grains=64, cap_claim_bricks=1 << 12))
+        ctx.set_schedule({"contain": blocks})
+        ctx.set_thermal_field(W.Field(W.FIELD_UNIFORM, dT=3.0))
+        ctx.load_state(centre, quat, parts, EMPTY_CLAIMS, np.zeros(0, np.int32), 0.0, 0)
+        return ctx
+    ctx = start(1 << 18)
+    stops = ctx.step(1e-4, 1)["contained"]
+    assert stops > 1000
+    full, key = gpu_parts(ctx)
+    stopped = key[full["state"] == 1]
+    ctx.close()
+    cap = loaded + stops // 2
+    ctx = start(cap)
+    with pytest.raises(B.GrainEnvError) as e:
+        ctx.step(1e-4, 1)
+    assert e.value.status == B.GE_ECAPACITY
+    q = ctx.particles()
+    q = q[q["state"] == 1]
+    got = ident(q["grain"], q["site"], q["dir"])
+    assert len(got) == cap == len(np.unique(got))
+    assert np.isin(got, stopped).all()
+    # The context is usable again with a state that fits.
+    ctx.load_state(centre, quat, {k: v[:100] for k, v in parts.items()}, EMPTY_CLAIMS,
+                   np.zeros(0, np.int32), 0.0, 0)
+    assert ctx.step(1e-4, 1)["step"] == 1
+    ctx.close()
+
+
 def test_stopped_particles_block_and_survive_steps():
     """A stopped wall of grain 0 stops grain 1's particles arriving later."""
     require_gpu()
