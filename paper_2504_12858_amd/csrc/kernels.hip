@@ -779,6 +779,16 @@ __device__ __forceinline__ bool dead(const Dev& D) {
   return (__hip_atomic_load(&D.cnt->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
           (ERR_CAPACITY | HOLD)) != 0u;
 }
+// The same, taken once for the whole block: in a launch that can raise the
+// error itself the word may change between the loads of two waves of a block,
+// and those that went on would read what the others had not written to LDS.
+// Its barrier also orders what the block wrote to LDS before.
+__device__ __forceinline__ bool block_dead(const Dev& D) {
+  __shared__ uint32_t s_dead;
+  if (threadIdx.x == 0) s_dead = dead(D) ? 1u : 0u;
+  __syncthreads();
+  return s_dead != 0u;
+}
 
 // The context as seen by a kernel of the current step: the launch argument
 // (the same for every step) with the roles of the double-buffered stores set
@@ -1144,7 +1154,7 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
   // Step of an adjoint recording (tagged particles only).
   const int32_t adj_k = REC ? (int32_t)(D.cnt->step - D.adj_step0) : 0;
   if (REC && V.b == 0 && threadIdx.x == 0) D.adj_linc[adj_k] = lin_c;
-  if (dead(D)) return;
+  const uint32_t n = D.cnt->n_active;
   __shared__ uint32_t s_nsp, s_adv, s_exit, s_bad, s_max;
   __shared__ uint3 s_sp[ADV_SP];  // {grain and direction, site words} of the first spawners
   if (threadIdx.x == 0) {
@@ -1154,8 +1164,7 @@ __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
     s_bad = 0;
     s_max = 0;
   }
-  __syncthreads();
-  const uint32_t n = D.cnt->n_active;
+  if (block_dead(D)) return;
   // The totals of the step's brick scan.
   if (V.b == 0 && threadIdx.x == 0) D.cnt->n_out = D.cnt->n_occ = 0u;
   const Chunk ch = chunk_of(V, n, TPB);
@@ -1590,13 +1599,12 @@ __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
-  if (dead(D)) return;
   __shared__ uint32_t s_sp, s_ch;
   if (threadIdx.x == 0) {
     s_sp = 0;
     s_ch = 0;
   }
-  __syncthreads();
+  if (block_dead(D)) return;
   __shared__ uint32_t s_off[STREAM_GRID + 1];
   const SpawnView it = spawn_view<true>(D, V, s_off);
   if (it.begin >= it.end) return;
@@ -1667,13 +1675,14 @@ __global__ __launch_bounds__(TPB) void k_scan(Bind Bd, int mode) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
-  if (dead(D) || (mode == 1 && !resort_due(D))) return;
+  if (mode == 1 && !resort_due(D)) return;
   const uint32_t epoch = step_epoch(D);
   __shared__ unsigned long long wsum[TPB / 64], s_base;
   const uint64_t b0 = ((uint64_t)V.b * TPB + threadIdx.x) * ITEMS;
   uint32_t c[ITEMS];
 #pragma unroll
   for (int k = 0; k < ITEMS; k += 8) load_counts8(D, b0 + k, c + k);
+  if (block_dead(D)) return;
   unsigned long long v = 0;
   uint32_t any = 0;
 #pragma unroll
@@ -1750,7 +1759,7 @@ __global__ __launch_bounds__(TPB) void k_scan_top(Bind Bd, int mode) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
-  if (dead(D) || (mode == 1 && !resort_due(D))) return;
+  if ((mode == 1 && !resort_due(D)) || block_dead(D)) return;
   const uint32_t ntiles = (uint32_t)((D.n_bricks + SCAN_TILE - 1) / SCAN_TILE);
   __shared__ unsigned long long wsum[TPB / 64];
   // Each thread takes a run of consecutive tiles: their sum, one block scan
@@ -3056,7 +3065,7 @@ __global__ __launch_bounds__(TPB) void k_finish(Bind Bd, double dt) {
   Bd.bind(D, V);
   Counters* c = D.cnt;
   uint32_t fired = 0, err = c->err;
-  if (D.n_sites != 0u && c->n_cand != 0u && !dead(D)) fired = fire_candidates(D, &err);
+  if (D.n_sites != 0u && c->n_cand != 0u && !block_dead(D)) fired = fire_candidates(D, &err);
   if (threadIdx.x >= 64u) return;
   Bank b = {};
   if (threadIdx.x < N_BANKS) {
@@ -3493,13 +3502,12 @@ __global__ __launch_bounds__(TPB) void k_walkback(Bind Bd) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
-  if (dead(D)) return;
   const int lane = lane_id();
+  const uint32_t n = D.cnt->n_melt_slots;
   __shared__ uint32_t s_new;
   if (threadIdx.x == 0) s_new = 0;
-  __syncthreads();
+  if (block_dead(D)) return;
   uint32_t made = 0;
-  const uint32_t n = D.cnt->n_melt_slots;
   const uint32_t waves = V.G * (TPB / 64);
   for (uint32_t k = V.b * (TPB / 64) + (threadIdx.x >> 6); k < n; k += waves) {
     const uint64_t slot = D.mslots[k];

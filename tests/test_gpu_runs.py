@@ -172,6 +172,42 @@ def test_claim_capacity_error_is_reported_and_sticky():
     ctx.close()
 
 
+@pytest.mark.parametrize("caps", [dict(cap_particles=18000), dict(cap_claim_bricks=1024)])
+def test_capacity_error_within_a_large_launch(caps):
+    """Two grains of 8838 particles each that reach their next sites in the
+    same step, and the active store (in the brick scan) or the directory of
+    claim blocks (in the branching, 192 blocks) runs out with many blocks of
+    the launch still to start: the error is reported, the particles left are those
+    of the two grains, and the context steps as a new one does once it has
+    loaded a state that fits."""
+    require_gpu()
+    all_caps = dict(cap_particles=1 << 17, cap_stopped=1 << 12, cap_claim_bricks=1 << 14)
+    w = W.single_grain(shell_r=47)
+    w.grain_centre = np.array([[2.5e-4] * 3, [7.5e-4] * 3])
+    w.grain_quat = np.repeat(w.grain_quat, 2, axis=0)
+    w.grain_shell = np.repeat(w.grain_shell, 2)
+    dt = 6e-3  # 0.45 lambda0 per step
+    ctx = context_for(w, **{**all_caps, **caps})
+    with pytest.raises(B.GrainEnvError) as e:
+        for _ in range(12):
+            ctx.step(dt, 1)
+    assert e.value.status == B.GE_ECAPACITY
+    q = ctx.particles()
+    assert (q["grain"] < 2).all() and (q["dir"] < 6).all()
+    assert (np.abs(q["site"].astype(np.int64)).sum(1) <= 52).all()
+    parts = dict(grain=np.zeros(6, np.int32), site=np.zeros((6, 3), np.int32),
+                 dir=np.arange(6, dtype=np.int32), s=np.zeros(6), state=np.zeros(6, np.int32))
+    claims = dict(grain=np.zeros(1, np.int32), site=np.zeros((1, 3), np.int32),
+                  flags=np.full(1, 3, np.uint8))
+    new = context_for(w, **all_caps)
+    for c in (ctx, new):
+        c.load_state(w.grain_centre[:1], w.grain_quat[:1], parts, claims, np.zeros(0, np.int32), 0.0, 0)
+        assert c.step(dt, 40)["children"] > 0
+    assert ctx.digest() == new.digest()
+    ctx.close()
+    new.close()
+
+
 def test_cfl_error():
     require_gpu()
     w = W.nucleus_uniform(lambda0=5e-6, dT=5.0)

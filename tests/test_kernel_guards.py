@@ -32,3 +32,28 @@ def test_places_of_stops_are_all_written():
     body = _functions()["k_stoplink"]
     assert "stopped_put" in body
     assert "dead(" not in body and "->err" not in body
+
+
+def _closure(functions, direct):
+    """Names of the functions whose body, or that of one they call, matches."""
+    found = {n for n, b in functions.items() if re.search(direct, b)}
+    while True:
+        more = {n for n, b in functions.items() if n not in found and
+                any(re.search(r"\b%s(<[^;()]*>)?\(" % f, b) for f in found)}
+        if not more:
+            return found
+        found |= more
+
+
+def test_blocks_take_the_error_word_as_a_whole():
+    """A kernel whose own launch can raise the capacity error, and whose waves
+    share LDS, reads the word once per block: taken wave by wave, some waves
+    of a block could leave and the others read what those had not written."""
+    functions = _functions()
+    functions = {n: b for n, b in functions.items() if n not in ("dead", "block_dead")}
+    raises = _closure(functions, r"\bERR_CAPACITY\b")
+    shares = _closure(functions, r"__syncthreads\(|\bblock_dead\(")
+    assert {"k_advance", "k_branch", "k_scan", "k_stoplink", "k_finish"} <= raises & shares
+    assert "k_scatter" in shares - raises and "k_classify_new" in raises - shares
+    for name in sorted(raises & shares):
+        assert not re.search(r"(?<!block_)\bdead\(", functions[name]), name
