@@ -2971,8 +2971,8 @@ __global__ __launch_bounds__(TPB) void k_nuc_test(Bind Bd) {
 // One block: candidates in site order; a candidate is blocked by a site fired
 // earlier in the same step when it lies within rc of that site or rounds to
 // that grain's origin site.
-// Returns the sites fired; *err gets the error of a full store.
-__device__ uint32_t fire_candidates(const Dev& D, uint32_t* err) {
+// Returns the sites fired.
+__device__ uint32_t fire_candidates(const Dev& D) {
   __shared__ uint32_t list[TPB];
   __shared__ uint32_t wsum[TPB / 64];
   __shared__ uint32_t s_nlist, s_nfired, s_blocked;
@@ -3019,7 +3019,6 @@ __device__ uint32_t fire_candidates(const Dev& D, uint32_t* err) {
         const uint32_t g = ng0 + nf;
         if (g >= D.cap_grains || (uint64_t)n_out + 6ull * (nf + 1) > (uint64_t)D.cap_p) {
           atomicOr(&D.cnt->err, ERR_CAPACITY);
-          *err = ERR_CAPACITY;
         } else {
           float* Gd = D.gtab + (size_t)g * GT_STRIDE;
           for (int k = 0; k < GT_STRIDE; ++k) Gd[k] = T[k];
@@ -3064,9 +3063,12 @@ __global__ __launch_bounds__(TPB) void k_finish(Bind Bd, double dt) {
   VGrid V;
   Bd.bind(D, V);
   Counters* c = D.cnt;
-  uint32_t fired = 0, err = c->err;
-  if (D.n_sites != 0u && c->n_cand != 0u && !block_dead(D)) fired = fire_candidates(D, &err);
+  uint32_t fired = 0;
+  if (D.n_sites != 0u && c->n_cand != 0u && !block_dead(D)) fired = fire_candidates(D);
   if (threadIdx.x >= 64u) return;
+  // After the firing, which may run out of grains, particles or claims: then
+  // the step does not end.
+  const bool stuck = dead(D);
   Bank b = {};
   if (threadIdx.x < N_BANKS) {
     b = D.bank[threadIdx.x];
@@ -3087,7 +3089,7 @@ __global__ __launch_bounds__(TPB) void k_finish(Bind Bd, double dt) {
   c->pair_tests += pair_tests;
   c->n_stopped += n_newstop;
   if (max_step > c->max_step) c->max_step = max_step;
-  if (err & (ERR_CAPACITY | HOLD)) return;
+  if (stuck) return;
   // The step's sorted output becomes the next step's input; the step ends.
   c->par ^= 1u;
   c->t = c->t + dt;

@@ -1,6 +1,7 @@
 """Multi-step GPU runs against the FP64 oracle: scaled directional and CET
 workloads (grain maps agree on >= 99.9% of voxels), nucleation firing steps,
 determinism, and the device error paths."""
+import ctypes as C
 import math
 
 import numpy as np
@@ -206,6 +207,33 @@ def test_capacity_error_within_a_large_launch(caps):
     assert ctx.digest() == new.digest()
     ctx.close()
     new.close()
+
+
+@pytest.mark.parametrize("short", ["claims", "grains", "particles"])
+def test_sites_that_do_not_fit_do_not_end_the_step(short):
+    """Three hundred sites far apart fire in one step, with room for fewer in
+    the directory of claim blocks (192), the grain table or the active store:
+    the error is reported, and the time, the step count and the active
+    particles stay as they were."""
+    require_gpu()
+    caps = dict(cap_grains=200 if short == "grains" else 512,
+                cap_particles=1200 if short == "particles" else 1 << 14,
+                cap_claim_bricks=1024 if short == "claims" else 1 << 14)
+    p = B.make_params((0, 0, 0), (1e-3,) * 3, 5e-6, 5e-6, 5e-6, W.KIN_A, W.KIN_B,
+                      cap_stopped=1 << 14, cap_sites=300, **caps)
+    ctx = B.Context(p)
+    ctx.set_thermal_field(W.Field(W.FIELD_UNIFORM, dT=5.0))
+    ctx.init_grains(np.full((1, 3), 5e-5), np.array([[1.0, 0, 0, 0]]), np.zeros(1, np.int32))
+    before = ctx.step(1e-4, 3)
+    g = W.rng(11)
+    ctx.nucleate(1e-4 + 8e-4 * g.random((300, 3)), np.zeros(300), W.shoemake_quaternions(g, 300))
+    st = B.ge_step_stats()
+    assert ctx.lib.ge_step(ctx.ctx, 1e-4, 1, C.byref(st)) == B.GE_ECAPACITY
+    assert (st.t, st.step, st.n_active) == (before["t"], 3, 6)
+    with pytest.raises(B.GrainEnvError) as e:
+        ctx.step(1e-4, 1)
+    assert e.value.status == B.GE_ESTATE
+    ctx.close()
 
 
 def test_cfl_error():
