@@ -309,8 +309,8 @@ void launch_resample(const Dev& d, hipStream_t s);
 void launch_melt(const Dev& d, hipStream_t s);
 void launch_count_reached(const Dev& d, hipStream_t s);
 // Mushy-zone deposition: counts of every reached site (counts cleared
-// first), and g^m = min(1, count lambda0^3 / cell volume) per cell.
-void launch_deposit_all(const Dev& d, hipStream_t s);
+// first; reach: greatest coordinate of a grain's centre), and g^m = min(1, count lambda0^3 / cell volume) per cell.
+void launch_deposit_all(const Dev& d, double reach, hipStream_t s);
 void launch_mushy_fraction(const uint32_t* cnt, uint64_t n, double site_over_cell, float* out,
                            hipStream_t s);
 // Node undercooling liq_T + liq_m w - T of a SOLUTE field (FP64 in, FP32 out).

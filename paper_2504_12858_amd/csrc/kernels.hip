@@ -4157,12 +4157,16 @@ __global__ __launch_bounds__(TPB) void k_solute_nodes(const double* __restrict__
 // were cleared: one wave per occupied slot of the list of claim keys, a z
 // layer of 64 sites per pass, one site per lane (the bit of a site in its
 // layer word is its lane).  The sites of a slot lie in few cells: the wave
-// counts them in LDS over the box of cells that holds the slot (its centre
-// and half widths, with half a lattice step to spare against rounding) and
-// adds that box to the grid once.  Boxes of more than DEP_BOX cells, and
-// contexts with periodic axes (whose positions wrap), take a table of cells
-// in registers, one cell and its count per lane, filled by one ballot per
-// distinct cell of a layer.
+// counts them in LDS over the box of cells that holds the slot (the cells of
+// the ends of brick_box: rounding keeps the order of positions) and adds that
+// box to the grid once.  Boxes of more than DEP_BOX cells, and contexts without
+// `boxed`, take a table of cells in registers, one cell and its count per lane,
+// filled by one ballot per distinct cell of a layer: contexts with periodic axes
+// (whose positions wrap), and grains so far from the origin that the half
+// lattice step by which brick_box is padded might not cover the rounding of the
+// positions (seven roundings of 2^-24 of up to |c| + 48000 lambda0: 0.1 lambda0
+// at 2 10^5 lambda0; at 10^7 2 % of the sites lie outside the box).  The host
+// decides that: tested here, per slot, it took 16 to 70 us of the 235.
 //
 // Bound by the site arithmetic and the counting.  272k slots (33M sites) of a
 // moving-source state took 2666 us with an atomic on the grid per site and a
@@ -4170,7 +4174,7 @@ __global__ __launch_bounds__(TPB) void k_solute_nodes(const double* __restrict__
 // 250 us now.
 constexpr int DEP_BOX = 256;
 template <class Bind>
-__global__ __launch_bounds__(TPB) void k_deposit_all(Bind Bd) {
+__global__ __launch_bounds__(TPB) void k_deposit_all(Bind Bd, int32_t boxed) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
@@ -4208,7 +4212,7 @@ __global__ __launch_bounds__(TPB) void k_deposit_all(Bind Bd) {
       m[a] = c1 - c0[a] + 1.0f;
       off |= !(m[a] >= 1.0f);
     }
-    if (!D.periodic && (off || m[0] * m[1] * m[2] <= (float)DEP_BOX)) {
+    if (boxed && (off || m[0] * m[1] * m[2] <= (float)DEP_BOX)) {
       if (off) continue;
 #pragma unroll
       for (int z = 0; z < 8; ++z) {
@@ -4677,8 +4681,9 @@ void launch_solute_nodes(const double* T, const double* w, double liq_T, double 
                          uint64_t n, float* out, hipStream_t s) {
   k_solute_nodes<<<grid_for(n, 8192), TPB, 0, s>>>(T, w, liq_T, liq_m, n, out);
 }
-void launch_deposit_all(const Dev& d, hipStream_t s) {
-  k_deposit_all<<<grid_for(d.cmask + 1, 4096), TPB, 0, s>>>(Plain{d});
+void launch_deposit_all(const Dev& d, double reach, hipStream_t s) {
+  const bool boxed = !d.periodic && reach < 2e5 * (double)d.lambda0;
+  k_deposit_all<<<grid_for(d.cmask + 1, 4096), TPB, 0, s>>>(Plain{d}, boxed ? 1 : 0);
 }
 void launch_mushy_fraction(const uint32_t* cnt, uint64_t n, double site_over_cell, float* out,
                            hipStream_t s) {

@@ -249,6 +249,7 @@ struct ge_ctx {
   std::vector<double> site_dT64, site_q64;
   std::vector<double> grain_c64, grain_q64;
   std::vector<uint8_t> grain_host;
+  double reach = 0.0;  // greatest coordinate (magnitude) of a grain or site so far
   bool dead;
   std::string err;
   // phase timing
@@ -606,6 +607,10 @@ ge_status ge_destroy(ge_ctx* c) {
 
 const char* ge_last_error(const ge_ctx* c) { return c ? c->err.c_str() : g_create_err.c_str(); }
 
+static void note_reach(ge_ctx* c, const double* xyz, size_t n) {
+  for (size_t k = 0; k < 3 * n; ++k) c->reach = std::max(c->reach, std::fabs(xyz[k]));
+}
+
 // Keeps the FP64 centre and quaternion of grains g0 .. g0 + n - 1 defined on
 // the host (for saved states).
 static void remember_grains(ge_ctx* c, uint32_t g0, int32_t n, const double* centre,
@@ -670,6 +675,7 @@ ge_status ge_init_grains(ge_ctx* c, int32_t n, const double* centre, const doubl
   const uint32_t na = H.n_active;
   if ((uint64_t)na + recs.size() > (uint64_t)c->p.cap_particles)
     return fail(c, GE_ECAPACITY, "cap_particles exceeded");
+  note_reach(c, centre, (size_t)n);
   hipStream_t s = c->stream;
   HIPCHK(c, hipMemcpyAsync(c->d.gtab + (size_t)g0 * ge::GT_STRIDE, rows.data(),
                            rows.size() * sizeof(float), hipMemcpyHostToDevice, s));
@@ -811,6 +817,7 @@ ge_status ge_nucleate(ge_ctx* c, int32_t n, const double* xyz, const double* dT_
                            rows.size() * sizeof(float), hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipMemsetAsync(c->d.sstate + c->n_sites, 0, 4 * (size_t)n, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  note_reach(c, xyz, (size_t)n);
   c->n_sites += (uint32_t)n;
   c->d.n_sites = c->n_sites;
   c->site_xyz.insert(c->site_xyz.end(), xyz, xyz + 3 * (size_t)n);
@@ -1366,6 +1373,7 @@ static ge_status load_state(ge_ctx* c, const ge_state_in& S, const void* slots, 
   ge_status st = reset_device(c);
   if (st != GE_OK) return st;
   // Grains.
+  note_reach(c, S.centre, (size_t)S.n_grains);
   std::vector<float> rows((size_t)S.n_grains * ge::GT_STRIDE);
   std::vector<int32_t> boxes((size_t)S.n_grains * 6);
   for (int32_t g = 0; g < S.n_grains; ++g) {
@@ -1446,7 +1454,7 @@ static ge_status load_state(ge_ctx* c, const ge_state_in& S, const void* slots, 
   if (c->d.gcnt) {
     // Deposition counts of the loaded claims.
     HIPCHK(c, hipMemsetAsync(c->d.gcnt, 0, 4 * c->dep_nodes, s));
-    ge::launch_deposit_all(c->d, s);
+    ge::launch_deposit_all(c->d, c->reach, s);
   }
   // Reached sites per grain of the loaded claims.
   ge::launch_count_reached(c->d, s);
@@ -1750,7 +1758,7 @@ ge_status ge_set_deposition_grid(ge_ctx* c, const int32_t n[3], const double ori
   c->dep_nodes = nodes;
   c->dep_cell_volume = spacing[0] * spacing[1] * spacing[2];
   HIPCHK(c, hipMemsetAsync(d.gcnt, 0, 4 * nodes, c->stream));
-  ge::launch_deposit_all(d, c->stream);
+  ge::launch_deposit_all(d, c->reach, c->stream);
   HIPCHK(c, hipGetLastError());
   return sync_dev(c);
 }

@@ -87,6 +87,28 @@ def test_recount_matches_the_fp32_checker(cells, inside):
     ctx.close()
 
 
+@pytest.mark.parametrize("cells", [(24, 24, 24), (5, 3, 2)])
+@pytest.mark.parametrize("off", [-1.0, 8.0, 64.0])
+def test_recount_far_from_the_origin(cells, off):
+    """Boxes so far from the origin (up to 1.6e7 site spacings) that a site's
+    position is rounded by as much as the distance between sites."""
+    require_gpu()
+    q = W.shoemake_quaternions(W.rng(11), 3)
+    c = off + np.array([[4e-5, 5e-5, 5e-5], [6e-5, 4e-5, 5e-5], [5e-5, 6e-5, 6e-5]])
+    p = B.make_params((off,) * 3, (off + 1e-4,) * 3, 4e-6, 4e-6, 4e-6, W.KIN_A, W.KIN_B,
+                      cap_particles=1 << 14, cap_stopped=1 << 14, cap_claim_bricks=1 << 12,
+                      field_n=(24, 24, 24))
+    ctx = B.Context(p)
+    ctx.init_grains(c, q, np.array([9, 7, 0], np.int32))
+    spacing = tuple(9e-5 / k for k in cells)
+    origin = tuple(off + 5e-6 + 0.5 * s for s in spacing)
+    ctx.set_deposition_grid(cells, origin, spacing)
+    want = _checker(ctx, cells, origin, spacing)
+    assert want.any()
+    np.testing.assert_array_equal(ctx.mushy_counts(), want)
+    ctx.close()
+
+
 def test_deposition_agrees_with_the_oracle_run():
     require_gpu()
     w = _cet()
