@@ -36,6 +36,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <cstdlib>
 #include <initializer_list>
 #include <mutex>
 
@@ -3999,8 +4000,9 @@ __global__ __launch_bounds__(TPB) void k_claim_slots(Bind Bd, const SlotOut* in,
 //
 // A block takes a tile of MAP_X x 4 ty x 4 tz voxels and lists the grains
 // whose lattice bounding box meets the tile (in the grain's own frame: the
-// tile's centre and half widths there, a lattice step of margin for the
-// rounding to sites and of the arithmetic).  Each sub-tile of 256 voxels, one
+// tile's centre and half widths there, with `slack` lattice steps of margin: one
+// for the rounding to sites and of the arithmetic, and 17 ulps of the
+// coordinates, by which the positions of voxels and tiles may be off).  Each sub-tile of 256 voxels, one
 // per thread, narrows that list in chunks of 256 and tests what is left, in
 // the order of the grains.  Bound by those tests and the directory probes
 // behind them: 408 us for 8M voxels and 760 grains, 22 us for 432k voxels and 8
@@ -4020,7 +4022,7 @@ __device__ __forceinline__ MapEntry map_entry(const Dev& D, uint32_t q) {
   if (!D.periodic) return {q, 13};
   return {q / 27u, (int)(q % 27u)};
 }
-__device__ __forceinline__ bool map_meets(const Dev& D, float inv_l, const MapTile& t, uint32_t q) {
+__device__ __forceinline__ bool map_meets(const Dev& D, float inv_l, float slack, const MapTile& t, uint32_t q) {
   const MapEntry e = map_entry(D, q);
   P3 c = t.c;
   if (D.periodic && !image_of(D, t.c, e.image, c)) return false;
@@ -4031,7 +4033,7 @@ __device__ __forceinline__ bool map_meets(const Dev& D, float inv_l, const MapTi
   for (int k = 0; k < 3; ++k) {
     const float l = (G[4 + k] * dx + G[7 + k] * dy + G[10 + k] * dz) * inv_l;
     const float h = (fabsf(G[4 + k]) * t.h.x + fabsf(G[7 + k]) * t.h.y + fabsf(G[10 + k]) * t.h.z) * inv_l;
-    const float w = 1.0001f * h + 1e-5f * fabsf(l) + 1.0f;
+    const float w = 1.0001f * h + 1e-5f * fabsf(l) + slack;
     if (l + w < (float)bb[k] || l - w > (float)bb[3 + k]) return false;
   }
   return true;
@@ -4056,7 +4058,8 @@ __device__ __forceinline__ uint32_t block_rank(bool take, uint32_t* wcnt, uint32
 template <class Bind>
 __global__ __launch_bounds__(TPB) void k_grain_map(Bind Bd, uint32_t n0, uint32_t n1, uint32_t n2,
                                                    float o0, float o1, float o2, float s0, float s1,
-                                                   float s2, uint32_t ty, uint32_t tz, uint32_t* out) {
+                                                   float s2, float slack, uint32_t ty, uint32_t tz,
+                                                   uint32_t* out) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
@@ -4081,7 +4084,7 @@ __global__ __launch_bounds__(TPB) void k_grain_map(Bind Bd, uint32_t n0, uint32_
     uint32_t n_list = 0;
     for (uint32_t q0 = 0; q0 < ng && n_list <= MAP_LIST; q0 += TPB) {
       const uint32_t q = q0 + threadIdx.x;
-      const bool take = q < ng && map_meets(D, inv_l, T, q);
+      const bool take = q < ng && map_meets(D, inv_l, slack, T, q);
       uint32_t tot;
       const uint32_t r = n_list + block_rank(take, s_cnt, tot);
       if (take && r < MAP_LIST) s_list[r] = q;
@@ -4107,7 +4110,7 @@ __global__ __launch_bounds__(TPB) void k_grain_map(Bind Bd, uint32_t n0, uint32_
         bool take = false;
         if (c0 + threadIdx.x < n_src) {
           q = listed ? s_list[c0 + threadIdx.x] : c0 + threadIdx.x;
-          take = map_meets(D, inv_l, S, q);
+          take = map_meets(D, inv_l, slack, S, q);
         }
         uint32_t n_sub;
         const uint32_t r = block_rank(take, s_cnt, n_sub);
@@ -4799,9 +4802,15 @@ void launch_grain_map(const Dev& d, const int32_t n[3], const float origin[3],
             (uint64_t)((nv[2] + 4u * t - 1u) / (4u * t));
     if (t == 1u || tiles >= 2048u) break;
   }
+  // Greatest coordinate (with periodic axes, of an image) that a voxel's is a
+  // sum of.
+  float reach = 0.0f;
+  for (int a = 0; a < 3; ++a)
+    reach = std::max(reach, std::abs(origin[a]) + (float)n[a] * spacing[a] + d.L[a]);
+  const float slack = 1.0f + 2e-6f * reach / d.lambda0;
   k_grain_map<<<(unsigned)std::min<uint64_t>(tiles, 1u << 20), TPB, 0, s>>>(
       Plain{d}, nv[0], nv[1], nv[2], origin[0], origin[1], origin[2], spacing[0], spacing[1],
-      spacing[2], t, t, out);
+      spacing[2], slack, t, t, out);
 }
 void launch_digest(const Dev& d, unsigned long long* out, hipStream_t s) {
   k_digest<<<2048, TPB, 0, s>>>(Plain{d}, out);

@@ -64,3 +64,46 @@ def test_grain_map_matches_brute_force(n_grains, r, n, periodic):
     assert unsure.mean() < 0.02 + 1e-5 * n_grains
     assert (best > 0).any() or n_grains == 1
     np.testing.assert_array_equal(got[~unsure], best[~unsure])
+
+
+@pytest.mark.parametrize("off,n,part,r", [(-1.0, (37, 18, 23), 1.2, 3), (8.0, (37, 18, 23), 1.2, 1),
+                                          (64.0, (64, 64, 64), 0.3, 0), (64.0, (64, 64, 64), 0.3, 1)])
+def test_grain_map_far_from_the_origin(off, n, part, r):
+    """Boxes so far from the origin (up to 1.3e7 site spacings) that positions
+    are rounded by as much as the distance between sites: every voxel equals
+    the rule in the FP32 arithmetic of the map, tried for every grain."""
+    require_gpu()
+    L, n_grains = 2e-4, 40
+    f4, f8 = np.float32, np.float64
+    g = W.rng(7)
+    c = off + L * (0.05 + 0.9 * g.random((n_grains, 3)))
+    p = B.make_params((off,) * 3, (off + L,) * 3, LAM, LAM, LAM, W.KIN_A, W.KIN_B, cap_particles=1 << 16,
+                      cap_stopped=1 << 16, cap_grains=64, cap_claim_bricks=1 << 12)
+    ctx = B.Context(p)
+    ctx.init_grains(c, W.shoemake_quaternions(g, n_grains), np.full(n_grains, r, np.int32))
+    sp = part * L / np.array(n)
+    lo = np.full(3, off + 0.5 * L * (1 - part))
+    got = ctx.grain_map(n, lo, sp).ravel()
+    rows = ctx.grains()
+    ctx.close()
+
+    def fma(a, b, x):  # the product is exact in FP64
+        return (a.astype(f8) * b.astype(f8) + x.astype(f8)).astype(f4)
+    k, j, i = np.meshgrid(*(np.arange(m) for m in n[::-1]), indexing="ij")
+    ijk = np.stack([i, j, k], -1).reshape(-1, 3).astype(f4)
+    y = lo.astype(f4) + (ijk + f4(0.5)) * sp.astype(f4)
+    best, bd = np.zeros(len(y), int), np.full(len(y), np.inf, f4)
+    for m, G in enumerate(rows):
+        d = y - G[:3]
+        s = np.empty_like(y)
+        for a in range(3):
+            s[:, a] = np.rint(fma(G[10 + a], d[:, 2], fma(G[7 + a], d[:, 1], G[4 + a] * d[:, 0])) *
+                              (f4(1) / f4(LAM)))
+        x = np.stack([fma(G[13 + 3 * a], s[:, 0], fma(G[14 + 3 * a], s[:, 1],
+                                                     fma(G[15 + 3 * a], s[:, 2], G[a]))) for a in range(3)], 1)
+        e = y - x
+        d2 = (e[:, 0] * e[:, 0] + e[:, 1] * e[:, 1]) + e[:, 2] * e[:, 2]
+        win = (np.abs(s).sum(1) <= r) & (d2 < bd)
+        best[win], bd[win] = m + 1, d2[win]
+    assert (best > 0).any()
+    np.testing.assert_array_equal(got, best)
