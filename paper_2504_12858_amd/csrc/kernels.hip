@@ -3998,17 +3998,23 @@ __global__ __launch_bounds__(TPB) void k_claim_slots(Bind Bd, const SlotOut* in,
 // Grain map: voxel centre y takes the grain whose reached site is y's rounded
 // lattice position; nearest such site wins, then the lower grain.
 //
-// A block takes a tile of MAP_X x 4 ty x 4 tz voxels and lists the grains
+// A block takes a tile of ty x tz sub-tiles of 256 voxels, one per thread, each
+// X voxels along x and equally many along y and z, and lists the grains
 // whose lattice bounding box meets the tile (in the grain's own frame: the
 // tile's centre and half widths there, with `slack` lattice steps of margin: one
 // for the rounding to sites and of the arithmetic, and 17 ulps of the
-// coordinates, by which the positions of voxels and tiles may be off).  Each sub-tile of 256 voxels, one
-// per thread, narrows that list in chunks of 256 and tests what is left, in
+// coordinates, by which the positions of voxels and tiles may be off).  Each
+// sub-tile narrows that list in chunks of 256 and tests what is left, in
 // the order of the grains.  Bound by those tests and the directory probes
-// behind them: 408 us for 8M voxels and 760 grains, 22 us for 432k voxels and 8
+// behind them: 406 us for 8M voxels and 760 grains, 22 us for 432k voxels and 8
 // grains with two periodic axes, where the loop over every grain at every
 // voxel took 6057 and 130 us.
-constexpr uint32_t MAP_X = 16, MAP_LIST = 1024;
+//
+// X is 16, and 4 or 1 for grids of at most 8 or 2 voxels along x: lanes past
+// the grid's end wait for the rest of their wave (a 1 x 400 x 400 slice of the 760
+// grains, the whole query: 686 us with 16, 57 with 1, 251 in the
+// loop over every grain).
+constexpr uint32_t MAP_LIST = 1024;
 struct MapTile {
   P3 c, h;  // centre and half widths of the voxel centres
 };
@@ -4055,7 +4061,8 @@ __device__ __forceinline__ uint32_t block_rank(bool take, uint32_t* wcnt, uint32
   return r;
 }
 
-template <class Bind>
+// LX: log2 of X.
+template <class Bind, uint32_t LX>
 __global__ __launch_bounds__(TPB) void k_grain_map(Bind Bd, uint32_t n0, uint32_t n1, uint32_t n2,
                                                    float o0, float o1, float o2, float s0, float s1,
                                                    float s2, float slack, uint32_t ty, uint32_t tz,
@@ -4063,24 +4070,26 @@ __global__ __launch_bounds__(TPB) void k_grain_map(Bind Bd, uint32_t n0, uint32_
   Dev D;
   VGrid V;
   Bd.bind(D, V);
+  constexpr uint32_t X = 1u << LX, LY = (8u - LX) / 2u, Y = 1u << LY;
+  static_assert(X * Y * Y == (uint32_t)TPB, "a voxel per thread");
   __shared__ uint32_t s_list[MAP_LIST], s_sub[TPB], s_cnt[TPB / 64];
   const uint32_t ng = D.cnt->n_grains * (D.periodic ? 27u : 1u);
   const float inv_l = 1.0f / D.lambda0;
-  const uint32_t b0 = (n0 + MAP_X - 1u) / MAP_X, b1 = (n1 + 4u * ty - 1u) / (4u * ty),
-                 b2 = (n2 + 4u * tz - 1u) / (4u * tz);
+  const uint32_t b0 = (n0 + X - 1u) / X, b1 = (n1 + Y * ty - 1u) / (Y * ty),
+                 b2 = (n2 + Y * tz - 1u) / (Y * tz);
   const uint64_t tiles = (uint64_t)b0 * b1 * b2;
   // Tile of nx x ny x nz voxels from voxel (i, j, k).
   auto tile = [&](uint32_t i, uint32_t j, uint32_t k, uint32_t ny, uint32_t nz) {
     MapTile t;
-    t.h = P3{0.5f * (float)(MAP_X - 1u) * s0, 0.5f * (float)(ny - 1u) * s1, 0.5f * (float)(nz - 1u) * s2};
+    t.h = P3{0.5f * (float)(X - 1u) * s0, 0.5f * (float)(ny - 1u) * s1, 0.5f * (float)(nz - 1u) * s2};
     t.c = P3{o0 + ((float)i + 0.5f) * s0 + t.h.x, o1 + ((float)j + 0.5f) * s1 + t.h.y,
              o2 + ((float)k + 0.5f) * s2 + t.h.z};
     return t;
   };
   for (uint64_t v = V.b; v < tiles; v += V.G) {
-    const uint32_t i0 = (uint32_t)(v % b0) * MAP_X, j0 = (uint32_t)((v / b0) % b1) * 4u * ty,
-                   k0 = (uint32_t)(v / ((uint64_t)b0 * b1)) * 4u * tz;
-    const MapTile T = tile(i0, j0, k0, 4u * ty, 4u * tz);
+    const uint32_t i0 = (uint32_t)(v % b0) * X, j0 = (uint32_t)((v / b0) % b1) * Y * ty,
+                   k0 = (uint32_t)(v / ((uint64_t)b0 * b1)) * Y * tz;
+    const MapTile T = tile(i0, j0, k0, Y * ty, Y * tz);
     uint32_t n_list = 0;
     for (uint32_t q0 = 0; q0 < ng && n_list <= MAP_LIST; q0 += TPB) {
       const uint32_t q = q0 + threadIdx.x;
@@ -4095,14 +4104,14 @@ __global__ __launch_bounds__(TPB) void k_grain_map(Bind Bd, uint32_t n0, uint32_
     const bool listed = n_list <= MAP_LIST;
     const uint32_t n_src = listed ? n_list : ng;
     for (uint32_t sub = 0; sub < ty * tz; ++sub) {
-      const uint32_t j1 = j0 + 4u * (sub % ty), k1 = k0 + 4u * (sub / ty);
+      const uint32_t j1 = j0 + Y * (sub % ty), k1 = k0 + Y * (sub / ty);
       if (j1 >= n1 || k1 >= n2) continue;
-      const uint32_t i = i0 + threadIdx.x % MAP_X, j = j1 + ((threadIdx.x / MAP_X) & 3u),
-                     k = k1 + threadIdx.x / (4u * MAP_X);
+      const uint32_t i = i0 + (threadIdx.x & (X - 1u)), j = j1 + ((threadIdx.x >> LX) & (Y - 1u)),
+                     k = k1 + (threadIdx.x >> (LX + LY));
       const bool valid = i < n0 && j < n1 && k < n2;
       const P3 y = {o0 + ((float)i + 0.5f) * s0, o1 + ((float)j + 0.5f) * s1,
                     o2 + ((float)k + 0.5f) * s2};
-      const MapTile S = tile(i0, j1, k1, 4u, 4u);
+      const MapTile S = tile(i0, j1, k1, Y, Y);
       uint32_t best = 0;
       float bd = INFINITY;
       for (uint32_t c0 = 0; c0 < n_src; c0 += TPB) {
@@ -4795,11 +4804,12 @@ void launch_grain_map(const Dev& d, const int32_t n[3], const float origin[3],
   // unit, then 4, then 1 (a list is formed once per block, but the blocks have
   // to fill the chip).
   const uint32_t nv[3] = {(uint32_t)n[0], (uint32_t)n[1], (uint32_t)n[2]};
+  const uint32_t lx = nv[0] > 8u ? 4u : nv[0] > 2u ? 2u : 0u, y = 1u << (8u - lx) / 2u;
   uint32_t t = 4;
   uint64_t tiles = 0;
   for (;; t >>= 1) {
-    tiles = (uint64_t)((nv[0] + MAP_X - 1u) / MAP_X) * (uint64_t)((nv[1] + 4u * t - 1u) / (4u * t)) *
-            (uint64_t)((nv[2] + 4u * t - 1u) / (4u * t));
+    tiles = (uint64_t)((nv[0] + (1u << lx) - 1u) >> lx) * (uint64_t)((nv[1] + y * t - 1u) / (y * t)) *
+            (uint64_t)((nv[2] + y * t - 1u) / (y * t));
     if (t == 1u || tiles >= 2048u) break;
   }
   // Greatest coordinate (with periodic axes, of an image) that a voxel's is a
@@ -4808,9 +4818,14 @@ void launch_grain_map(const Dev& d, const int32_t n[3], const float origin[3],
   for (int a = 0; a < 3; ++a)
     reach = std::max(reach, std::abs(origin[a]) + (float)n[a] * spacing[a] + d.L[a]);
   const float slack = 1.0f + 2e-6f * reach / d.lambda0;
-  k_grain_map<<<(unsigned)std::min<uint64_t>(tiles, 1u << 20), TPB, 0, s>>>(
-      Plain{d}, nv[0], nv[1], nv[2], origin[0], origin[1], origin[2], spacing[0], spacing[1],
-      spacing[2], slack, t, t, out);
+  auto run = [&](auto kernel) {
+    kernel<<<(unsigned)std::min<uint64_t>(tiles, 1u << 20), TPB, 0, s>>>(
+        Plain{d}, nv[0], nv[1], nv[2], origin[0], origin[1], origin[2], spacing[0], spacing[1], spacing[2],
+        slack, t, t, out);
+  };
+  if (lx == 4u) run(k_grain_map<Plain, 4>);
+  else if (lx == 2u) run(k_grain_map<Plain, 2>);
+  else run(k_grain_map<Plain, 0>);
 }
 void launch_digest(const Dev& d, unsigned long long* out, hipStream_t s) {
   k_digest<<<2048, TPB, 0, s>>>(Plain{d}, out);

@@ -107,3 +107,11 @@ def test_grain_map_far_from_the_origin(off, n, part, r):
         best[win], bd[win] = m + 1, d2[win]
     assert (best > 0).any()
     np.testing.assert_array_equal(got, best)
+
+
+@pytest.mark.parametrize("n_grains,r,n,periodic", [
+    (300, 2, (1, 70, 33), 0), (300, 2, (2, 17, 64), 0), (300, 2, (3, 65, 16), 0), (300, 2, (8, 33, 40), 0),
+    (300, 2, (9, 33, 40), 0), (1500, 1, (1, 40, 37), 0), (60, 3, (2, 31, 38), 7), (60, 3, (5, 31, 18), 7)])
+def test_thin_grain_map_matches_brute_force(n_grains, r, n, periodic):
+    """Grids of few voxels along x, whose tiles extend along y and z instead."""
+    test_grain_map_matches_brute_force(n_grains, r, n, periodic)
