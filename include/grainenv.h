@@ -496,8 +496,10 @@ ge_status ge_hold(ge_ctx* ctx, int32_t on);
    stopped store's re-sort, scatter,
    child scatter, dirty-brick pass, containment, stop linking.  The schedule
    changes only speed, never results.  The default, set by ge_create, is the
-   number of blocks the device keeps resident at once for each kernel, at most
-   one per 256 particles of cap_particles.
+   number of blocks the device keeps resident at once for each kernel, but no
+   more than one per 256 particles of cap_particles for the advance and the
+   scatters, and than the greater of that and 512 for the branching, the
+   dirty-brick pass, the containment and the stop linking.
    ge_get_schedule writes the current schedule.  ge_set_schedule takes a new
    one; an entry of 0 keeps the current value; EINVAL for an entry outside
    [1, GE_MAX_BLOCKS].

@@ -4590,10 +4590,20 @@ static inline unsigned grid_for(uint64_t n, unsigned cap = 65535u) {
 // device keeps resident at once (a chunked kernel whose last blocks wait for
 // a second round takes about two block durations), a multiple of the 8 XCDs,
 // at most STREAM_GRID.  For one context (not a batch, whose launches the members
-// share) at most one block per TPB particles of the stores: a block more has
-// work in no state that they hold, and takes its dispatch and prologue all the
-// same (a state of 10k particles in stores of 288k, 208 steps: 7.4 ms with 2048
-// blocks, 6.9 with 1128; 285k particles take 26 ms with either).
+// share) also by its capacities: the advance and the scatters take 256 particles
+// per block and round, so a block more than cap_p / 256 has work in no state that
+// the stores hold, and takes its dispatch and prologue all the same (a state of
+// 10k particles in stores of 288k, 208 steps: 7.4 ms with 2048 blocks in every
+// launch, 6.9 with 1128; 285k particles take 26 ms with either).  The branching,
+// the dirty-brick pass, the containment and the stop linking take down to 32
+// spawners, 4 bricks, 32 particles and one region per block, so that stores with
+// little room to spare would leave them too few blocks: they keep FINE_BLOCKS,
+// two per compute unit (64 steps of 52k active particles in stores of 57k: 6.4 ms
+// with cap_p / 256 blocks, 5.0 with at least 512, 4.8 with 1024, 4.9 with 2048;
+// 192 steps of 3.7k to 58k particles in such stores: 5.7, 5.6, 5.7 and 5.9 ms for
+// the smallest).  The cell scan is the re-sort's, over the stopped particles'
+// bricks, and is not bounded by cap_p.
+constexpr uint32_t FINE_BLOCKS = 512;
 hipError_t resident_grids(Dev& d, bool shared) {
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -4619,7 +4629,9 @@ hipError_t resident_grids(Dev& d, bool shared) {
   const uint32_t useful = std::max<uint32_t>(64u, ((d.cap_p / (uint32_t)TPB) + 8u) / 8u * 8u);
   for (int t = 0; t < TK_N && e == hipSuccess; ++t) {
     e = family({ks[t]}, d.sched[t]);
-    if (!shared) d.sched[t] = std::min(d.sched[t], useful);
+    if (shared || t == TK_CELLSCAN) continue;
+    const bool fine = t == TK_BRANCH || t == TK_DIRTY || t == TK_CONTAIN || t == TK_STOPLINK;
+    d.sched[t] = std::min(d.sched[t], fine ? std::max(useful, FINE_BLOCKS) : useful);
   }
   return e;
 }

@@ -538,3 +538,26 @@ def test_single_step_calls_replayed_or_launched(resort_every):
     assert adv > 0
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("cap", [64, 1 << 14, 1 << 17, (1 << 17) + 1, 1 << 20])
+def test_default_schedule_follows_the_work_per_block(cap):
+    """Kernels that take 256 particles per block have no more blocks than the
+    store can fill; those that take fewer items per block, or work on the
+    stopped store, are not held down by a small one."""
+    require_gpu()
+
+    def schedule(n):
+        p = B.make_params((0, 0, 0), (1e-3,) * 3, 5e-6, 1e-5, 5e-6, W.KIN_A, W.KIN_B,
+                          cap_particles=n, cap_stopped=1 << 16, cap_claim_bricks=1 << 10)
+        ctx = B.Context(p)
+        s = ctx.schedule()
+        ctx.close()
+        return s
+    top, got = schedule(1 << 20), schedule(cap)
+    full = -(-cap // 256)
+    for k in ("advance", "scatter", "children"):
+        assert min(full, top[k]) <= got[k] <= min(max(full + 8, 64), top[k])
+    for k in ("branch", "dirty", "contain", "stoplink"):
+        assert min(max(full, 512), top[k]) <= got[k] <= min(max(full + 8, 512), top[k])
+    assert got["cellscan"] == top["cellscan"]
