@@ -3067,9 +3067,9 @@ __global__ __launch_bounds__(TPB) void k_finish(Bind Bd, double dt) {
   uint32_t fired = 0;
   if (D.n_sites != 0u && c->n_cand != 0u && !block_dead(D)) fired = fire_candidates(D);
   if (threadIdx.x >= 64u) return;
-  // After the firing, which may run out of grains, particles or claims: then
-  // the step does not end.
-  const bool stuck = dead(D);
+  // Read after the firing, which may run out of grains, particles or claims:
+  // then the step does not end.
+  const uint32_t err = __hip_atomic_load(&c->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   Bank b = {};
   if (threadIdx.x < N_BANKS) {
     b = D.bank[threadIdx.x];
@@ -3090,7 +3090,7 @@ __global__ __launch_bounds__(TPB) void k_finish(Bind Bd, double dt) {
   c->pair_tests += pair_tests;
   c->n_stopped += n_newstop;
   if (max_step > c->max_step) c->max_step = max_step;
-  if (stuck) return;
+  if (err & (ERR_CAPACITY | HOLD)) return;
   // The step's sorted output becomes the next step's input; the step ends.
   c->par ^= 1u;
   c->t = c->t + dt;
