@@ -472,18 +472,24 @@ const char* ge_phase_name(int32_t phase);
 ge_status ge_profile_phase(ge_ctx* ctx, int32_t phase);
 
 /* Recorded step sequences.  With graphs on (the default), a ge_step call of
-   at least 2 resort_every steps runs plain steps up to a step count that is
+   at least 2 resort_every steps takes single steps up to a step count that is
    a multiple of resort_every, then replays a recorded hipGraph of
-   resort_every steps (one launch each), then the remaining steps plain.
+   resort_every steps (one launch each), then takes the remaining steps singly,
+   as shorter calls do.  A single step that no re-sort follows is replayed from
+   a graph of its own once ge_prepare_step has recorded it or eight such steps
+   in a row had the same launch arguments and time step; others, and all steps
+   on a stream that is being captured, are launched kernel by kernel.  If the
+   single step cannot be recorded, it is launched as well.
    Every argument of every kernel is the same from step to step (the step
    state lives in device memory), so replays give the same results as plain
-   steps.  The recording is made again after any change of the launch
+   steps.  The recordings are made again after any change of the launch
    arguments (schedule, model, field, sites, time step).  Phase profiling
    (ge_profile, ge_profile_phase) runs plain steps.  ge_use_graphs(ctx, 0)
    turns it off. */
 ge_status ge_use_graphs(ge_ctx* ctx, int32_t on);
-/* Records the step sequence for time step dt now, so that the next ge_step
-   call with that dt starts replaying at once. */
+/* Records the step sequence and the single step for time step dt now, so that
+   the next ge_step call with that dt, of one step or of many, starts replaying
+   at once. */
 ge_status ge_prepare_step(ge_ctx* ctx, double dt);
 
 /* Holds (on = 1) or releases (on = 0) a context: while held, its steps

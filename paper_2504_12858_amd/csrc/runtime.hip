@@ -231,7 +231,8 @@ struct ge_ctx {
   uint64_t gversion = 0;
   double gdt = 0.0;
   // one recorded step that is not followed by a re-sort, for calls of a few
-  // steps; recorded once STEP_SEEN such steps in a row had the same arguments
+  // steps; recorded by ge_prepare_step, or once STEP_SEEN such steps in a row had
+  // the same arguments (g1_seen counts them; -1: the recording failed)
   hipGraphExec_t g1exec = nullptr;
   bool g1_valid = false;
   uint64_t g1version = 0;
@@ -933,18 +934,21 @@ static void step_once(ge_ctx* c, double dt) {
 
 // Records n steps of the context from step count h and instantiates them
 // (nothing runs during the recording).
-static ge_status record_steps(ge_ctx* c, double dt, int32_t n, uint64_t h, hipGraphExec_t* out) {
+static hipError_t record_steps(ge_ctx* c, double dt, int32_t n, uint64_t h, hipGraphExec_t* out) {
+  hipError_t e = hipSuccess;
   if (*out) {
-    HIPCHK(c, hipGraphExecDestroy(*out));
+    e = hipGraphExecDestroy(*out);
     *out = nullptr;
   }
-  if (!c->cap_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
+  if (e == hipSuccess && !c->cap_stream)
+    e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
+  if (e != hipSuccess) return e;
   const uint64_t h0 = c->hstep;
   hipStream_t user = c->stream;
   c->stream = c->cap_stream;
   c->hstep = h;
   hipGraph_t g = nullptr;
-  hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
+  e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
     c->capturing = true;
     for (int32_t k = 0; k < n; ++k) step_once(c, dt);
@@ -953,11 +957,12 @@ static ge_status record_steps(ge_ctx* c, double dt, int32_t n, uint64_t h, hipGr
   }
   c->stream = user;
   c->hstep = h0;
-  HIPCHK(c, e);
-  e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(g);
-  HIPCHK(c, e);
-  return GE_OK;
+  if (e == hipSuccess) {
+    e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
+    if (e != hipSuccess) *out = nullptr;
+  }
+  if (g) (void)hipGraphDestroy(g);
+  return e;
 }
 
 // The recorded sequence of resort_every steps, from a step count that is a
@@ -965,19 +970,41 @@ static ge_status record_steps(ge_ctx* c, double dt, int32_t n, uint64_t h, hipGr
 static ge_status ensure_graph(ge_ctx* c, double dt) {
   if (c->graph_valid && c->gversion == c->dev_version && c->gdt == dt) return GE_OK;
   c->graph_valid = false;
-  ge_status st = record_steps(c, dt, c->resort_every, 0, &c->gexec);
-  if (st != GE_OK) return st;
+  HIPCHK(c, record_steps(c, dt, c->resort_every, 0, &c->gexec));
   c->graph_valid = true;
   c->gversion = c->dev_version;
   c->gdt = dt;
   return GE_OK;
 }
 
-// One step by itself: replayed where the same step has come STEP_SEEN times in
-// a row, else launched.  A small state's step takes 34 us on the device, and a
-// call of one step with its counters took 68 us launched and takes 53 replayed.
-// Recording costs a few steps' time and a coupled solver's fields change every
-// few steps, hence the count.
+// Whether the recorded single step is the one of these arguments; with others
+// the count of equal steps starts anew.
+static bool step_recorded(ge_ctx* c, double dt) {
+  if (c->g1version != c->dev_version || c->g1dt != dt) {
+    c->g1_valid = false;
+    c->g1_seen = 0;
+    c->g1version = c->dev_version;
+    c->g1dt = dt;
+  }
+  return c->g1_valid;
+}
+// Records it.  A recording that fails is not tried again for the same arguments:
+// the steps are launched.
+static void record_step(ge_ctx* c, double dt) {
+  c->g1_valid = record_steps(c, dt, 1, 0, &c->g1exec) == hipSuccess;
+  if (!c->g1_valid) {
+    (void)hipGetLastError();
+    c->g1_seen = -1;
+  }
+}
+
+// One step by itself: replayed where ge_prepare_step has recorded it or the same
+// step has come STEP_SEEN times in a row, else launched.  A small state's step
+// takes 34 us on the device, and a call of one step with its counters took 68 us
+// launched and takes 53 replayed.  A recording costs about 40 us of host time and
+// a coupled solver's fields change every few steps, hence the count; at worst,
+// with arguments that change every ten steps, 96 such calls of a larger state
+// take 8.65 ms, with a change every eight (none recorded) 8.25 and with none 8.1.
 static ge_status step_alone(ge_ctx* c, double dt) {
   constexpr int32_t STEP_SEEN = 8;
   const bool resorts = (c->hstep + 1) % (uint64_t)c->resort_every == 0;
@@ -986,17 +1013,7 @@ static ge_status step_alone(ge_ctx* c, double dt) {
     const hipError_t e = hipStreamIsCapturing(c->stream, &cap);
     if (e != hipSuccess) (void)hipGetLastError();
     if (e == hipSuccess && cap == hipStreamCaptureStatusNone) {
-      if (c->g1version != c->dev_version || c->g1dt != dt) {
-        c->g1_valid = false;
-        c->g1_seen = 0;
-        c->g1version = c->dev_version;
-        c->g1dt = dt;
-      }
-      if (!c->g1_valid && ++c->g1_seen > STEP_SEEN) {
-        ge_status st = record_steps(c, dt, 1, 0, &c->g1exec);
-        if (st != GE_OK) return st;
-        c->g1_valid = true;
-      }
+      if (!step_recorded(c, dt) && c->g1_seen >= 0 && ++c->g1_seen > STEP_SEEN) record_step(c, dt);
       if (c->g1_valid) {
         HIPCHK(c, hipGraphLaunch(c->g1exec, c->stream));
         c->hstep += 1;
@@ -1245,7 +1262,10 @@ ge_status ge_prepare_step(ge_ctx* c, double dt) {
   if (!c) return GE_EINVAL;
   if (c->dead) return fail(c, GE_ESTATE, "context unusable after an earlier error");
   if (!(std::isfinite(dt) && dt > 0)) return fail(c, GE_EINVAL, "bad dt");
-  return c->use_graphs ? ensure_graph(c, dt) : GE_OK;
+  if (!c->use_graphs) return GE_OK;
+  const ge_status st = ensure_graph(c, dt);
+  if (st == GE_OK && !step_recorded(c, dt)) record_step(c, dt);
+  return st;
 }
 
 ge_status ge_use_graphs(ge_ctx* c, int32_t on) {

@@ -561,3 +561,34 @@ def test_default_schedule_follows_the_work_per_block(cap):
     for k in ("branch", "dirty", "contain", "stoplink"):
         assert min(max(full, 512), top[k]) <= got[k] <= min(max(full + 8, 512), top[k])
     assert got["cellscan"] == top["cellscan"]
+
+
+def test_single_steps_while_another_stream_is_captured():
+    """A program captures work of its own on one stream while it steps a
+    context on another: the steps (launched, then recorded and replayed) and
+    the captured work are what they are by themselves."""
+    torch = require_gpu()
+    w = W.directional(seed=5, n_grains=4, size=(2e-4, 2e-4, 4e-4), dT0=10.0, dt=5e-4)
+    p = B.params_from_workload(w, cap_particles=1 << 16, cap_stopped=1 << 16, cap_grains=64,
+                               cap_claim_bricks=1 << 12)
+    a, b = B.Context(p, stream=torch.cuda.Stream()), B.Context(p)
+    for c in (a, b):
+        c.init_from_workload(w)
+    x = torch.arange(1000, dtype=torch.float32, device="cuda")
+    y = torch.zeros_like(x)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for k in range(40):
+            y.add_(x)
+            a.step(w.dt, 1, stats=False)
+    b.step(w.dt, 40)
+    assert a.counts()["step"] == 40
+    assert a.digest() == b.digest()
+    for k in range(3):
+        a.step(w.dt, 1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, 40 * (k + 1) * x)
+    a.close()
+    b.close()
