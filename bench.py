@@ -47,7 +47,7 @@ CET_KNOBS = dict(dT0=12.0, lambda0=1e-6, h=2e-6)
 TARGET_ACTIVE = 20_000_000
 HBM_PEAK_GBS = 8000.0
 # Algorithmic bytes per particle update of the whole step at this workload:
-# read state 20, write position and travel 16, write the cell-ordered record
+# read state 20, write position and travel 16, write the brick-ordered record
 # 16, read it in the containment sweep 16, cell key 8, field resample write
 # and gather read 2 x 64 MiB per step over ~20M updates 6.7.
 STEP_BYTES_PER_UPDATE = 83.0
@@ -55,7 +55,7 @@ KERNEL_SOURCES = ("paper_2504_12858_amd/csrc/kernels.hip", "paper_2504_12858_amd
 
 # Algorithmic bytes per unit of each phase (what the method must move):
 #   advance  : read and write the 16-B record of each active particle
-#   scatter  : read a record, write it and its 16-B position to their cell slot
+#   scatter  : read a record, write it and its 16-B position to their brick's stretch
 #   contain  : read each active position once (neighbours counted in their own cell)
 #   branch   : read and write the spawner's record
 #   resort   : read and write record and position of each stopped particle

@@ -84,7 +84,7 @@ typedef int32_t ge_status;
  * the containment test visits 2^3 cells per particle, otherwise 3^3.
  * Lattice sites must stay within +-16000 of a grain's centre:
  * (box diagonal) / lambda0 < 16000, the extent of a periodic axis counted
- * twice.  Dense per-cell tables take 24 bytes per cell (padded to whole
+ * twice.  Dense per-cell tables take 29 bytes per cell (padded to whole
  * bricks).
  *
  * Periodic axes (Sec. 3.4 imposes periodic conditions on the faces normal
@@ -243,7 +243,11 @@ typedef struct ge_state_in {
 
 typedef struct ge_ctx ge_ctx;
 
-/* Bytes of device workspace the parameters need.  EINVAL on invalid params. */
+/* Bytes of device workspace the parameters need: about 80 per particle of
+   cap_particles (16 of them for the positions, in cell order, of those near
+   another grain), 68 per particle of cap_stopped, 426 per claim brick (their
+   number rounded up to a power of two), 29 per cell, 12.5 per field node, 132
+   per grain and 108 per site.  EINVAL on invalid params. */
 ge_status ge_workspace_size(const ge_params* p, size_t* bytes);
 
 /* Checks the parameters without touching a device. */

@@ -2049,11 +2049,11 @@ __device__ __forceinline__ void scatter_children(const Dev& D, const VGrid& V) {
 // Both scatters in one launch: they write different places and share no other
 // state.  On a large state the children's blocks follow those of the kept
 // particles and fill the chip as these end, finding the bricks' words in the
-// caches (14M active particles: 423 us, as two launches 432; with the children
+// caches (12.8M active particles: 423 us, as two launches 432; with the children
 // first and alternating another 70 and 100).  On a small one the blocks of the
 // two alternate (285k active particles: 15 us, one after the other 20, as two
 // launches 24).  Bound by scattered atomics and partly written lines: with runs
-// that spawners end and one atomic per child the 14M took 423 us, with long runs
+// that spawners end and one atomic per child the 12.8M took 423 us, with long runs
 // 273.
 template <class Bind>
 __global__ __launch_bounds__(TPB, 8) void k_scatter(Pair<Bind> Bd, uint32_t n_kept, uint32_t n_born) {
@@ -2085,8 +2085,8 @@ __global__ __launch_bounds__(TPB, 8) void k_scatter(Pair<Bind> Bd, uint32_t n_ke
 // Bound by instruction issue on a large state (hence the scalar arithmetic of
 // the brick's coordinates), by latency on a small one.  Advance, branching,
 // cell scan, scatter and this kernel together, sorted by cell and by brick: 1232
-// and 1106 us at 14M active particles (this kernel 231 and 234), 88 and 68 us at
-// 285k, 45 and 37 at 4k in a periodic box.
+// and 1106 us at 12.8M active particles (this kernel 231 and 234 on that box, 248
+// on others), 88 and 68 us at 285k, 45 and 37 at 4k in a periodic box.
 template <class Bind>
 __global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
   Dev D;
@@ -2563,7 +2563,7 @@ struct ContainShared {
 // Bound by the latency of its scattered loads, hence as many of them in flight
 // as the registers of six waves per SIMD hold (U cells).  Against one cell's
 // words at a time, each lane writing the sources of its own cells and 64
-// particles in every wave: 315 -> 261 us at 14M active particles (2 x 2 x 2
+// particles in every wave: 315 -> 261 us at 12.8M active particles (2 x 2 x 2
 // cells), 52 -> 21 us at 285k and 43 -> 12 us at 4k (3 x 3 x 3).
 template <bool S8, bool PER>
 __device__ __forceinline__ void contain_body(const Dev& D, const VGrid& V, uint32_t epoch,
@@ -2842,7 +2842,7 @@ __global__ __launch_bounds__(TPB, 6) void k_contain(Bind Bd) {
 // per-block stop lists, behind the n_stopped particles stored so far (k_finish
 // adds the step's).  A block with stops sums the counts of the regions before
 // its own; one atomic per region on the store's length took 20 ns each, one
-// after another (46 us for 1536 regions at 14M active particles, now 19 us).
+// after another (46 us for 1536 regions at 12.8M active particles, now 18 us).
 //
 // The blocks leave by the step's count of stops, which this launch does not
 // change and which is zero for a context held or in error, and not by the
