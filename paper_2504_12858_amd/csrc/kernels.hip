@@ -1676,14 +1676,13 @@ __global__ __launch_bounds__(TPB) void k_scan(Bind Bd, int mode) {
   Dev D;
   VGrid V;
   Bd.bind(D, V);
-  if (mode == 1 && !resort_due(D)) return;
+  if ((mode == 1 && !resort_due(D)) || block_dead(D)) return;
   const uint32_t epoch = step_epoch(D);
   __shared__ unsigned long long wsum[TPB / 64], s_base;
   const uint64_t b0 = ((uint64_t)V.b * TPB + threadIdx.x) * ITEMS;
   uint32_t c[ITEMS];
 #pragma unroll
   for (int k = 0; k < ITEMS; k += 8) load_counts8(D, b0 + k, c + k);
-  if (block_dead(D)) return;
   unsigned long long v = 0;
   uint32_t any = 0;
 #pragma unroll
