@@ -1144,7 +1144,10 @@ __device__ __forceinline__ void stopped_put(const Dev& D, uint32_t j, uint4 r, f
 // and, for the spawners, of the claim slot.  The spawners' records for the
 // marks at the end are kept in LDS, up to ADV_SP per block (a block of a large
 // state has more and reads the rest back).  Per step before and after: 13 -> 9.7
-// us at 4k active particles in a periodic box, 18 -> 17 us at 285k.
+// us at 4k active particles in a periodic box, 18 -> 17 us at 285k.  On a large
+// state the traffic of those loads counts as much (21M active particles, 0.33 ms:
+// 1.06 GB, 3.2 TB/s where a large copy reaches 4.7; vector instructions are
+// issued for 0.12 ms of it).
 constexpr uint32_t ADV_SP = 256;
 template <class Bind, int PM, bool MELT, bool REC>
 __global__ __launch_bounds__(TPB, 8) void k_advance(Bind Bd, float dt) {
@@ -1594,7 +1597,9 @@ __device__ __forceinline__ void branch_alone(const Dev& D, const SpawnView& it, 
 }
 
 // At most 80 registers, for six waves per SIMD: more waves in flight hide
-// more of the latency of the branching's loads and atomics.
+// more of the latency of the branching's loads and atomics (21M active particles,
+// 2.6M spawners, 0.34 ms: 0.68 GB, 2.0 TB/s, 3.4M atomics; waves wait for three
+// quarters of their time).
 template <class Bind>
 __global__ __launch_bounds__(TPB, 6) void k_branch(Bind Bd) {
   Dev D;
@@ -2051,9 +2056,11 @@ __device__ __forceinline__ void scatter_children(const Dev& D, const VGrid& V) {
 // caches (12.8M active particles: 423 us, as two launches 432; with the children
 // first and alternating another 70 and 100).  On a small one the blocks of the
 // two alternate (285k active particles: 15 us, one after the other 20, as two
-// launches 24).  Bound by scattered atomics and partly written lines: with runs
-// that spawners end and one atomic per child the 12.8M took 423 us, with long runs
-// 273.
+// launches 24).  Bound by its traffic in partly written lines and by scattered
+// atomics: with runs that spawners end and one atomic per child the 12.8M took
+// 423 us, with long runs 273.  (21M active particles, 0.46 ms: 1.52 GB for the 1.0
+// of records and positions, 3.3 TB/s where a large copy reaches 4.7, and 2.7M
+// atomics, 6 per ns.)
 template <class Bind>
 __global__ __launch_bounds__(TPB, 8) void k_scatter(Pair<Bind> Bd, uint32_t n_kept, uint32_t n_born) {
   Dev D;
@@ -2081,11 +2088,14 @@ __global__ __launch_bounds__(TPB, 8) void k_scatter(Pair<Bind> Bd, uint32_t n_ke
 // The store itself is sorted by brick alone: about half of the occupied bricks
 // of a grown structure are dirty, and sorting 27 particles in LDS costs less
 // than a count and a rank atomic per cell and a scan of every brick's cells.
-// Bound by instruction issue on a large state (hence the scalar arithmetic of
-// the brick's coordinates), by latency on a small one.  Advance, branching,
-// cell scan, scatter and this kernel together, sorted by cell and by brick: 1232
-// and 1106 us at 12.8M active particles (this kernel 231 and 234 on that box, 248
-// on others), 88 and 68 us at 285k, 45 and 37 at 4k in a periodic box.
+// Bound by latency, on a large state with a third of the time in vector
+// instructions (hence the scalar arithmetic of the brick's coordinates) and
+// traffic at more than half of a copy's rate (21M active particles, 0.41 ms: 86M
+// wave instructions, 0.14 ms of issue; 1.10 GB, 2.7 TB/s; waves wait for half of
+// their time).  Advance, branching, cell scan, scatter and this kernel together,
+// sorted by cell and by brick: 1232 and 1106 us at 12.8M active particles (this
+// kernel 231 and 234 in that run, 248 in later ones), 88 and 68 us at 285k, 45 and
+// 37 at 4k in a periodic box.
 template <class Bind>
 __global__ __launch_bounds__(TPB, 8) void k_dirty(Bind Bd) {
   Dev D;
@@ -2559,8 +2569,10 @@ struct ContainShared {
 // side can come within r_c.  Every particle in such a cell is a candidate: the
 // owner word cannot tell a particle's own period from the next one.
 //
-// Bound by the latency of its scattered loads, hence as many of them in flight
-// as the registers of six waves per SIMD hold (U cells).  Against one cell's
+// Bound by its scattered loads: by their latency, hence as many of them in flight
+// as the registers of six waves per SIMD hold (U cells), and on a large state by
+// their traffic (21M active particles, 0.44 ms: 1.70 GB, 3.9 TB/s where a large
+// copy reaches 4.7; half of the requests miss the L2).  Against one cell's
 // words at a time, each lane writing the sources of its own cells and 64
 // particles in every wave: 315 -> 261 us at 12.8M active particles (2 x 2 x 2
 // cells), 52 -> 21 us at 285k and 43 -> 12 us at 4k (3 x 3 x 3).
